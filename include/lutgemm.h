@@ -10,7 +10,8 @@
  * form, section 3.3 eq. 3; one scale per group of g input columns, section 3.4).
  * The product is evaluated the way section 3.1 describes: every run of mu = 8
  * activations becomes a 2^mu-entry table of signed partial sums, and mu packed weight
- * bits, read as one byte, index that table. Nothing is dequantised.
+ * bits, read as one byte, index that table; for several activation vectors the planes may
+ * be multiplied on the matrix cores instead (lutgemm_gemm). Nothing is dequantised.
  *
  * Conventions shared by every entry point
  *   - Return value: LUTGEMM_OK (0) or a negative LUTGEMM_E* code. Nothing throws,
@@ -116,10 +117,11 @@ enum {
   LUTGEMM_ALPHA_SHARED = 2,
   /* lutgemm_gemm only: let the library take the matrix-core path (lutgemm_gemm_mfma) where
      it measured faster on MI355X and is applicable (group size a multiple of 64, per-plane
-     scales): from five activation vectors on, and from three on layers of at most 2^27
-     weights.  Section 6 of the paper: the lookup path pays per vector, the matrix cores
-     do not.  Either path meets the same tolerance; which one ran is decided by shape and
-     batch only, so results stay reproducible.                                            */
+     scales): from six activation vectors on, from five on layers of less than 2^28 weights, and from
+     three on layers of at most 2^25.  Section 6 of the paper: the lookup path pays per
+     vector, the matrix cores do not.  Up to sixteen vectors the two ways mostly run the same
+     kernel anyway (see lutgemm_gemm).  Either path meets the same tolerance; which one ran is
+     decided by shape and batch only, so results stay reproducible.                       */
   LUTGEMM_PATH_AUTO = 4
 };
 
@@ -236,27 +238,36 @@ int lutgemm_gemv_static(const void* x, const void* bits, const void* alpha, cons
 size_t lutgemm_static_scratch_bytes(void);
 
 /* As lutgemm_gemv for `batch` activation vectors (1 <= batch <= 32): x is fp16
-   [batch][n], y is [batch][m], workspace sized for this batch.  The vectors are taken four
-   at a time; two or one left over have kernels of their own, three left over run as four
-   (the fourth table set repeats the third vector, its results are dropped).  One table set
-   per activation vector, each fetched key looked up in all of them with one LDS read, so
-   the weights are streamed once per four vectors (the small-batch case discussed in
-   section 6).  A vector's result does not depend on the other vectors of the call, only on
-   whether it is processed in a group of four, two or one; between those three it agrees
-   to the documented tolerance, not bit for bit.  Bitwise reproducible from run to run.                                       */
+   [batch][n], y is [batch][m], workspace sized for this batch.  Two kinds of kernel, chosen by
+   shape, batch and group size:
+   - Group sizes that are multiples of 128 columns (g == 0, row-wise, included) and up to six planes:
+     the binary planes on the matrix cores as 4-bit floats, up to sixteen vectors per launch, from
+     three vectors on (two on layers of 256 rows and more, up to 2^28 weights and five planes); odd
+     multiples of 64 columns and up to four planes: the same for five to eight vectors at a
+     time.  Nothing is dequantised and no activation is rounded: each is split into five 6-bit
+     digits of its block of 32 columns, of which it needs no more unless it is 2^14 times
+     smaller than the largest there.
+   - Else lookups: the vectors are taken four at a time; two or one left over have kernels of
+     their own, three left over run as four (the fourth table set repeats the third vector, its
+     results are dropped).  One table set per activation vector, each fetched key looked up in
+     all of them with one LDS read, so the weights are streamed once per four vectors (the
+     small-batch case discussed in section 6).
+   A vector's result does not depend on the values of the other vectors of the call, only on how
+   many are processed with it; between these it agrees to the documented tolerance, not bit for
+   bit.  Bitwise reproducible from run to run.                                             */
 int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void* z, void* y,
                  int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,
                  void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Same arguments, same result (to the same tolerance) as lutgemm_gemm, computed without
-   tables of partial sums: every key byte is expanded to eight values of +-1 and each
-   plane's B_i . X runs on the matrix cores, fp32 accumulation, one multiplication by the
-   scale per group (section 3.2: y = sum_i A_i o (B_i . x); offset term of eq. 3).  Its
-   time does not grow with batch up to 16 vectors, where the lookup path's does (the
-   limitation discussed in section 6), so it is the faster of the two from a batch of
-   three to six, depending on the layer (LUTGEMM_PATH_AUTO).  Requires a group size that is a multiple of 64 columns (g == 0, row-wise,
-   included when n % 64 == 0): LUTGEMM_EUNSUPPORTED otherwise, as is
-   LUTGEMM_ALPHA_SHARED or LUTGEMM_PATH_AUTO.  Bitwise reproducible.                     */
+   tables of partial sums: each plane's B_i . X runs on the matrix cores, fp32 accumulation, one
+   multiplication by the scale per group (section 3.2: y = sum_i A_i o (B_i . x); offset term
+   of eq. 3).  Where lutgemm_gemm takes the whole batch to the 4-bit-float kernel in one launch,
+   this is that kernel; else every key byte is expanded to eight fp16 values of +-1, in a
+   kernel whose time does not grow with batch up to 16 vectors.  Requires a group size that is a
+   multiple of 64 columns (g == 0, row-wise, included when n % 64 == 0):
+   LUTGEMM_EUNSUPPORTED otherwise, as is LUTGEMM_ALPHA_SHARED or LUTGEMM_PATH_AUTO.
+   Bitwise reproducible.                                                                  */
 int lutgemm_gemm_mfma(const void* x, const void* bits, const void* alpha, const void* z, void* y,
                       int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,
                       void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -276,7 +287,8 @@ int lutgemm_gemm_dequant_mfma(const void* x, const void* bits, const void* alpha
                               int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,
                               void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* HOST.  The workgroup grid the lookup kernels are launched with for an m x n layer of q
+/* HOST.  The workgroup grid the lookup kernels are launched with (where they are, see
+   lutgemm_gemm) for an m x n layer of q
    planes and group size g, as chosen from these alone (appendix B: every block owns a tile
    of the weights and a set of tables; the partial outputs of the blocks along a row are
    then combined):

@@ -1160,6 +1160,7 @@ __global__ __launch_bounds__(kThreads) void lutgemm_pair_kernel(GemvParams p) {
 
 #include "lutgemm_quad.h"
 #include "lutgemm_planes_mfma.h"
+#include "lutgemm_planes_fp4.h"
 
 #if !defined(LUT_PART) || LUT_PART == 0
 // Zero the arrival counters of a fresh workspace.
@@ -1196,9 +1197,35 @@ const void* dequant_family(int q, bool has_z, int batch);
 const void* group_family0(int q, int64_t g);
 const void* group_family1(int q, int64_t g);
 const void* group_family2(int q, int64_t g);
+// planes as 4-bit floats; family: 0 no offsets, 1 offsets, 2 shared scales; sb: scale groups per K
+// step; r: operand rows per vector and group
+const void* fp4_family0(int q, int sb, int r);
+const void* fp4_family1(int q, int sb, int r);
+const void* fp4_family2(int q, int sb, int r);
 }  // namespace lutgemm_parts
 
 namespace {
+
+template <int ZM, int SB, int R>
+GemvKernel pick_fp4_q(int q) {   // up to six planes, four where a K step has two scale groups: see fp4_pass
+  switch (q) {
+    case 1: return reinterpret_cast<const void*>(lutgemm_fp4_kernel<1, ZM, SB, R>);
+    case 2: return reinterpret_cast<const void*>(lutgemm_fp4_kernel<2, ZM, SB, R>);
+    case 3: return reinterpret_cast<const void*>(lutgemm_fp4_kernel<3, ZM, SB, R>);
+    case 4: return reinterpret_cast<const void*>(lutgemm_fp4_kernel<4, ZM, SB, R>);
+  }
+  if constexpr (SB == 1) {
+    if (q == 5) return reinterpret_cast<const void*>(lutgemm_fp4_kernel<5, ZM, SB, R>);
+    if (q == 6) return reinterpret_cast<const void*>(lutgemm_fp4_kernel<6, ZM, SB, R>);
+  }
+  return nullptr;
+}
+
+template <int ZM>
+GemvKernel pick_fp4(int q, int sb, int r) {
+  if (sb == 2) return pick_fp4_q<ZM, 2, 1>(q);
+  return r == 4 ? pick_fp4_q<ZM, 1, 4>(q) : (r == 2 ? pick_fp4_q<ZM, 1, 2>(q) : pick_fp4_q<ZM, 1, 1>(q));
+}
 
 template <bool HAS_Z, int AM2, int AM1>
 GemvKernel pick_q(int q) {
@@ -1529,6 +1556,159 @@ void plan_planes_grid(int cus, int waves, int batch, GemvParams* p) {
   }
 }
 
+// ---- planes as 4-bit floats (lutgemm_planes_fp4.h) ----
+
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int kFp4MaxPlanes = 6, kFp4MaxPlanesSplit = 4;   // planes of layers with one and two scale groups per K step
+
+// Scale groups that a K step of 128 columns may touch, 0 if the kernel does not take the group size.
+int fp4_scale_groups(int64_t n, int64_t gg) { return n == gg || gg % 128 == 0 ? 1 : (gg % 64 == 0 ? 2 : 0); }
+
+// Operand rows per (vector, scale group) of a launch for `vectors`.
+int fp4_rows_per_vector(int vectors, int sb) { return sb > 1 || vectors > 8 ? 1 : (vectors > 4 ? 2 : 4); }
+
+// How many of `left` activation vectors one launch of the kernel takes, 0 if they are faster elsewhere
+// (or not for it).  Where the lines lie, old path / this kernel in microseconds (MI355X, weights in no
+// cache):
+//   * One scale group per K step, up to six planes: from three vectors on.  49152 x 12288, q = 3:
+//     75 / 57 at 3 and 4 vectors, 113 / 69 at 8, 123 / 97 at 16; 5120 x 5120, q = 4: 15.1 / 10.1, 14.4 / 11.7,
+//     15.7 / 13.9; 8192 x 8192, q = 6 with offsets: 27 / 19, 48 / 23, 50 / 36.  (The old paths there: lookups
+//     up to four or five vectors, fp16 matrix cores above; the lookups, where asked for, are
+//     2 to 5 times slower from five vectors on.)  At seven and eight planes two units do not fit the
+//     registers: 31 / 42 at q = 8.
+//   * Two vectors: 12288 x 12288 19.7 / 18.7, 15360 x 5120 15.8 / 13.2, 1024 x 1024 7.8 / 6.3, but 36864 x 12288
+//     40.0 / 42.8, 64 x 5120 6.7 / 7.3, 8192 x 8192 with six planes 18 / 23: layers of 256 rows up to
+//     2^28 weights, up to five planes.
+//   * Two scale groups per step take an operand row per vector and group: from five vectors on
+//     (8192 x 22016, q = 3, g = 64: 62 / 36 at 6, 69 / 39 at 8; at four 36 / 41), up to four planes.
+// The offsets formed inside the four row blocks of a unit are 32-bit, hence the bound on groups.
+int fp4_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
+  const int sb = fp4_scale_groups(n, gg);
+  if (sb == 0 || q > (sb == 1 ? kFp4MaxPlanes : kFp4MaxPlanesSplit) || n / gg >= (int64_t)1 << 21) return 0;
+  if (left < (sb == 1 ? 2 : 5)) return 0;
+  if (left == 2 && (q > 5 || m < 256 || m * n > (int64_t)1 << 28)) return 0;
+  const int most = 16 / sb;
+  return left < most ? left : most;
+}
+
+int fp4_lds_bytes(const Fp4Params& p) {
+  const int per_unit = (p.SPG + p.run - 1) / p.run;   // items of a row unit; a single one needs no place for its sums
+  return kFp4FixedBytes + p.SPG * fp4_step_bytes(p.vectors) + (per_unit > 1 ? p.stretch * per_unit * p.vectors * kFp4UnitRows * 4 : 0);
+}
+
+// Grid of one launch: K groups of SPG steps, row ranges (one workgroup per compute unit), K steps per
+// item, row units per stretch.  The least of a cost in microseconds: rounds of items of a workgroup,
+// each as long as its units take with the wavefronts sharing memory and matrix cores, plus the
+// start (digits), the sums of items and the hand-off between K groups.  Constants fitted to 20
+// layers (64 x 38912 to 49152 x 12288, one to six planes, with and without offsets) at 2, 4, 6, 8, 12 and 16 vectors,
+// every K group count and item length timed: the choice is within 2.2 % of the best measured
+// on average, 15 % at worst.  (Constants of such a fit are no physical quantities.)
+void plan_fp4_grid(int cus, int q, bool has_z, int sb, int max_groups, Fp4Params* p) {
+  const int r = fp4_rows_per_vector(p->vectors, sb), chain = (kFp4Digits + r - 1) / r, row_units = (p->RB + 3) / 4;
+  cus = cus > 256 ? 256 : cus;
+  const int step_bytes = fp4_step_bytes(p->vectors);
+  const int most = (kLdsBytes - kFp4FixedBytes) / step_bytes;     // K steps whose digits fit
+  const int products = 4 * q + (has_z ? 1 : 0);
+  const double matrix = products * (r == 4 ? 0.0077 : (r == 2 ? 0.0060 : 0.0074));   // a unit among others, and ...
+  const double memory = (q * 1024 + 128.0 * (q + (has_z ? 1 : 0)) * sb) / 52800.0;
+  const double alone = 0.80 + 0.0046 * products * chain;                               // ... a wavefront by itself
+  double best = 1e30;
+  auto consider = [&](int kg, int pieces) {
+    const int spg = (p->steps + kg - 1) / kg;
+    kg = (p->steps + spg - 1) / spg;
+    if (spg > most || (kg > 1 && kg > max_groups) || pieces > spg) return;
+    const int run = (spg + pieces - 1) / pieces, per_unit = (spg + run - 1) / run;
+    if (run > kFp4MaxRun) return;
+    const int table = kFp4FixedBytes + spg * step_bytes;
+    const int per_row = per_unit > 1 ? per_unit * p->vectors * kFp4UnitRows * 4 : 0;
+    if (table + per_row > kLdsBytes) return;
+    int rs = cus / kg;
+    rs = rs < 1 ? 1 : (rs > row_units ? row_units : rs);
+    const int units = (row_units + rs - 1) / rs;
+    const int room = per_row ? (kLdsBytes - table) / per_row : units;
+    const int stretch = room < units ? room : units;
+    const double workgroups = (double)kg * rs, filled = workgroups < cus ? workgroups / cus : 1.0;
+    const int items = stretch * per_unit;
+    const double rounds = items <= 2 * kFp4Waves ? (items + kFp4Waves - 1) / kFp4Waves : (double)items / kFp4Waves + 0.045;
+    const double shared = matrix > memory * filled ? matrix : memory * filled;
+    const double unit = shared * (items < kFp4Waves ? items : kFp4Waves) > alone ? shared * (items < kFp4Waves ? items : kFp4Waves) : alone;
+    const double tasks = (double)spg * 4 * p->vectors / (64.0 * kFp4Waves);
+    double cost = (workgroups > cus ? workgroups / cus : 1.0) *
+                  (rounds * ((double)units / stretch) * (run * unit + 0.13) + 1.12 * (tasks < 1.0 ? 1.0 : tasks));
+    if (per_unit > 1) cost += 0.55 * ((units + stretch - 1) / stretch) + 0.215 * per_unit * units * p->vectors * 16 / (64.0 * kFp4Waves);
+    if (kg > 1) cost += 0.7 + 1.18 * ((units * ((p->vectors + 3) / 4) + kFp4Waves - 1) / kFp4Waves) * ((kg + 7) / 8);
+    if (cost < best) {
+      best = cost;
+      p->KG = kg;
+      p->SPG = spg;
+      p->run = run;
+      p->row_splits = rs;
+      p->stretch = stretch;
+    }
+  };
+  p->KG = 0;
+  const int first = (p->steps + most - 1) / most;
+  for (int kg = first; kg <= p->steps && (kg == 1 || kg <= max_groups); kg += kg < first + 16 ? 1 : kg / 4)
+    for (int pieces : {1, 2, 3, 4, 6, 8, 16, 32}) consider(kg, pieces);
+  if (p->KG == 0) return;
+  p->range_base = row_units / p->row_splits;
+  p->range_rem = row_units % p->row_splits;
+}
+
+// The grid of a shape, from a small table of the calling thread's last ones (the choice goes through
+// some hundred candidates, several microseconds of host time).
+void fp4_grid(int cus, int q, bool has_z, int sb, int max_groups, Fp4Params* p) {
+  struct Entry {
+    int cus, m, n, key, groups;   // key: planes, offsets, scale groups, vectors (0: empty)
+    Fp4Params grid;
+  };
+  constexpr int kEntries = 32;
+  static thread_local Entry table[kEntries];
+  const int key = 1 + (((q * 2 + (has_z ? 1 : 0)) * 8 + sb) * 64 + p->vectors);
+  const uint64_t h = ((uint64_t)(uint32_t)p->m * 0x9e3779b97f4a7c15ull) ^ ((uint64_t)(uint32_t)p->n * 0xc2b2ae3d27d4eb4full) ^
+                     ((uint64_t)(uint32_t)key * 0x165667b19e3779f9ull);
+  Entry& e = table[(h >> 40) % kEntries];
+  if (e.key != key || e.cus != cus || e.m != p->m || e.n != p->n || e.groups != max_groups) {
+    Fp4Params plan = *p;
+    plan_fp4_grid(cus, q, has_z, sb, max_groups, &plan);
+    e = Entry{cus, p->m, p->n, key, max_groups, plan};
+  }
+  p->KG = e.grid.KG;
+  p->SPG = e.grid.SPG;
+  p->run = e.grid.run;
+  p->stretch = e.grid.stretch;
+  p->row_splits = e.grid.row_splits;
+  p->range_base = e.grid.range_base;
+  p->range_rem = e.grid.range_rem;
+}
+
+// Launches the kernel for p.vectors vectors of a layer.  `max_groups`: K groups whose partials the
+// workspace holds.
+int launch_fp4(int cus, int q, bool shared, int64_t gg, int max_groups, Fp4Params p, hipStream_t stream) {
+  const int sb = fp4_scale_groups(p.n, gg), r = fp4_rows_per_vector(p.vectors, sb);
+  const bool has_z = p.z != nullptr;
+  const GemvKernel kern = shared ? lutgemm_parts::fp4_family2(q, sb, r)
+                                 : (has_z ? lutgemm_parts::fp4_family1(q, sb, r) : lutgemm_parts::fp4_family0(q, sb, r));
+  if (!kern) return LUTGEMM_EUNSUPPORTED;
+  fp4_grid(cus, q, has_z, sb, max_groups, &p);
+  if (p.KG == 0) return LUTGEMM_EUNSUPPORTED;
+  void* args[] = {&p};
+  if (hipLaunchKernel(kern, dim3(p.KG, p.row_splits), dim3(kFp4Waves * 64), args, fp4_lds_bytes(p), stream) != hipSuccess) return LUTGEMM_EHIP;
+  return LUTGEMM_OK;
+}
+
+void fill_fp4_shape(Fp4Params* p, int64_t m, int64_t n, int64_t gg, bool y_f32) {
+  p->m = (int)m;
+  p->n = (int)n;
+  p->RB = (int)((m + 15) / 16);
+  p->nchunks = (int)(n / 8);
+  p->NT = (p->nchunks + 127) / 128;
+  p->steps = (p->nchunks + 15) / 16;
+  p->NG = (int)(n / gg);
+  p->g = (int)gg;
+  p->y_f32 = y_f32 ? 1 : 0;
+}
+
 }  // namespace
 
 namespace lutgemm_parts {
@@ -1573,6 +1753,15 @@ const void* dequant_family(int q, bool has_z, int batch) {
   if (batch <= 16) return has_z ? pick_dequant_q<true, 1>(q) : pick_dequant_q<false, 1>(q);
   return has_z ? pick_dequant_q<true, 2>(q) : pick_dequant_q<false, 2>(q);
 }
+#endif
+#if LUT_HAS_PART(14)
+const void* fp4_family0(int q, int sb, int r) { return pick_fp4<0>(q, sb, r); }
+#endif
+#if LUT_HAS_PART(15)
+const void* fp4_family1(int q, int sb, int r) { return pick_fp4<1>(q, sb, r); }
+#endif
+#if LUT_HAS_PART(16)
+const void* fp4_family2(int q, int sb, int r) { return pick_fp4<2>(q, sb, r); }
 #endif
 #if LUT_HAS_PART(9)
 const void* planes_family(int q, bool has_z, int batch) {
@@ -1674,11 +1863,10 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   if (m > (int64_t)1 << 30 || n > (int64_t)1 << 30) return LUTGEMM_EUNSUPPORTED;
   const bool shared = (flags & LUTGEMM_ALPHA_SHARED) != 0;
   if (shared && !z) return LUTGEMM_EINVAL;   // the shared-scale form always comes with offsets
-  // Measured on MI355X (q = 3, thirteen layer shapes from 4096^2 to 49152 x 12288): the
-  // lookup path costs less than two GEMVs per four vectors, the matrix-core path the same
-  // for any batch up to 16; the lookup path wins up to four vectors (two on layers of at most
-  // 2^25 weights), the two tie at five and six on the layers of more than 2^28 weights, and
-  // the matrix cores win beyond.
+  // The caller lets the library choose: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel
+  // that the loop below takes as well; beyond, the fp16 matrix-core kernel, whose time grows
+  // least: 49152 x 12288 at 32 vectors 166 us against 2 x 93) for six vectors and more, from five on below 2^28
+  // weights, from three on up to 2^25.
   if ((flags & LUTGEMM_PATH_AUTO) != 0 && !shared && gg % 64 == 0 &&
       (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25)))
     return lutgemm_gemm_mfma(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags & LUTGEMM_Y_F32, workspace,
@@ -1716,25 +1904,46 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   // repeating the third vector and its results being dropped (cheaper than a pair plus one).
   GemvParams pq = p, pp = p;
   GemvKernel quad_kern = nullptr, pair_kern = nullptr;
-  if (batch >= 3) {
+  auto plan_quad = [&]() {
+    if (quad_kern) return;
     pq.NT = 4 * p.NT;   // quarter ids; those a ragged last tile does not have are skipped by the kernel
     plan_grid(cus, 4, q, gg, &pq);
     quad_kern = pick_quad_kernel(q, z != nullptr, shared, gg);
-    if (!quad_kern) return LUTGEMM_EUNSUPPORTED;
-  }
-  if (batch % 4 == 2) {
+  };
+  auto plan_pair = [&]() {
     const int last_chunks = p.nchunks - 128 * (p.NT - 1);
     pp.NT = 2 * (p.NT - 1) + (last_chunks > 64 ? 2 : 1);   // half tiles
     plan_grid(cus, 2, q, gg, &pp);
     pair_kern = pick_pair_kernel(q, z != nullptr, shared, gg);
-    if (!pair_kern) return LUTGEMM_EUNSUPPORTED;
-  }
+  };
+  Fp4Params pf = {};
+  pf.bits = p.bits;
+  pf.alpha = p.alpha;
+  pf.z = p.z;
+  pf.kg_stride = p.kg_stride;
+  pf.vec_stride = m_pad;
+  fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
   for (int b = 0; b < batch;) {
     const int left = batch - b;
+    const int pass = fp4_pass(q, m, n, gg, left);
+    if (pass > 0) {
+      pf.x = static_cast<const __half*>(x) + (int64_t)b * n;
+      pf.y = static_cast<char*>(y) + (int64_t)b * m * y_elem;
+      pf.partial = partials + (int64_t)b * m_pad;
+      pf.counters = counters;
+      pf.vectors = pass;
+      const int rc = launch_fp4(cus, q, shared, gg, p.NT * (batch >= 3 ? 4 : 2), pf, stream);
+      if (rc != LUTGEMM_OK) return rc;
+      b += pass;
+      continue;
+    }
     const int take = left >= 3 ? 4 : left;          // kernel width: 4, 2 or 1
     const int live = left >= 4 ? 4 : left;          // vectors it really computes
+    if (take == 4) plan_quad();
+    if (take == 2) plan_pair();
     GemvParams pb = take == 4 ? pq : (take == 2 ? pp : p);
     GemvKernel kb = take == 4 ? quad_kern : (take == 2 ? pair_kern : kern);
+    if (!kb) return LUTGEMM_EUNSUPPORTED;
     pb.x = static_cast<const __half*>(x) + (int64_t)b * n;
     pb.partial = partials + (int64_t)b * m_pad;
     pb.counters = counters + (int64_t)b * 256;
@@ -1781,6 +1990,21 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
   fill_shape(&p, m, n, gg);
   p.batch = batch;
   p.y_f32 = (flags & LUTGEMM_Y_F32) ? 1 : 0;
+  if (!dequant && fp4_pass(q, m, n, gg, batch) == batch) {   // one launch
+    Fp4Params pf = {};
+    pf.x = p.x;
+    pf.bits = p.bits;
+    pf.alpha = p.alpha;
+    pf.z = p.z;
+    pf.y = y;
+    pf.vec_stride = (int64_t)(p.RB + (p.RB & 1)) * 16;
+    pf.kg_stride = pf.vec_stride * (batch + (batch % 4 == 3 ? 1 : 0));
+    pf.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
+    pf.counters = static_cast<uint32_t*>(workspace);
+    pf.vectors = batch;
+    fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
+    return launch_fp4(cus, q, false, gg, p.NT * (batch >= 3 ? 4 : 2), pf, static_cast<hipStream_t>(hip_stream));
+  }
   const int waves = q > 4 ? 4 : 8;
   plan_planes_grid(cus, waves, batch, &p);
   {

@@ -1,0 +1,115 @@
+"""GPU parity of the kernel that multiplies the binary planes as 4-bit floats on the matrix cores
+(two to sixteen activation vectors): at the edges of its row units (64 rows), K steps (128 columns), tiles
+of one and two sub-slabs and vector counts, for every plane count it takes, all scale layouts, and
+for activations its digits do not hold (infinities, NaNs) or hold only just (subnormals beside the
+largest numbers)."""
+import numpy as np
+import pytest
+
+import paper_2206_09557_amd as L
+from oracle import bcq_oracle as O
+from oracle import c_oracle
+from paper_2206_09557_amd import synth
+
+from gpu_util import Packed, check_parity, row_l1_bound, run
+
+pytestmark = pytest.mark.gpu
+
+MODES = {"greedy": L.LUTGEMM_Q_GREEDY, "greedy_z": L.LUTGEMM_Q_GREEDY_MEAN_OFFSET, "rtn": L.LUTGEMM_Q_UNIFORM_RTN}
+
+# m, n, q, g, mode, batch.  One scale group per K step: 4, 2 and 1 operand rows per vector (batch <= 4, <= 8,
+# <= 16), up to six planes; two groups per step (g = 64, 192): batch 5 to 8, up to four planes.
+CASES = [
+    (1, 128, 1, 128, "greedy", 3),           # one row, one K step, one plane
+    (63, 256, 2, 128, "greedy_z", 4),
+    (64, 1024, 3, 128, "greedy", 5),         # exactly one row unit and one tile
+    (65, 1152, 3, 128, "rtn", 8),            # a row more, a last tile of one K step in one sub-slab
+    (129, 1536, 4, 0, "greedy_z", 9),        # last tile with exactly 64 chunks: one sub-slab, four steps
+    (257, 1544, 6, 0, "greedy", 16),         # ... and with 65: two sub-slabs, a step of 8 columns
+    (300, 1032, 5, 0, "rtn", 2),             # row-wise scales on a length no step divides
+    (256, 8, 3, 8, "greedy", 2),             # a single chunk
+    (700, 2048, 6, 256, "greedy_z", 7),
+    (333, 640, 4, 64, "rtn", 5),             # two groups per step
+    (500, 2112, 3, 64, "greedy_z", 8),       # ... the last step holds one of them
+    (130, 4224, 2, 192, "greedy", 13),       # ... groups that straddle steps, eight vectors and five
+    (48, 65536, 3, 128, "greedy_z", 3),      # many K groups on one row unit
+    (20000, 384, 2, 128, "greedy", 12),      # many row units on one K group
+    (4100, 3072, 4, 128, "rtn", 19),         # sixteen vectors and three
+]
+
+
+@pytest.mark.parametrize("m,n,q,g,mode,batch", CASES)
+def test_edges_match_oracle(m, n, q, g, mode, batch):
+    print(f"case fp4 m={m} n={n} q={q} g={g} mode={mode} batch={batch}", flush=True)
+    W = synth.weights_fp16(m, n, seed=16000 + m + 7 * n + q)
+    X = synth.activations_fp16(n, seed=16500 + m + n, batch=batch)
+    p = Packed.from_weights(W, q, g, MODES[mode])
+    gg = n if g == 0 else g
+    z = None if p.z is None else O.decode_z(p.z, m, n // gg)
+    bound = row_l1_bound(O.decode_alpha(p.alpha, m, n // gg, q), z, gg)
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g)
+    y = run(p, X, f32_out=True)
+    for b in range(batch):
+        check_parity(y[b], y_ref[b], X[b], bound, f32_out=True)
+    np.testing.assert_array_equal(y.astype(np.float16), run(p, X))
+    np.testing.assert_array_equal(run(p, X, f32_out=True), y)        # bitwise reproducible
+    if mode == "rtn":                                                # one scale per group: the same bits
+        p.share()
+        np.testing.assert_array_equal(run(p, X, f32_out=True, shared=True), y)
+    if gg % 64 == 0 and 3 <= batch <= 8 and q <= 4:                  # one kernel behind the three ways to ask
+        np.testing.assert_array_equal(run(p, X, f32_out=True, auto=True), run(p, X, f32_out=True, mfma=True))
+
+
+@pytest.mark.parametrize("g,batch", [(128, 4), (128, 8), (128, 16), (64, 8)])
+def test_wide_range_activations(g, batch):
+    # Subnormals, ordinary numbers and the largest ones within one block of 32 columns.  A digit expansion
+    # is off by at most 2^-25 of the block's largest magnitude per activation (16 subnormal bits
+    # of 2^-24 against 6e4 are below that); everything else is exact or an fp32 rounding, of which a sum
+    # of up to 12 steps of 3 planes, added up in 64 bits behind that, has at most 16 in a row:
+    # |error| <= sum(alpha) * (32 * 2^-25 * sum over blocks of the largest + 16 * 2^-24 * |x|_1).
+    m, n, q = 200, 2048, 3
+    W = synth.weights_fp16(m, n, seed=16900)
+    p = Packed.from_weights(W, q, g)
+    X = synth.activations_fp16(n, seed=16901, batch=batch)
+    X[:, ::5] = np.float16(6.0e-8)
+    X[:, 1::37] *= np.float16(1000.0)
+    X[0, 7::64] = np.float16(60000.0)
+    X[1, :] = (np.arange(n) % 1024 + 1).astype(np.float16) * np.float16(2.0 ** -24)   # subnormals alone: exact digits
+    X[2, 2::3] = 0
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g)
+    y = run(p, X, f32_out=True).astype(np.float64)
+    a = O.decode_alpha(p.alpha, m, n // g, q).astype(np.float64).sum(axis=0).max(axis=1)
+    ax = np.abs(X.astype(np.float64))
+    for b in range(batch):
+        limit = a * (32 * 2.0 ** -25 * ax[b].reshape(-1, 32).max(axis=1).sum() + 16 * 2.0 ** -24 * ax[b].sum())
+        assert (np.abs(y[b] - y_ref[b]) <= limit).all(), f"vector {b}: {np.abs(y[b] - y_ref[b]).max()} against {limit.min()}"
+
+
+@pytest.mark.parametrize("n,g,batch,mode", [(2048, 128, 3, "greedy"), (1544, 0, 7, "greedy"), (16384, 128, 16, "greedy_z"), (640, 64, 6, "greedy")])
+def test_infinities_and_nans(n, g, batch, mode):
+    # They reach the rows of their own vector and no other: +-inf where all planes of the column (and a
+    # second one's) agree in sign, else NaN; the other vectors' results stay what they are without them.
+    m, q = 150, 2
+    W = synth.weights_fp16(m, n, seed=17000 + n)
+    p = Packed.from_weights(W, q, g, MODES[mode])
+    B = L.lutgemm_unpack_bcq(p.bits, m, n, q).astype(np.float64)
+    X = synth.activations_fp16(n, seed=17001, batch=batch)
+    clean = run(p, X, f32_out=True)
+    c0, c1 = 5, n - 3
+    X[0, c0] = np.inf
+    X[1, [c0, c1]] = [-np.inf, np.inf]
+    X[2, c1] = np.nan
+    y = run(p, X, f32_out=True)
+    np.testing.assert_array_equal(y[3:], clean[3:])
+    assert np.isnan(y[2]).all()
+    gg = n if g == 0 else g
+    z = np.zeros((m, n // gg)) if p.z is None else O.decode_z(p.z, m, n // gg).astype(np.float64)
+    for v, cols in ((0, [c0]), (1, [c0, c1])):
+        with np.errstate(invalid="ignore"):
+            terms = [s * X[v, c].astype(np.float64) for c in cols for s in (B[0, :, c], B[1, :, c])]
+            if p.z is not None:
+                terms += [z[:, c // gg] * X[v, c].astype(np.float64) for c in cols]
+            want = sum(terms)
+        np.testing.assert_array_equal(np.isnan(y[v]), np.isnan(want))
+        np.testing.assert_array_equal(y[v][~np.isnan(want)], want[~np.isnan(want)])
+        assert np.isinf(y[v]).any() or (p.z is not None)
