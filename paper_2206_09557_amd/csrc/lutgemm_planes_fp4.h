@@ -32,15 +32,15 @@
 // are added by the last workgroup to arrive for a row range, in group order: the result does
 // not depend on who computed what.
 //
-// What bounds it (MI355X, 49152 x 12288, q = 3, g = 128, weights in no cache; before: lookups up to 4 vectors,
-// fp16 matrix cores beyond): 50 us at 2 and 4 vectors (before 54 and 75), 64 at 8 (112), 93 at 16 (118).
-// Up to four vectors the weight stream: 255 MB in the 44 us between the digits (3 us) and the
-// hand-off are 5.8 TB/s.  From there on the matrix cores: an instruction takes 10 ns of a SIMD with
-// random operands (clocks drop with operands that toggle; 7.4 ns with zeros), 5 for 16 vectors x 2048
-// weights, 52 of them per plane and row unit of K step.  Vector instructions run beside them: 13
-// per chain.  8 wavefronts at 256 registers beat 12 at 168 and 16 at 128 (50 against 51 and 110 us, the
-// latter with spills).  A fourth of the K steps' 1 KB key slabs is read at a time, in pieces of 128 bytes:
-// no slower than whole slabs (a copy of the loop without the arithmetic: 7.7 TB/s).
+// What bounds it (MI355X, 49152 x 12288, q = 3, g = 128, weights in no cache; microseconds, before: lookups
+// at 4 vectors, fp16 matrix cores beyond): 57 at 4 vectors (before 72), 69 at 8 (113), 97 at 16 (118).
+// Up to eight vectors mostly the weight stream (255 MB, 38 us at the 6.7 TB/s of a read loop), with
+// 2 to 3 us until the digits stand and 2 to 8 for the hand-off around it.  At 16 the matrix and the
+// vector units together: 4320 matrix instructions per SIMD (10 to 11 ns each with random operands, 7.4
+// with zeros: 45 us) and 20,000 vector instructions, on two wavefronts that hide the one
+// behind the other only in part; the hand-off, 3 MB of partial sums per K group, is most of the
+// rest.  Eight wavefronts at 256 registers: with twelve or sixteen the accumulators spill or it
+// measured slower.
 #pragma once
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
