@@ -1865,7 +1865,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   if (shared && !z) return LUTGEMM_EINVAL;   // the shared-scale form always comes with offsets
   // The caller lets the library choose: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel
   // that the loop below takes as well; beyond, the fp16 matrix-core kernel, whose time grows
-  // least: 49152 x 12288 at 32 vectors 166 us against 2 x 93) for six vectors and more, from five on below 2^28
+  // least: 49152 x 12288 at 32 vectors 167 us against 191 below) for six vectors and more, from five on below 2^28
   // weights, from three on up to 2^25.
   if ((flags & LUTGEMM_PATH_AUTO) != 0 && !shared && gg % 64 == 0 &&
       (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25)))
@@ -1990,7 +1990,13 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
   fill_shape(&p, m, n, gg);
   p.batch = batch;
   p.y_f32 = (flags & LUTGEMM_Y_F32) ? 1 : 0;
-  if (!dequant && fp4_pass(q, m, n, gg, batch) == batch) {   // one launch
+  // Small layers of one or two planes whose groups are long, nine vectors and more, stay with the fp16
+  // operands: there the scaling of two times five matrix instructions per group is what costs, and
+  // the weights are few (3061 x 256, q = 2 row-wise, 10 vectors 5.3 us against 5.6; 193 x 10048, q = 2 row-wise, 16
+  // 10.3 / 10.8; 110 x 6144, q = 1, g = 256, 16 8.5 / 9.1; at 10085 x 1792, q = 1, g = 256, 13 9.2 / 8.5, and at g = 128
+  // 776 x 1920, q = 2, 16 9.7 / 8.5).
+  const bool few_scales = batch > 8 && q <= 2 && gg >= 256 && m * n <= (int64_t)1 << 22;
+  if (!dequant && !few_scales && fp4_pass(q, m, n, gg, batch) == batch) {   // one launch
     Fp4Params pf = {};
     pf.x = p.x;
     pf.bits = p.bits;
