@@ -196,8 +196,7 @@ __device__ __forceinline__ float quad_rows_reduce(const float (&acc)[4], int lan
 //   kAlphaQuad     the four slots of the quad lie in one group (g % (32 * T) == 0): one
 //                  fetch of four rows x q planes serves all the lane's lookups.
 //   kAlphaPerSlot  one fetch per dword (slot); the two chunks of a slot share a group
-//                  (g % 16 == 0, or T == 1).
-//   kAlphaPerChunk one fetch per (dword, sub-slab): g % 16 != 0 with T == 2.
+//                  (g % 16 == 0, or one sub-slab).  (g % 16 == 8 with T == 2: lutgemm_chunk.h.)
 //   kAlphaSlotPair one fetch per pair of slots (g % 32 == 0 with T == 2: slots 2P and 2P + 1
 //                  are 32 columns of one group).  Which of a lane's dwords make a pair depends
 //                  on the lane (its dword s holds slot (s + k) mod 4 of the quad): dwords
@@ -208,7 +207,7 @@ __device__ __forceinline__ float quad_rows_reduce(const float (&acc)[4], int lan
 // Added to any of them, kAlphaShared says that the scale buffer holds ONE value per (row,
 // group), alpha_0, and that plane i has the scale 2^i * alpha_0 (appendix C: the scales of
 // uniformly quantised weights): one fetch of four rows instead of four rows x q planes.
-enum { kAlphaQuad = 0, kAlphaPerSlot = 1, kAlphaPerChunk = 2, kAlphaSlotPair = 3, kAlphaShared = 4 };
+enum { kAlphaQuad = 0, kAlphaPerSlot = 1, kAlphaSlotPair = 3, kAlphaShared = 4 };
 
 // The s-th dword a lane works on, as an index into its fetched key words.
 template <int AMODE>
@@ -223,15 +222,13 @@ __device__ __forceinline__ int dword_of(int s, int lane) {
 template <int Q, int I0, int QP, int T, int AMODE, bool HAS_Z>
 struct Unit {
   static constexpr int NS = ((AMODE & 3) == kAlphaQuad) ? 1 : ((AMODE & 3) == kAlphaSlotPair ? 2 : 4);   // scale sets along the dwords
-  static constexpr int NC = ((AMODE & 3) == kAlphaPerChunk) ? T : 1;             // ... and along the sub-slabs
   u32x4 w[QP][T];           // key words: dword s = four rows of slot 4j + (s + k) mod 4
-  u32x2 al[NS][NC][QP];     // fp16 scales of the lane's four rows
-  u32x2 zz[NS][NC];         // fp16 offsets of the lane's four rows (used when I0 == 0)
-  float prev;               // partial sum of the earlier tiles of this K group (used when I0 == 0)
+  u32x2 al[NS][QP];         // fp16 scales of the lane's four rows
+  u32x2 zz[NS];             // fp16 offsets of the lane's four rows (fetched when I0 == 0)
 };
 
 // Group index of every (dword, sub-slab) of this lane in tile kt.
-template <int T, bool SHIFT = true, int AMODE = kAlphaQuad>
+template <int T, int AMODE = kAlphaQuad>
 __device__ __forceinline__ void lane_groups(const GemvParams& p, int kt, int lane, int chunks_in_tile, int (&grp)[4][T]) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -239,7 +236,7 @@ __device__ __forceinline__ void lane_groups(const GemvParams& p, int kt, int lan
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       const int cc = min(T * slot + t, chunks_in_tile - 1);
-      grp[s][t] = SHIFT ? group_of_chunk(p, 128 * kt + cc) : ((128 * kt + cc) * 8) / p.g;
+      grp[s][t] = group_of_chunk(p, 128 * kt + cc);
     }
   }
 }
@@ -248,8 +245,7 @@ __device__ __forceinline__ void lane_groups(const GemvParams& p, int kt, int lan
 // follows it), so that the wait counters let later fetches stay in flight.
 template <bool SUB = false, int Q, int I0, int QP, int T, int AMODE, bool HAS_Z>
 __device__ __forceinline__ void load_unit(Unit<Q, I0, QP, T, AMODE, HAS_Z>& u, const GemvParams& p, int64_t tile_base,
-                                          int rb, int lane, const int (&grp)[4][T], const float* partial, int out_row,
-                                          bool add_prev, int sub_T = T, int sub_t0 = 0) {
+                                          int rb, int lane, const int (&grp)[4][T], int sub_T = T, int sub_t0 = 0) {
   // SUB: the unit is ONE sub-slab (sub_t0) of a tile laid out with sub_T sub-slabs per plane
   // (the pair kernel); otherwise all T sub-slabs of the tile are fetched.
   using U = Unit<Q, I0, QP, T, AMODE, HAS_Z>;
@@ -261,21 +257,17 @@ __device__ __forceinline__ void load_unit(Unit<Q, I0, QP, T, AMODE, HAS_Z>& u, c
 #pragma unroll
     for (int t = 0; t < T; ++t) u.w[i][t] = __builtin_nontemporal_load(bp + ((I0 + i) * tile_T + t0 + t) * 64);
 #pragma unroll
-  for (int s = 0; s < U::NS; ++s)
+  for (int s = 0; s < U::NS; ++s) {
+    const int64_t blk = (int64_t)rb * p.NG + grp[s * (4 / U::NS) % 4][0];   // first dword of the set
+    if ((AMODE & kAlphaShared) != 0) {   // one scale per (row, group), laid out like the offsets
+      u.al[s][0] = *reinterpret_cast<const u32x2*>(p.alpha + blk * 16 + (lane & 3) * 4);
+    } else {
+      const u32x2* ap = reinterpret_cast<const u32x2*>(p.alpha + ((blk * 4 + (lane & 3)) * Q) * 4);
 #pragma unroll
-    for (int c = 0; c < U::NC; ++c) {
-      const int64_t blk = (int64_t)rb * p.NG + grp[s * (4 / U::NS) % 4][c];   // first dword of the set
-      if ((AMODE & kAlphaShared) != 0) {   // one scale per (row, group), laid out like the offsets
-        u.al[s][c][0] = *reinterpret_cast<const u32x2*>(p.alpha + blk * 16 + (lane & 3) * 4);
-      } else {
-        const u32x2* ap = reinterpret_cast<const u32x2*>(p.alpha + ((blk * 4 + (lane & 3)) * Q) * 4);
-#pragma unroll
-        for (int i = 0; i < QP; ++i) u.al[s][c][i] = ap[I0 + i];
-      }
-      if (HAS_Z && I0 == 0) u.zz[s][c] = *reinterpret_cast<const u32x2*>(p.z + blk * 16 + (lane & 3) * 4);
+      for (int i = 0; i < QP; ++i) u.al[s][i] = ap[I0 + i];
     }
-  // first tile of the K group: nothing to add (the value read is never used)
-  if (I0 == 0) u.prev = add_prev ? load_device_coherent(partial + rb * 16 + out_row) : 0.0f;
+    if (HAS_Z && I0 == 0) u.zz[s] = *reinterpret_cast<const u32x2*>(p.z + blk * 16 + (lane & 3) * 4);
+  }
 }
 
 __device__ __forceinline__ float half_of(const u32x2& v, int j) {   // j-th of the 4 halves
@@ -325,12 +317,10 @@ __device__ __forceinline__ void accumulate_unit(const Unit<Q, I0, QP, T, AMODE, 
           const float v = lds_f32(__builtin_amdgcn_perm(kw[t][s], lane_base[s], sel_t[t]));
           run = run_open ? run + v : v;
           run_open = true;
-          const bool close = ((AMODE & 3) == kAlphaPerChunk) || ((AMODE & 3) == kAlphaPerSlot && t == T - 1) ||
-                             (kPairs && (s & 1) && t == T - 1) || (s == 3 && t == T - 1);
+          const bool close = ((AMODE & 3) == kAlphaPerSlot && t == T - 1) || (kPairs && (s & 1) && t == T - 1) || (s == 3 && t == T - 1);
           if (close) {
             const int ss = ((AMODE & 3) == kAlphaQuad) ? 0 : (kPairs ? s >> 1 : s);
-            const int cc = ((AMODE & 3) == kAlphaPerChunk) ? t : 0;
-            acc[rho] = fmaf(scale_of<AMODE>(u.al[ss][cc], i, I0 + i, rho), run, acc[rho]);
+            acc[rho] = fmaf(scale_of<AMODE>(u.al[ss], i, I0 + i, rho), run, acc[rho]);
             run_open = false;
           }
         }
@@ -339,47 +329,27 @@ __device__ __forceinline__ void accumulate_unit(const Unit<Q, I0, QP, T, AMODE, 
   }
   if (HAS_Z && I0 == 0) {   // offset term of eq. 3: z[r][G] * (sum of the activations of the columns it covers)
 #pragma unroll
-    for (int s = 0; s < U::NS; ++s)
+    for (int s = 0; s < U::NS; ++s) {
+      float sx;
+      if ((AMODE & 3) == kAlphaQuad) {
+        sx = 0.0f;
 #pragma unroll
-      for (int c = 0; c < U::NC; ++c) {
-        float sx;
-        if ((AMODE & 3) == kAlphaQuad) {
-          sx = 0.0f;
+        for (int s2 = 0; s2 < 4; ++s2)
 #pragma unroll
-          for (int s2 = 0; s2 < 4; ++s2)
+          for (int t = 0; t < T; ++t) sx += sum_x[s2][t];
+      } else if ((AMODE & 3) == kAlphaPerSlot) {
+        sx = (T == 2) ? sum_x[s][0] + sum_x[s][T - 1] : sum_x[s][0];
+      } else {
+        sx = 0.0f;
 #pragma unroll
-            for (int t = 0; t < T; ++t) sx += sum_x[s2][t];
-        } else if ((AMODE & 3) == kAlphaPerSlot) {
-          sx = (T == 2) ? sum_x[s][0] + sum_x[s][T - 1] : sum_x[s][0];
-        } else if (kPairs) {
-          sx = 0.0f;
+        for (int s2 = 2 * s; s2 < 2 * s + 2; ++s2)
 #pragma unroll
-          for (int s2 = 2 * s; s2 < 2 * s + 2; ++s2)
-#pragma unroll
-            for (int t = 0; t < T; ++t) sx += sum_x[s2][t];
-        } else {
-          sx = sum_x[s][c];
-        }
-#pragma unroll
-        for (int rho = 0; rho < 4; ++rho) acc[rho] = fmaf(half_of(u.zz[s][c], rho), sx, acc[rho]);
+          for (int t = 0; t < T; ++t) sx += sum_x[s2][t];
       }
+#pragma unroll
+      for (int rho = 0; rho < 4; ++rho) acc[rho] = fmaf(half_of(u.zz[s], rho), sx, acc[rho]);
+    }
   }
-}
-
-// Planes I0, I0+PP, ... of one unit, PP at a time: fetch, then accumulate.
-template <int Q, int I0, int PP, int T, int AMODE, bool HAS_Z>
-__device__ __forceinline__ void plane_passes(const GemvParams& p, int64_t tile_base, int rb, int lane,
-                                             const int (&grp)[4][T], const float* partial, int out_row, bool add_prev,
-                                             const uint32_t (&lane_base)[4], const float (&sum_x)[4][T], float (&acc)[4],
-                                             float* prev) {
-  constexpr int QP = (Q - I0 < PP) ? Q - I0 : PP;
-  Unit<Q, I0, QP, T, AMODE, HAS_Z> u;
-  load_unit(u, p, tile_base, rb, lane, grp, partial, out_row, add_prev);
-  accumulate_unit(u, lane_base, sum_x, acc);
-  if constexpr (I0 == 0) *prev = u.prev;
-  if constexpr (I0 + QP < Q)
-    plane_passes<Q, I0 + QP, PP, T, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, partial, out_row, add_prev, lane_base, sum_x,
-                                                  acc, prev);
 }
 
 // Whole-unit compute for layers fetched in one piece.  Returns the 64-lane sum for the row
@@ -501,36 +471,12 @@ __device__ __forceinline__ void tile_body(const GemvParams& p, float* lut, int k
   const int64_t tile_base = (int64_t)kt * p.RB * Q * 2048;
 
   int grp[4][T];
-  // (the per-chunk scale mode has no registers to spare for the two code paths of the shift)
-  lane_groups<T, (AMODE & 3) != kAlphaPerChunk, AMODE>(p, kt, lane, chunks_in_tile, grp);
+  lane_groups<T, AMODE>(p, kt, lane, chunks_in_tile, grp);
   // the row of the 16-row block whose sum this lane ends up with (see quad_rows_reduce)
   const int out_row = 4 * (lane & 3) + ((lane & 4) ? 2 : 0) + ((lane & 8) ? 1 : 0);
 
-  // Planes fetched together: all of them (up to 8 x 2 x 4 registers of key words: measured 2
-  // to 15 % faster than two halves for five to eight planes); one at a time when every
-  // (dword, sub-slab) has a scale set of its own.  Keeps a wavefront within its registers in
-  // every variant.
-  constexpr int PP = ((AMODE & 3) == kAlphaPerChunk) ? 1 : Q;
-  if constexpr (PP < Q) {
-    // ---- several fetches per unit, no fetch-ahead ----
-    build_slot<T>(lut, chunks_in_tile, wave, lane, fetch_slot_x<T>(p, kt, chunks_in_tile, wave, lane));
-    __syncthreads();
-    uint32_t lane_base[4];
-    float sum_x[4][T];
-    lane_tables<T, HAS_Z, AMODE>(lane, lane_base, sum_x);
-    for (int rb = rb0 + wave; rb < rb1; rb += kWaves) {
-      float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      float prev = 0.0f;
-      // (this register-bound variant has no running sums in LDS: the sum of the
-      // K group's earlier tiles comes back from the workspace with the first fetch of a unit,
-      // always in the wavefront that wrote it, and the new sum goes there again)
-      plane_passes<Q, 0, PP, T, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, partial, out_row, !first_tile, lane_base, sum_x,
-                                              acc, &prev);
-      int row_in_block;
-      const float s = quad_rows_reduce(acc, lane, &row_in_block) + prev;
-      store_row_sum(p, partial, direct, rb * 16 + row_in_block, s);
-    }
-  } else {
+  // All planes are fetched together (up to 8 x 2 x 4 registers of key words: measured 2 to 15 %
+  // faster than two halves for five to eight planes).
   // Units of the workgroup: u = 0 .. n_units-1 (row block rb0 + u).  A wavefront starts with
   // unit `wave` and takes every further one from the queue.  Nothing is fetched ahead of the
   // unit being computed: the other fifteen wavefronts cover a fetch.
@@ -563,13 +509,13 @@ __device__ __forceinline__ void tile_body(const GemvParams& p, float* lut, int k
     }
     __builtin_amdgcn_s_barrier();
     if (!builder) {
-      load_unit(u, p, tile_base, rb0 + min(cur, u_clamp), lane, grp, partial, out_row, false);
+      load_unit(u, p, tile_base, rb0 + min(cur, u_clamp), lane, grp);
     } else {
       build_slot<T>(lut, chunks_in_tile, slot0, lane, xr0);
       build_slot<T>(lut, chunks_in_tile, slot0 + 1, lane, xr1);
     }
     __syncthreads();
-    if (builder) load_unit(u, p, tile_base, rb0 + min(cur, u_clamp), lane, grp, partial, out_row, false);
+    if (builder) load_unit(u, p, tile_base, rb0 + min(cur, u_clamp), lane, grp);
   } else {
     build_slot<T>(lut, chunks_in_tile, wave, lane, fetch_slot_x<T>(p, kt, chunks_in_tile, wave, lane));
     __syncthreads();
@@ -589,7 +535,7 @@ __device__ __forceinline__ void tile_body(const GemvParams& p, float* lut, int k
     int parked_rb = 0, n_parked = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (!kEarly) load_unit(u, p, tile_base, rb0 + cur, lane, grp, partial, out_row, false);
+      if (!kEarly) load_unit(u, p, tile_base, rb0 + cur, lane, grp);
       int row_in_block;
       const float s = compute_unit(u, lane, lane_base, sum_x, &row_in_block);
       parked = (lane_row == j) ? s : parked;
@@ -597,7 +543,7 @@ __device__ __forceinline__ void tile_body(const GemvParams& p, float* lut, int k
       n_parked = j + 1;
       cur = next_unit(lut, lane);
       if (cur >= n_units) break;
-      if (kEarly) load_unit(u, p, tile_base, rb0 + cur, lane, grp, partial, out_row, false);   // no fetch in flight at the exit above
+      if (kEarly) load_unit(u, p, tile_base, rb0 + cur, lane, grp);   // no fetch in flight at the exit above
     }
     if (lane_row < n_parked) {
       if (carry)
@@ -606,7 +552,6 @@ __device__ __forceinline__ void tile_body(const GemvParams& p, float* lut, int k
         store_row_sum(p, partial, direct, parked_rb * 16 + out_row, parked);
     }
   }
-  }   // PP == Q
 }
 
 // Sum over the K groups and store for rows [rb0 * 16, row_end): RPP rows per thread per pass,
@@ -779,18 +724,15 @@ __device__ __forceinline__ void gemv_workgroup(const GemvParams& p, float* lut, 
   float* partial = p.partial + (int64_t)kg * p.kg_stride;
   const bool direct = p.NT == 1;   // one tile, hence one K group: the sums of the tile are y
   const int kt_end = min((kg + 1) * p.TPG, p.NT);
-  // several tiles per K group: running sums in LDS (see carries_in_lds; a last K group with a
+  // several tiles per K group: running sums in LDS (a last K group with a
   // single tile takes the same path as the others)
-  constexpr bool kCarry = (AM2 & 3) != kAlphaPerChunk;
-  const bool carry = kCarry && p.TPG > 1;
+  const bool carry = p.TPG > 1;
 
   for (int kt = kg * p.TPG; kt < kt_end; ++kt) {
     const bool first_tile = kt == kg * p.TPG;
     if (!first_tile) {
       // every lookup of the previous tile is done before its tables are overwritten, every
-      // running sum of it written before it is read (those that go through memory:
-      // acknowledged, as in finish_row_range)
-      if (!kCarry) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      // running sum of it written before it is read
       __syncthreads();
     }
     if (min(128, p.nchunks - 128 * kt) > 64)
@@ -907,13 +849,13 @@ __device__ __forceinline__ void accumulate_pair(const Unit<Q, I0, QP, 1, AMODE, 
     const f32x2(&cur)[4] = e[step & kAhead];
     if ((AMODE & 3) == kAlphaQuad) {   // section 3.2 rule 2: one scale per run of lookups
       const f32x2 run = (cur[0] + cur[1]) + (cur[2] + cur[3]);
-      const float a = scale_of<AMODE>(u.al[0][0], i, I0 + i, rho);
+      const float a = scale_of<AMODE>(u.al[0], i, I0 + i, rho);
       acc[0][rho] = fmaf(a, run.x, acc[0][rho]);
       acc[1][rho] = fmaf(a, run.y, acc[1][rho]);
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const float a = scale_of<AMODE>(u.al[s][0], i, I0 + i, rho);
+        const float a = scale_of<AMODE>(u.al[s], i, I0 + i, rho);
         acc[0][rho] = fmaf(a, cur[s].x, acc[0][rho]);
         acc[1][rho] = fmaf(a, cur[s].y, acc[1][rho]);
       }
@@ -927,7 +869,7 @@ __device__ __forceinline__ void accumulate_pair(const Unit<Q, I0, QP, 1, AMODE, 
       if ((AMODE & 3) == kAlphaQuad) sx = (sum_x[0] + sum_x[1]) + (sum_x[2] + sum_x[3]);
 #pragma unroll
       for (int rho = 0; rho < 4; ++rho) {
-        const float zf = half_of(u.zz[s][0], rho);
+        const float zf = half_of(u.zz[s], rho);
         acc[0][rho] = fmaf(zf, sx.x, acc[0][rho]);
         acc[1][rho] = fmaf(zf, sx.y, acc[1][rho]);
       }
@@ -941,7 +883,7 @@ __device__ __forceinline__ void pair_passes(const GemvParams& p, int64_t tile_ba
                                             const uint32_t (&lane_base)[4], const f32x2 (&sum_x)[4], float (&acc)[2][4]) {
   constexpr int QP = (Q - I0 < PP) ? Q - I0 : PP;
   Unit<Q, I0, QP, 1, AMODE, HAS_Z> u;
-  load_unit<true>(u, p, tile_base, rb, lane, grp, partial, out_row, false, tile_T, t0);
+  load_unit<true>(u, p, tile_base, rb, lane, grp, tile_T, t0);
   accumulate_pair(u, lane_base, sum_x, acc);
   if constexpr (I0 + QP < Q)
     pair_passes<Q, I0 + QP, PP, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, partial, out_row, tile_T, t0, lane_base, sum_x, acc);
@@ -1002,7 +944,7 @@ __device__ __forceinline__ void pair_tile_body(const GemvParams& p, float* lut, 
   if (PP == Q) {
 #pragma unroll
     for (int k = 0; k < D; ++k)
-      load_unit<true>(u[k], p, tile_base, rb0 + min(uid[k], u_clamp), lane, grp, nullptr, out_row, false, tile_T, t0);
+      load_unit<true>(u[k], p, tile_base, rb0 + min(uid[k], u_clamp), lane, grp, tile_T, t0);
   }
 
   // ---- tables: build slot b (of 16) = 16 keys [32 * (b % 8) + 16 * (b / 8), +16) of both vectors ----
@@ -1067,7 +1009,7 @@ __device__ __forceinline__ void pair_tile_body(const GemvParams& p, float* lut, 
         constexpr int kRing = D + 1;
         const int fill = (j + D) % kRing;   // the slot consumed one pass of j ago (for D == 0: this one)
         if (D > 0) uid[fill] = next_unit(lut, lane);
-        load_unit<true>(u[fill], p, tile_base, rb0 + min(uid[fill], u_clamp), lane, grp, nullptr, out_row, false, tile_T, t0);
+        load_unit<true>(u[fill], p, tile_base, rb0 + min(uid[fill], u_clamp), lane, grp, tile_T, t0);
         __builtin_amdgcn_sched_barrier(0);   // the fetch stays ahead of the lookups below
         if (uid[j] < n_units) {
           float acc[2][4] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
@@ -1158,6 +1100,7 @@ __global__ __launch_bounds__(kThreads) void lutgemm_pair_kernel(GemvParams p) {
   finish_row_range<2, (Q <= 4)>(p, lut, rs, rb0, rb1);
 }
 
+#include "lutgemm_chunk.h"
 #include "lutgemm_quad.h"
 #include "lutgemm_planes_mfma.h"
 #include "lutgemm_planes_fp4.h"
@@ -1242,16 +1185,33 @@ GemvKernel pick_q(int q) {
   return nullptr;
 }
 
+template <bool HAS_Z, bool SHARED>
+GemvKernel pick_chunk_q(int q) {
+  switch (q) {
+    case 1: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<1, HAS_Z, SHARED>);
+    case 2: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<2, HAS_Z, SHARED>);
+    case 3: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<3, HAS_Z, SHARED>);
+    case 4: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<4, HAS_Z, SHARED>);
+    case 5: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<5, HAS_Z, SHARED>);
+    case 6: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<6, HAS_Z, SHARED>);
+    case 7: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<7, HAS_Z, SHARED>);
+    case 8: return reinterpret_cast<const void*>(lutgemm_gemv_chunk_kernel<8, HAS_Z, SHARED>);
+  }
+  return nullptr;
+}
+
 template <bool HAS_Z, int SH>
 GemvKernel pick_mode(int q, int64_t g) {
   if (g % 64 == 0) return pick_q<HAS_Z, kAlphaQuad | SH, kAlphaQuad | SH>(q);
   if (g % 32 == 0) return pick_q<HAS_Z, kAlphaSlotPair | SH, kAlphaQuad | SH>(q);
   if (g % 16 == 0) return pick_q<HAS_Z, kAlphaPerSlot | SH, kAlphaPerSlot | SH>(q);
-  return pick_q<HAS_Z, kAlphaPerChunk | SH, kAlphaPerSlot | SH>(q);
+  return pick_chunk_q<HAS_Z, SH != 0>(q);
 }
 
 // shared: the scale buffer is in the shared-scale layout (offsets are then always present)
-GemvKernel pick_kernel(int q, bool has_z, bool shared, int64_t g) {
+// (lanes of a layer of one sub-slab: see scales_per_chunk)
+GemvKernel pick_kernel(int q, bool has_z, bool shared, int64_t n, int64_t g) {
+  if (n <= 512 && g % 16 != 0) g = 16;   // one chunk per dword: a scale set per dword
   if (shared) return lutgemm_parts::gemv_family2(q, g);
   return has_z ? lutgemm_parts::gemv_family1(q, g) : lutgemm_parts::gemv_family0(q, g);
 }
@@ -1381,11 +1341,12 @@ const Tuning& tuning() {
   return t;
 }
 
-// How the GEMV kernel of a (q, g) layer carries row sums from tile to tile of a K group: the
-// variants that fetch a unit in one piece keep them in LDS, which bounds the row range of a
-// workgroup; the register-bound one (a scale set per chunk: g % 16 != 0) sends them through
-// the workspace.
-bool carries_in_lds(int64_t g) { return g % 16 == 0; }
+// Whether the GEMV kernel of a layer is the one with a scale set per chunk (lutgemm_chunk.h).  It walks a
+// row range of any length in stretches; the other's running sums in LDS bound the row range of
+// a workgroup where a K group has several tiles.  A layer of one sub-slab (n <= 512) is faster with
+// the other, whose lanes have one chunk per dword there and hold all planes (4277 x 320, q = 2, g = 8 with
+// offsets 5.2 us against 6.0; 11216 x 456, q = 3, g = 24 5.3 / 5.5; 1422 x 432, q = 4 5.5 / 5.8).
+bool scales_per_chunk(int64_t n, int64_t g) { return g % 16 != 0 && n > 512; }
 
 // Workgroup grid: KG groups of TPG consecutive K tiles times row_splits row ranges, one
 // workgroup per compute unit.  Cost model in units of one round of units of a workgroup (16
@@ -1405,21 +1366,28 @@ bool carries_in_lds(int64_t g) { return g % 16 == 0; }
 // wavefronts fetching, the builders of the tile start only building: 5120 x 5120 at q = 4
 // 9.6 -> 8.8 us, 4096 x 4096 8.0 -> 7.1, 1024 x 1024 5.6 -> 5.0; four units per workgroup
 // are faster still below 2048 x 2048 and slower above.)
-inline int max_row_ranges(int RB) { return (RB + kWaves / 2 - 1) / (kWaves / 2); }
+// With a scale set per chunk a row block is chunk_parts = q + 1 items, and the limit is a full round of
+// items: 3001 x 5160, q = 5, g = 24 at 16 / 24 / 32 / 42 row ranges 16.0 / 12.9 / 11.2 / 10.8 us, 5120 x 5160,
+// q = 8 39.7 / 29.7 / 23.7 / 20.5.
+inline int max_row_ranges(int RB, int chunk_parts) {
+  const int64_t most = chunk_parts ? ((int64_t)RB * chunk_parts + kWaves - 1) / kWaves : (RB + kWaves / 2 - 1) / (kWaves / 2);
+  return (int)(most < RB ? most : RB);
+}
 
-void choose_grid(int cus, int NT, int RB, bool lds_carry, int* KG, int* TPG, int* RS) {
+void choose_grid(int cus, int NT, int RB, int chunk_parts, int* KG, int* TPG, int* RS) {
   double best = 1e30;
-  const int max_rs = max_row_ranges(RB);
+  const int max_rs = max_row_ranges(RB, chunk_parts);
   for (int tpg = 1; tpg <= NT && tpg <= 8; ++tpg) {
     const int kg = (NT + tpg - 1) / tpg;
     int rs = cus / kg;
     rs = rs < 1 ? 1 : (rs > max_rs ? max_rs : rs);
     const int blocks = (RB + rs - 1) / rs;
-    const double rounds = blocks >= 3 * kWaves ? (double)blocks / kWaves : (double)((blocks + kWaves - 1) / kWaves);
+    const int units = chunk_parts ? blocks * chunk_parts : blocks;
+    double rounds = units >= 3 * kWaves ? (double)units / kWaves : (double)((units + kWaves - 1) / kWaves);
+    if (chunk_parts) rounds /= chunk_parts;
     const int tiles = (NT + kg - 1) / kg;
-    if (lds_carry && tpg > 1 && blocks > kRunBlocks) continue;   // the running sums of a row range live in LDS
-    // (the variants that carry sums through memory pay a round trip per tile on top)
-    const double cost = tiles * (rounds + 0.6) + 0.03 * kg + 0.13 * kg * (RB / 3072.0) + (lds_carry ? 0.0 : 0.3 * (tpg - 1));
+    if (!chunk_parts && tpg > 1 && blocks > kRunBlocks) continue;   // the running sums of a row range live in LDS
+    const double cost = tiles * (rounds + 0.6) + 0.03 * kg + 0.13 * kg * (RB / 3072.0);
     if (cost < best) {
       best = cost;
       *KG = kg;
@@ -1467,17 +1435,17 @@ void choose_vector_grid(int vectors, int cus, int NT, int row_units, int* KG, in
 // vectors: 1 (GEMV kernel), 2 (pair kernel), 4 (quad kernel)
 void plan_grid(int cus, int vectors, int q, int64_t g, GemvParams* p) {
   const int wgs = cus > 256 ? 256 : cus;
-  const bool lds_carry = carries_in_lds(g);
+  const int chunk_parts = vectors == 1 && scales_per_chunk(p->n, g) ? q + 1 : 0;   // (whether there are offsets or not: one grid)
   if (vectors == 4)
     choose_vector_grid(4, wgs, p->NT, (p->RB + 1) / 2, &p->KG, &p->TPG, &p->row_splits);
   else if (vectors == 2)
     choose_vector_grid(2, wgs, p->NT, p->RB, &p->KG, &p->TPG, &p->row_splits);
   else
-    choose_grid(wgs, p->NT, p->RB, lds_carry, &p->KG, &p->TPG, &p->row_splits);
+    choose_grid(wgs, p->NT, p->RB, chunk_parts, &p->KG, &p->TPG, &p->row_splits);
   const int which = vectors == 4 ? 2 : (vectors == 2 ? 1 : 0);
   const int tpg = tuning().tpg[which], rs = tuning().rs[which];
   const int row_units = vectors == 4 ? (p->RB + 1) / 2 : p->RB;
-  const int max_rs = vectors == 1 ? max_row_ranges(row_units) : (row_units + kWaves - 1) / kWaves;
+  const int max_rs = vectors == 1 ? max_row_ranges(row_units, chunk_parts) : (row_units + kWaves - 1) / kWaves;
   if (tpg > 0) {
     p->TPG = tpg > p->NT ? p->NT : tpg;
     p->KG = (p->NT + p->TPG - 1) / p->TPG;
@@ -1485,9 +1453,9 @@ void plan_grid(int cus, int vectors, int q, int64_t g, GemvParams* p) {
     p->row_splits = p->row_splits < 1 ? 1 : (p->row_splits > max_rs ? max_rs : p->row_splits);
   }
   if (rs > 0) p->row_splits = rs > 256 ? 256 : (rs > row_units ? row_units : rs);
-  if (vectors == 1 && lds_carry && p->TPG > 1 && (p->RB + p->row_splits - 1) / p->row_splits > kRunBlocks) {
+  if (vectors == 1 && !chunk_parts && p->TPG > 1 && (p->RB + p->row_splits - 1) / p->row_splits > kRunBlocks) {
     // an override that the running sums in LDS do not cover: back to the chooser's own grid
-    choose_grid(wgs, p->NT, p->RB, lds_carry, &p->KG, &p->TPG, &p->row_splits);
+    choose_grid(wgs, p->NT, p->RB, chunk_parts, &p->KG, &p->TPG, &p->row_splits);
   }
 }
 
@@ -1889,9 +1857,9 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   const int64_t m_pad = (int64_t)(p.RB + (p.RB & 1)) * 16;   // an even number of row blocks (the quad kernel works on pairs)
   p.kg_stride = m_pad * (batch + (batch % 4 == 3 ? 1 : 0));   // room for the dropped fourth vector of a quad of three
 
-  GemvKernel kern = pick_kernel(q, z != nullptr, shared, gg);
+  GemvKernel kern = pick_kernel(q, z != nullptr, shared, n, gg);
   if (!kern) return LUTGEMM_EUNSUPPORTED;
-  if (p.TPG > 1 && carries_in_lds(gg) && (p.RB + p.row_splits - 1) / p.row_splits > kRunBlocks)
+  if (p.TPG > 1 && !scales_per_chunk(n, gg) && (p.RB + p.row_splits - 1) / p.row_splits > kRunBlocks)
     return LUTGEMM_EUNSUPPORTED;   // (never planned: the kernel's running sums would not fit)
 
   uint32_t* counters = static_cast<uint32_t*>(workspace);
@@ -2152,14 +2120,12 @@ int lutgemm_gemv_group(const void* const* x, const void* const* bits, const void
     p.y_f32 = (flags & LUTGEMM_Y_F32) ? 1 : 0;
     p.batch = 1;
     plan_grid(cus, 1, q, gg, &p);
-    if (p.TPG > 1 && carries_in_lds(gg) && (p.RB + p.row_splits - 1) / p.row_splits > kRunBlocks)
+    if (p.TPG > 1 && !scales_per_chunk(n[i], gg) && (p.RB + p.row_splits - 1) / p.row_splits > kRunBlocks)
       return LUTGEMM_EUNSUPPORTED;   // (never planned)
     if (p.row_splits > 256) return LUTGEMM_EUNSUPPORTED;   // 256 arrival counters per layer
     const int64_t m_pad = (int64_t)(p.RB + (p.RB & 1)) * 16;
     p.kg_stride = m_pad;
     p.vec_stride = m_pad;
-    p.range_base = p.RB / p.row_splits;
-    p.range_rem = p.RB % p.row_splits;
     p.counters = counters + (size_t)i * 256;
     p.partial = partials;
       const size_t one = lutgemm_workspace_bytes(m[i], n[i], q, g, mu, 1);
@@ -2167,6 +2133,11 @@ int lutgemm_gemv_group(const void* const* x, const void* const* bits, const void
     const size_t part_bytes = (one - kCounterBytes + 255) / 256 * 256;
     partials += part_bytes / sizeof(float);
     used += part_bytes;
+  }
+  for (int i = 0; i < count; ++i) {
+    GemvParams& p = gp.layer[i];
+    p.range_base = p.RB / p.row_splits;
+    p.range_rem = p.RB % p.row_splits;
     const int64_t wgs = (int64_t)p.KG * p.row_splits;
     if (gp.first_wg[i] + wgs > (int64_t)1 << 30) return LUTGEMM_EUNSUPPORTED;
     gp.first_wg[i + 1] = gp.first_wg[i] + (int)wgs;

@@ -77,13 +77,13 @@ __device__ __forceinline__ void accumulate_quad(const Unit<Q, I0, QP, 1, AMODE, 
     const f32x4v(&cur)[4] = e[step & kAhead];
     if ((AMODE & 3) == kAlphaQuad) {   // section 3.2 rule 2: one scale per run of lookups
       const f32x4v run = (cur[0] + cur[1]) + (cur[2] + cur[3]);
-      const float a = scale_of<AMODE>(u.al[0][0], i, I0 + i, rho);
+      const float a = scale_of<AMODE>(u.al[0], i, I0 + i, rho);
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[v][rho] = fmaf(a, run[v], acc[v][rho]);
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const float a = scale_of<AMODE>(u.al[s][0], i, I0 + i, rho);
+        const float a = scale_of<AMODE>(u.al[s], i, I0 + i, rho);
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[v][rho] = fmaf(a, cur[s][v], acc[v][rho]);
       }
@@ -96,7 +96,7 @@ __device__ __forceinline__ void accumulate_quad(const Unit<Q, I0, QP, 1, AMODE, 
       const f32x4v sx = sum_x[s];   // (quad-shared scales: the caller has put the sum over the four slots into sum_x[0])
 #pragma unroll
       for (int rho = 0; rho < 4; ++rho) {
-        const float zf = half_of(u.zz[s][0], rho);
+        const float zf = half_of(u.zz[s], rho);
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[v][rho] = fmaf(zf, sx[v], acc[v][rho]);
       }
@@ -110,7 +110,7 @@ __device__ __forceinline__ void quad_passes(const GemvParams& p, int64_t tile_ba
                                             const uint32_t (&lane_base)[4], const f32x4v (&sum_x)[4], float (&acc)[4][4]) {
   constexpr int QP = (Q - I0 < PP) ? Q - I0 : PP;
   Unit<Q, I0, QP, 1, AMODE, HAS_Z> u;
-  load_unit<true>(u, p, tile_base, rb, slab_lane, grp, partial, out_row, false, tile_T, t0);
+  load_unit<true>(u, p, tile_base, rb, slab_lane, grp, tile_T, t0);
   accumulate_quad(u, lane_base, sum_x, acc);
   if constexpr (I0 + QP < Q)
     quad_passes<Q, I0 + QP, PP, AMODE, HAS_Z>(p, tile_base, rb, slab_lane, grp, partial, out_row, tile_T, t0, lane_base,
@@ -205,7 +205,7 @@ __device__ __forceinline__ void quad_prepare(QuadQuarter<Q, AMODE, HAS_Z, AHEAD>
   if constexpr (QuadQuarter<Q, AMODE, HAS_Z, AHEAD>::kFirstUnit) {
     // (unconditional: a wavefront without a unit fetches the last one and does not use it)
     const int rb = min(rb0 + 2 * min(wave, n_units - 1) + half, p.RB - 1);
-    load_unit<true>(qq.u, p, qq.tile_base, rb, 32 * qq.h + lq, qq.grp, nullptr, 0, false, qq.tile_T, qq.t0);
+    load_unit<true>(qq.u, p, qq.tile_base, rb, 32 * qq.h + lq, qq.grp, qq.tile_T, qq.t0);
   }
   if (with_entries) quad_entries(qq, p, wave, lane, xraw);
 }
@@ -297,7 +297,7 @@ __device__ __forceinline__ void quad_quarters(const GemvParams& p, float* lut, i
       if (cur < n_units) {
         for (;;) {
           if (!QQ::kFirstUnit)
-            load_unit<true>(qq.u, p, qq.tile_base, min(rb0 + 2 * cur + half, rb_last), slab_lane, qq.grp, nullptr, 0, false,
+            load_unit<true>(qq.u, p, qq.tile_base, min(rb0 + 2 * cur + half, rb_last), slab_lane, qq.grp,
                             qq.tile_T, qq.t0);
           float acc[4][4];
 #pragma unroll
@@ -315,7 +315,7 @@ __device__ __forceinline__ void quad_quarters(const GemvParams& p, float* lut, i
           cur = next_unit(lut, lane);
           if (cur >= n_units) break;
           if (QQ::kFirstUnit)
-            load_unit<true>(qq.u, p, qq.tile_base, min(rb0 + 2 * cur + half, rb_last), slab_lane, qq.grp, nullptr, 0, false,
+            load_unit<true>(qq.u, p, qq.tile_base, min(rb0 + 2 * cur + half, rb_last), slab_lane, qq.grp,
                             qq.tile_T, qq.t0);
         }
       }
