@@ -1459,6 +1459,55 @@ void plan_grid(int cus, int vectors, int q, int64_t g, GemvParams* p) {
   }
 }
 
+// Row ranges of the layers of a group launch.  A layer alone is given about one workgroup per compute
+// unit; several such layers in one launch are as many rounds of workgroups, each with its own
+// start (activations, tables, first fetch) and the last of them ragged.  One round for all of
+// them together is faster where it can be dealt out evenly, every layer with its share of the
+// compute units: three layers of 5120 x 5120 at q = 4 21.7 -> 12.4 us, of 4096 x 4096 at q = 3 13.7 -> 9.5, of 12288 x
+// 12288 38.6 -> 35.9, eight of 5120 x 5120 at q = 2 39.5 -> 13.5, the four layers of a block of 12288 columns
+// (764 MB) 120.6 -> 115.6.  The K groups stay as
+// planned (a row's sum is the one lutgemm_gemv computes, bit for bit); only the row ranges get
+// longer.  Costs are choose_grid's, in rounds of units of a workgroup.  A few compute units are
+// left free: with every one taken two layers of 22016 x 8192 (34.7 us before) took 35.4 instead of 31 to 33.
+void share_compute_units(int wgs, GroupParams* gp) {
+  const auto cost = [](const GemvParams& p, int rs) { return p.TPG * (((p.RB + rs - 1) / rs) / (double)kWaves + 0.6); };
+  double work = 0.0, planned_cost = 0.0, planned_longest = 0.0;   // work in units (K tile, row block)
+  int64_t planned = 0;
+  for (int i = 0; i < gp->count; ++i) {
+    const GemvParams& p = gp->layer[i];
+    const double c = cost(p, p.row_splits);
+    work += (double)p.RB * p.NT;
+    planned += (int64_t)p.KG * p.row_splits;
+    planned_cost += (double)p.KG * p.row_splits * c / wgs;
+    planned_longest = planned_longest > c ? planned_longest : c;
+  }
+  if (planned <= wgs) return;
+  int rs[kMaxGroup];
+  int64_t total = 0;
+  for (int i = 0; i < gp->count; ++i) {
+    const GemvParams& p = gp->layer[i];
+    const double share = (wgs - wgs / 16) * ((double)p.RB * p.NT / work) / p.KG;
+    const int least = p.TPG > 1 ? (p.RB + kRunBlocks - 1) / kRunBlocks : 1;   // (the running sums in LDS)
+    rs[i] = share < least ? least : (share > p.row_splits ? p.row_splits : (int)share);
+    total += (int64_t)p.KG * rs[i];
+  }
+  // What rounding down has left goes to the layer that would be the last to end, while that can be.
+  double longest;
+  while (true) {
+    int last = 0;
+    for (int i = 1; i < gp->count; ++i)
+      if (cost(gp->layer[i], rs[i]) > cost(gp->layer[last], rs[last])) last = i;
+    const GemvParams& p = gp->layer[last];
+    longest = cost(p, rs[last]);
+    if (rs[last] >= p.row_splits || total + p.KG > wgs - wgs / 32) break;
+    ++rs[last];
+    total += p.KG;
+  }
+  // Rounds that overlap end, on average, half a workgroup after an even share of the work.
+  if (total > wgs || longest >= planned_cost + 0.5 * planned_longest) return;
+  for (int i = 0; i < gp->count; ++i) gp->layer[i].row_splits = rs[i];
+}
+
 constexpr size_t kCounterBytes = 32768;   // 32 activation vectors x 256 row ranges
 
 
@@ -2134,6 +2183,7 @@ int lutgemm_gemv_group(const void* const* x, const void* const* bits, const void
     partials += part_bytes / sizeof(float);
     used += part_bytes;
   }
+  share_compute_units(cus > 256 ? 256 : cus, &gp);
   for (int i = 0; i < count; ++i) {
     GemvParams& p = gp.layer[i];
     p.range_base = p.RB / p.row_splits;
