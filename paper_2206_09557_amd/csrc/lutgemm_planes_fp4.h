@@ -151,10 +151,18 @@ __device__ __forceinline__ bool fp4_make_digits(Fp4Task& t, const Fp4Params& p, 
   }
   const int exponent = max(top >> 10, 1) + 112;   // biased as in fp32: |x| < 2^(exponent - 126)
   *reinterpret_cast<int*>(lds + scales_at + ((t.local * p.vectors + t.v) * 4 + t.kb) * 4) = exponent;
+  // In the largest binade a first digit of 2 is 2^16, which the remainder's fp16 does not hold: such
+  // blocks are split as their halves.  (Lost with it: the last bit of subnormals, 2^-39 of the block's largest.)
+  const bool halves = top >= 0x7800;
+  if (halves) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) h[e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h16x2, h[e]) * (_Float16)0.5f);
+  }
+  const int first_unit = halves ? exponent - 1 : exponent;
   char* dst = lds + digits_at + (t.local * p.vectors + t.v) * kFp4VecBytes + t.kb * kFp4DigitBytes;
 #pragma unroll
   for (int d = 0; d < kFp4Digits; ++d) {
-    const float unit = __builtin_bit_cast(float, (exponent - 5 * d) << 23);
+    const float unit = __builtin_bit_cast(float, (first_unit - 5 * d) << 23);
     u32x16 packed;
 #pragma unroll
     for (int e = 0; e < 16; ++e) packed[e] = h[e];

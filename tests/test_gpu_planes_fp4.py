@@ -113,3 +113,57 @@ def test_infinities_and_nans(n, g, batch, mode):
         np.testing.assert_array_equal(np.isnan(y[v]), np.isnan(want))
         np.testing.assert_array_equal(y[v][~np.isnan(want)], want[~np.isnan(want)])
         assert np.isinf(y[v]).any() or (p.z is not None)
+
+
+class _Probe:
+    """A layer of one plane whose row r returns what the kernel makes of group r's activations: the scale is 1 for
+    (row r, group r) and 0 elsewhere, all signs are +1 but that of column 2 of a group's chunks."""
+
+    def __init__(self, g, groups=512):
+        self.g, self.groups, n = g, groups, g * groups
+        B = np.ones((1, groups, n), dtype=np.int8)
+        B[:, :, 2::8] = -1
+        alpha, _ = L.lutgemm_pack_scales(np.eye(groups, dtype=np.float16)[None], None, n, g)
+        self.p = Packed(L.lutgemm_pack_planes(B), alpha, None, groups, n, 1, g)
+
+    def __call__(self, values, batch, beside=0.0):
+        """What `values` come out as, each in a group of its own whose chunk holds +-beside as well (added and
+        taken away again)."""
+        per_call = batch * self.groups
+        v = np.zeros(-(-len(values) // per_call) * per_call, dtype=np.float16)
+        v[:len(values)] = values
+        out = []
+        for part in v.reshape(-1, batch, self.groups):
+            X = np.zeros((batch, self.groups, self.g), dtype=np.float16)
+            at = 8 * (np.arange(self.groups) % (self.g // 8))       # every chunk of a group in turn
+            for col, what in ((0, part), (1, beside), (2, beside)):
+                X[:, np.arange(self.groups), at + col] = what
+            out.append(run(self.p, X.reshape(batch, -1), f32_out=True))
+        return np.concatenate([o.ravel() for o in out])[:len(values)]
+
+
+def _finite_halves():
+    v = np.arange(1 << 16, dtype=np.uint16).view(np.float16)
+    return v[np.isfinite(v)]
+
+
+ROWS_PER_VECTOR = [(128, 4), (128, 8), (128, 16), (64, 8)]     # 4, 2, 1 operand rows per vector; two groups per step
+
+
+@pytest.mark.parametrize("g,batch", ROWS_PER_VECTOR)
+def test_every_finite_activation_alone(g, batch):
+    # The largest of its block of 32 columns: digits hold it bit for bit, and the sum has one term.
+    v = _finite_halves()
+    np.testing.assert_array_equal(_Probe(g)(v, batch), v.astype(np.float32))
+
+
+@pytest.mark.parametrize("g,batch", ROWS_PER_VECTOR)
+def test_activations_beside_the_largest_ones(g, batch):
+    # The largest binade, where the first digit may round up to 2^16, which fp16 does not hold: what five digits
+    # miss of a number (2^-24 of the power of two below the block's largest), the last bit of a
+    # subnormal, and the rounding of the fp32 sum.
+    probe, v = _Probe(g), _finite_halves()
+    for beside in (63456.0, 63488.0, 64504.0, 65504.0):
+        err = np.abs(probe(v, batch, beside).astype(np.float64) - v.astype(np.float64))
+        limit = 2.0 ** -24 * 32768.0 + 2.0 ** -24 + 2.0 ** -23 * np.abs(v.astype(np.float64))
+        assert (err <= limit).all(), f"beside {beside}: {v[err > limit][:4]} off by {err[err > limit][:4]}"
