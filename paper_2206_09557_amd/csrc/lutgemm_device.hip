@@ -1618,17 +1618,17 @@ int fp4_lds_bytes(const Fp4Params& p) {
 // each as long as its units take with the wavefronts sharing memory and matrix cores, plus the
 // start (digits), the sums of items and the hand-off between K groups.  Constants fitted to 20
 // layers (64 x 38912 to 49152 x 12288, one to six planes, with and without offsets) at 2, 4, 6, 8, 12 and 16 vectors,
-// every K group count and item length timed: the choice is within 2.2 % of the best measured
-// on average, 15 % at worst.  (Constants of such a fit are no physical quantities.)
+// every K group count and item length timed: the choice is within 2.6 % of the best measured
+// on average, 16 % at worst.  (Constants of such a fit are no physical quantities.)
 void plan_fp4_grid(int cus, int q, bool has_z, int sb, int max_groups, Fp4Params* p) {
   const int r = fp4_rows_per_vector(p->vectors, sb), chain = (kFp4Digits + r - 1) / r, row_units = (p->RB + 3) / 4;
   cus = cus > 256 ? 256 : cus;
   const int step_bytes = fp4_step_bytes(p->vectors);
   const int most = (kLdsBytes - kFp4FixedBytes) / step_bytes;     // K steps whose digits fit
   const int products = 4 * q + (has_z ? 1 : 0);
-  const double matrix = products * (r == 4 ? 0.0077 : (r == 2 ? 0.0060 : 0.0074));   // a unit among others, and ...
+  const double matrix = products * (r == 4 ? 0.0077 : (r == 2 ? 0.0060 : 0.0087));   // a unit among others, and ...
   const double memory = (q * 1024 + 128.0 * (q + (has_z ? 1 : 0)) * sb) / 52800.0;
-  const double alone = 0.80 + 0.0046 * products * chain;                               // ... a wavefront by itself
+  const double alone = 0.80 + 0.0050 * products * chain;                               // ... a wavefront by itself
   double best = 1e30;
   auto consider = [&](int kg, int pieces) {
     const int spg = (p->steps + kg - 1) / kg;
@@ -1646,14 +1646,14 @@ void plan_fp4_grid(int cus, int q, bool has_z, int sb, int max_groups, Fp4Params
     const int stretch = room < units ? room : units;
     const double workgroups = (double)kg * rs, filled = workgroups < cus ? workgroups / cus : 1.0;
     const int items = stretch * per_unit;
-    const double rounds = items <= 2 * kFp4Waves ? (items + kFp4Waves - 1) / kFp4Waves : (double)items / kFp4Waves + 0.045;
+    const double rounds = items <= 2 * kFp4Waves ? (items + kFp4Waves - 1) / kFp4Waves : (double)items / kFp4Waves + 0.047;
     const double shared = matrix > memory * filled ? matrix : memory * filled;
     const double unit = shared * (items < kFp4Waves ? items : kFp4Waves) > alone ? shared * (items < kFp4Waves ? items : kFp4Waves) : alone;
     const double tasks = (double)spg * 4 * p->vectors / (64.0 * kFp4Waves);
     double cost = (workgroups > cus ? workgroups / cus : 1.0) *
-                  (rounds * ((double)units / stretch) * (run * unit + 0.13) + 1.12 * (tasks < 1.0 ? 1.0 : tasks));
-    if (per_unit > 1) cost += 0.55 * ((units + stretch - 1) / stretch) + 0.215 * per_unit * units * p->vectors * 16 / (64.0 * kFp4Waves);
-    if (kg > 1) cost += 0.7 + 1.18 * ((units * ((p->vectors + 3) / 4) + kFp4Waves - 1) / kFp4Waves) * ((kg + 7) / 8);
+                  (rounds * ((double)units / stretch) * (run * unit + 0.13) + 2.14 * (tasks < 1.0 ? 1.0 : tasks));
+    if (per_unit > 1) cost += 0.62 * ((units + stretch - 1) / stretch) + 0.215 * per_unit * units * p->vectors * 16 / (64.0 * kFp4Waves);
+    if (kg > 1) cost += 0.87 + 1.18 * ((units * ((p->vectors + 3) / 4) + kFp4Waves - 1) / kFp4Waves) * ((kg + 7) / 8);
     if (cost < best) {
       best = cost;
       p->KG = kg;

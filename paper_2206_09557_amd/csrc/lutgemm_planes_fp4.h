@@ -3,7 +3,7 @@
 //
 // What it computes is what the lookup kernels compute, plane by plane and group by group:
 // y_r = sum_i alpha_i[r][G] * (B_i . x)_G + z[r][G] * (sum of x over G).  B_i . x runs on
-// v_mfma_scale_f32_16x16x128_f8f6f4 with the weights +-1 as e2m1 and the activations as five e2m3
+// v_mfma_scale_f32_16x16x128_f8f6f4 with the weights +-1 as e2m1 and the activations as six e2m3
 // numbers each:
 //   * Weights.  A key dword (four chunks of one row after a byte transpose) holds eight weights
 //     per bit position modulo 4.  A shift puts that bit of every nibble on its sign bit, one
@@ -11,17 +11,25 @@
 //     least, and the instruction covers 128 columns in the time the fp16 one covers 32.
 //   * Activations.  Within the 32 columns that share a block scale of the instruction, x is
 //     written as  2^e * sum_d a_d 32^-d  with balanced digits a_d that are multiples of 1/8 in
-//     [-2, 2]: exact values of e2m3.  Five digits carry 25 bits from the block's largest
-//     magnitude down, i.e. an fp16 activation is exact unless it is more than 2^14 times
-//     smaller than its block's largest, and then it is wrong by at most 2^-25 of that one.
-//     The digits are R rows of the operand and a chain of 5 / R instructions into one accumulator,
-//     smallest first: up to 16 vectors (R = 1) take 5 instructions, up to 8 (R = 2) 3, up to 4
-//     (R = 4) 2.
+//     [-2, 2]: exact values of e2m3.  With U the power of two below the block's largest
+//     magnitude, six digits end at 2^-28 U: an fp16 activation is exact unless it is more than 2^18
+//     times smaller than U, and then it is wrong by at most 2^-29 U, a thirty-second part of
+//     what an fp32 sum that holds the largest one resolves.  (Five digits, 2^-24 U, made the error
+//     of a product up to twice that of the lookups where a few activations are 2^14 times the others.)
+//     The digits of a vector are R rows of the operand, consecutive ones in a row, one instruction
+//     each: up to 16 vectors (R = 1) take 6 instructions, up to 8 (R = 2) 3, up to 4 (R = 4, three
+//     of the rows) 2.
 //   * Sums of digit products of a block are small integers in units of the block scale and
 //     exact inside the instruction; blocks whose scales differ by up to 2^14 add exactly (measured).
+//     Where a chain's accumulator enters an instruction its bits below 2^-24 of the largest product
+//     are cut off, not rounded: a row's two largest digits, whose products are exact, and the
+//     others have chains of their own, which meet in a rounded addition.  Error against 64-bit sums
+//     (2-norm, 8192 x 8192 to 4096 x 16384, q = 2 to 6, 2 to 16 vectors; N(0, 1) activations alone, with 30
+//     times larger ones every 1024 columns, or 2^14 times larger ones every 32): 0.64e-7 to 1.0e-7;
+//     one chain 2.6e-7 at worst; lookups 0.84e-7 to 1.8e-7, fp16 matrix path 1.0e-7 to 3.0e-7.
 //
 // Work split.  A K step is 128 columns, a row unit four row blocks (64 rows), a unit the two
-// together: per plane one 16-byte key load per lane and 4 x 5 instructions, number b of the 4
+// together: per plane one 16-byte key load per lane and 4 x 6 / R instructions, number b of the 4
 // taking row 4k + b of each of 16 (row block, k) pairs, so that no key has to move between
 // lanes.  Where a K step touches SB = 2 scale groups, the 16 rows of the activation operand are
 // (vector, group) pairs instead of vectors, each with zeros outside its group's columns.
@@ -72,16 +80,20 @@ struct Fp4Params {
   int y_f32;
 };
 
-constexpr int kFp4Digits = 5;
+constexpr int kFp4Digits = 6;
 constexpr int kFp4DigitBytes = 24;                        // 32 six-bit digits
 constexpr int kFp4RowBytes = 4 * kFp4DigitBytes;          // one digit of a vector's K step: four 32-column blocks
-constexpr int kFp4VecBytes = kFp4Digits * kFp4RowBytes;   // one vector of a K step
+constexpr int kFp4ScalesAt = kFp4Digits * kFp4RowBytes;   // one vector of a K step: the digits, ...
+// ... then its four block scales.  592 bytes, 20 banks beyond a multiple of all 64, keep the 16 rows of an
+// operand of sixteen vectors in different banks; with 576 (the scales elsewhere) they met in
+// four (8192 x 8192, q = 6, 16 vectors 53 us instead of 30).
+constexpr int kFp4VecBytes = kFp4ScalesAt + 16;
 constexpr int kFp4UnitRows = 64;
-// LDS: [24 zero bytes, queue, spare][one word per wavefront][digits][block scales][group numbers]
+// LDS: [24 zero bytes, queue, spare][one word per wavefront][digits and block scales][group numbers]
 //      [partial sums: item, vector, row]
 constexpr int kFp4FixedBytes = 32 + 64;
 
-__host__ __device__ constexpr int fp4_step_bytes(int vectors) { return vectors * (kFp4VecBytes + 16) + 16; }
+__host__ __device__ constexpr int fp4_step_bytes(int vectors) { return vectors * kFp4VecBytes + 16; }
 
 __device__ __forceinline__ f32x4 fp4_mfma(const i32x8& a, const i32x8& b, const f32x4& c, int scale_a) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 2 /* A: e2m3 */, 4 /* B: e2m1 */, 0, scale_a, 0, 127);
@@ -122,7 +134,7 @@ __device__ __forceinline__ void fp4_fetch_task(Fp4Task& t, const Fp4Params& p, i
 // 8 * beta + 2 * c + h of a block is column 4h + beta of its slot c: the order in which fp4_expand
 // leaves the weights.  Returns whether the block holds an infinity or NaN; these count as zero
 // here, see fp4_overlay_specials.
-__device__ __forceinline__ bool fp4_make_digits(Fp4Task& t, const Fp4Params& p, char* lds, int step0, int digits_at, int scales_at) {
+__device__ __forceinline__ bool fp4_make_digits(Fp4Task& t, const Fp4Params& p, char* lds, int step0, int digits_at) {
   const int step = step0 + t.local;
   const bool one = fp4_one_slab(p, step);
   uint32_t h[16];   // pairs of elements
@@ -150,7 +162,8 @@ __device__ __forceinline__ bool fp4_make_digits(Fp4Task& t, const Fp4Params& p, 
     }
   }
   const int exponent = max(top >> 10, 1) + 112;   // biased as in fp32: |x| < 2^(exponent - 126)
-  *reinterpret_cast<int*>(lds + scales_at + ((t.local * p.vectors + t.v) * 4 + t.kb) * 4) = exponent;
+  char* vec = lds + digits_at + (t.local * p.vectors + t.v) * kFp4VecBytes;
+  *reinterpret_cast<int*>(vec + kFp4ScalesAt + t.kb * 4) = exponent;
   // In the largest binade a first digit of 2 is 2^16, which the remainder's fp16 does not hold: such
   // blocks are split as their halves.  (Lost with it: the last bit of subnormals, 2^-39 of the block's largest.)
   const bool halves = top >= 0x7800;
@@ -159,7 +172,7 @@ __device__ __forceinline__ bool fp4_make_digits(Fp4Task& t, const Fp4Params& p, 
     for (int e = 0; e < 16; ++e) h[e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h16x2, h[e]) * (_Float16)0.5f);
   }
   const int first_unit = halves ? exponent - 1 : exponent;
-  char* dst = lds + digits_at + (t.local * p.vectors + t.v) * kFp4VecBytes + t.kb * kFp4DigitBytes;
+  char* dst = vec + t.kb * kFp4DigitBytes;
 #pragma unroll
   for (int d = 0; d < kFp4Digits; ++d) {
     const float unit = __builtin_bit_cast(float, (first_unit - 5 * d) << 23);
@@ -191,16 +204,15 @@ struct Fp4Lane {
   int r, k, kb, lg, row;
   uint32_t key_off2, key_off1;      // the lane's 16 key bytes within a K step of a two- / one-sub-slab tile
   uint32_t sel_even, sel_odd;       // byte selectors of the second transpose step
-  static constexpr int C = (kFp4Digits + R - 1) / R;   // instructions of a chain
-  uint32_t a_at;                    // LDS address of the lane's digit of the chain's first instruction in the first step
+  static constexpr int C = (kFp4Digits + R - 1) / R;   // digits of a row: consecutive ones, one per instruction
+  uint32_t a_at;                    // LDS address of the lane's largest digit in the first step
   uint32_t a_step;                  // ... and per step (0: always the zero bytes)
-  uint32_t a_next;                  // ... and per instruction of the chain
-  uint32_t a_last, a_last_step;     // R > 1: the same for the last instruction, where not every row has a digit
-  uint32_t s_at, s_minus;           // block scale in the first step, 5 * first digit
+  uint32_t a_next;                  // ... and per digit
+  uint32_t s_at, s_minus;           // block scale in the first step, 5 * largest digit's number
 };
 
 template <int SB, int R>
-__device__ __forceinline__ Fp4Lane<SB, R> fp4_lane(int lane, int vectors, int digits_at, int scales_at) {
+__device__ __forceinline__ Fp4Lane<SB, R> fp4_lane(int lane, int vectors, int digits_at) {
   Fp4Lane<SB, R> L;
   L.row = lane & 15;
   L.k = lane & 3;
@@ -216,16 +228,15 @@ __device__ __forceinline__ Fp4Lane<SB, R> fp4_lane(int lane, int vectors, int di
   }
   L.sel_odd = L.sel_even + 0x02020202u;
   const int v = L.row / (SB * R), sb = (L.row / R) % SB, part = L.row % R;
-  const bool mine = v < vectors && (SB == 1 || (L.kb >> 1) == sb);   // SB == 2: blocks 0 and 1 are the first 64 columns
-  L.s_at = (uint32_t)(scales_at + ((v < vectors ? v : 0) * 4 + L.kb) * 4);
-  L.s_minus = 5u * part;
-  L.a_at = mine ? (uint32_t)(digits_at + v * kFp4VecBytes + part * kFp4RowBytes + L.kb * kFp4DigitBytes) : 0u;
+  constexpr int C = Fp4Lane<SB, R>::C;
+  static_assert(kFp4Digits % C == 0, "a row has all its digits or none");
+  // SB == 2: blocks 0 and 1 are the first 64 columns.  R == 4: three rows have two digits each, the fourth none.
+  const bool mine = v < vectors && part * C < kFp4Digits && (SB == 1 || (L.kb >> 1) == sb);
+  L.s_at = (uint32_t)(digits_at + (v < vectors ? v : 0) * kFp4VecBytes + kFp4ScalesAt + L.kb * 4);
+  L.s_minus = 5u * C * part;
+  L.a_at = mine ? (uint32_t)(digits_at + v * kFp4VecBytes + part * C * kFp4RowBytes + L.kb * kFp4DigitBytes) : 0u;
   L.a_step = mine ? (uint32_t)(vectors * kFp4VecBytes) : 0u;
-  L.a_next = mine ? (uint32_t)(R * kFp4RowBytes) : 0u;
-  constexpr int kLast = R * (Fp4Lane<SB, R>::C - 1);
-  const bool has_last = mine && kLast + part < kFp4Digits;
-  L.a_last = has_last ? L.a_at + kLast * kFp4RowBytes : 0u;
-  L.a_last_step = has_last ? L.a_step : 0u;
+  L.a_next = mine ? (uint32_t)kFp4RowBytes : 0u;
   return L;
 }
 
@@ -321,11 +332,10 @@ __device__ __forceinline__ i32x8 fp4_specials(const Fp4Params& p, const Fp4Lane<
   return a;
 }
 
-// The lane's part of the activation operand of instruction c of the chain in a K step.
+// The lane's part of the activation operand for digit c of its row in a K step.
 template <int SB, int R>
 __device__ __forceinline__ i32x8 fp4_digit(const Fp4Lane<SB, R>& L, const char* lds, int local, int c) {
-  const bool last = R > 1 && c == Fp4Lane<SB, R>::C - 1;
-  const uint32_t at = last ? L.a_last + (uint32_t)local * L.a_last_step : L.a_at + (uint32_t)local * L.a_step + c * L.a_next;
+  const uint32_t at = L.a_at + (uint32_t)local * L.a_step + c * L.a_next;
   const u32x2* src = reinterpret_cast<const u32x2*>(lds + at);
   const u32x2 q0 = src[0], q1 = src[1], q2 = src[2];
   return i32x8{(int)q0.x, (int)q0.y, (int)q1.x, (int)q1.y, (int)q2.x, (int)q2.y, 0, 0};
@@ -339,26 +349,31 @@ template <int Q, int ZM, int SB, int R>
 __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const Fp4Params& p, const Fp4Lane<SB, R>& L,
                                             const Fp4Weights& kw, const char* lds, int local, f32x4 (&acc)[4]) {
   constexpr int C = Fp4Lane<SB, R>::C;
-  constexpr bool kHold = 6 * C + 2 * (4 * Q + SB * (2 * Q + (ZM != 0 ? 2 : 0))) <= 84;
+  constexpr bool kHold = 6 * C + 2 * (4 * Q + SB * (2 * Q + (ZM != 0 ? 2 : 0))) <= 100;
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  const int scale = *reinterpret_cast<const int*>(lds + L.s_at + (uint32_t)local * (uint32_t)(p.vectors * 16)) - (int)L.s_minus;
+  const int scale = *reinterpret_cast<const int*>(lds + L.s_at + (uint32_t)local * (uint32_t)(p.vectors * kFp4VecBytes)) - (int)L.s_minus;
   i32x8 held[kHold ? C : 1];
   if (kHold) {
 #pragma unroll
     for (int c = C - 1; c >= 0; --c) held[kHold ? c : 0] = fp4_digit(L, lds, local, c);
   }
   auto digit = [&](int c) { return kHold ? held[kHold ? c : 0] : fp4_digit(L, lds, local, c); };
+  // The two largest digits of a row, then the others (see the head of this file).
+  constexpr int kHi = C < 2 ? C : 2, kChains = C > kHi ? 2 : 1;
   f32x4 sum[4] = {zero, zero, zero, zero};
   if (ZM != 0) {   // offset term of eq. 3: z times the sum of the activations
     const int m1 = (int)0xaaaaaaaa;
     const i32x8 w = {m1, m1, m1, m1, 0, 0, 0, 0};
-    f32x4 sx = zero;
 #pragma unroll
-    for (int c = C - 1; c >= 0; --c) sx = fp4_mfma(digit(c), w, sx, scale - 5 * R * c);
+    for (int h = kChains - 1; h >= 0; --h) {
+      f32x4 sx = zero;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+      for (int c = (h ? C : kHi) - 1; c >= (h ? kHi : 0); --c) sx = fp4_mfma(digit(c), w, sx, scale - 5 * c);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sum[b][e] = half_of(u.zz[(e / R) % SB], b) * sx[e];
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[b][e] = fmaf(half_of(u.zz[(e / R) % SB], b), sx[e], sum[b][e]);
+    }
   }
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -368,21 +383,28 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
     i32x8 w[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) w[b] = fp4_expand(row[b], kw);
-    f32x4 s[4] = {zero, zero, zero, zero};   // four independent chains
 #pragma unroll
-    for (int c = C - 1; c >= 0; --c) {
-      const i32x8 a = digit(c);
+    for (int h = kChains - 1; h >= 0; --h) {
+      f32x4 s[4] = {zero, zero, zero, zero};   // four independent chains
 #pragma unroll
-      for (int b = 0; b < 4; ++b) s[b] = fp4_mfma(a, w[b], s[b], scale - 5 * R * c);
-    }
+      for (int c = (h ? C : kHi) - 1; c >= (h ? kHi : 0); --c) {
+        const i32x8 a = digit(c);
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float al = half_of(u.al[(e / R) % SB][ZM == 2 ? 0 : i], b);
-        if (ZM == 2) al *= (float)(1 << i);   // exact: the per-plane layout's scale bit for bit
-        sum[b][e] = fmaf(al, s[b][e], sum[b][e]);
+        for (int b = 0; b < 4; ++b) s[b] = fp4_mfma(a, w[b], s[b], scale - 5 * c);
       }
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float al = half_of(u.al[(e / R) % SB][ZM == 2 ? 0 : i], b);
+          if (ZM == 2) al *= (float)(1 << i);   // exact: the per-plane layout's scale bit for bit
+          sum[b][e] = fmaf(al, s[b][e], sum[b][e]);
+        }
+      if (kChains > 1) {   // chain after chain: left alone, the compiler keeps all planes' products for later (and spills)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) asm volatile("" : "+v"(sum[b]));
+      }
+    }
   }
 #pragma unroll
   for (int b = 0; b < 4; ++b) acc[b] += sum[b];
@@ -620,13 +642,12 @@ __global__ __launch_bounds__(kFp4Waves * 64) void lutgemm_fp4_kernel(Fp4Params p
   const int kg = blockIdx.x, rs = blockIdx.y;
   const int step0 = kg * p.SPG, steps = min(p.SPG, p.steps - step0);
   const int range0 = rs * p.range_base + min(rs, p.range_rem), range_units = p.range_base + (rs < p.range_rem ? 1 : 0);
-  const int digits_at = kFp4FixedBytes, scales_at = digits_at + steps * p.vectors * kFp4VecBytes;
-  const int groups_at = scales_at + steps * p.vectors * 16;
+  const int digits_at = kFp4FixedBytes, groups_at = digits_at + steps * p.vectors * kFp4VecBytes;
   float* part = reinterpret_cast<float*>(lds + groups_at + steps * 16);
   uint32_t* wave_flag = reinterpret_cast<uint32_t*>(lds + 32);
   const int per_unit = (steps + p.run - 1) / p.run;      // items of a row unit
   const uint32_t per_unit_magic = 0xffffffffu / (uint32_t)per_unit + 1u;   // t / per_unit, exact for the few thousand items there are
-  const Fp4Lane<SB, R> L = fp4_lane<SB, R>(lane, p.vectors, digits_at, scales_at);
+  const Fp4Lane<SB, R> L = fp4_lane<SB, R>(lane, p.vectors, digits_at);
 
   // ---- digits.  The activations are asked for first and waited for: asked for behind the first
   // unit's weights they would arrive behind them.
@@ -647,10 +668,10 @@ __global__ __launch_bounds__(kFp4Waves * 64) void lutgemm_fp4_kernel(Fp4Params p
   Fp4Unit<Q, ZM, SB> ua;
   fp4_load_unit(ua, p, L, ru, step0 + local, first_groups);
   bool special = false;
-  if ((int)threadIdx.x < tasks) special = fp4_make_digits(task, p, lds, step0, digits_at, scales_at);
+  if ((int)threadIdx.x < tasks) special = fp4_make_digits(task, p, lds, step0, digits_at);
   for (int t = threadIdx.x + kFp4Waves * 64; t < tasks; t += kFp4Waves * 64) {
     fp4_fetch_task(task, p, t, step0);
-    special |= fp4_make_digits(task, p, lds, step0, digits_at, scales_at);
+    special |= fp4_make_digits(task, p, lds, step0, digits_at);
   }
   for (int t = threadIdx.x; t < steps * 4; t += kFp4Waves * 64)
     *reinterpret_cast<int*>(lds + groups_at + t * 4) = min((step0 * 4 + t) * 32, p.n - 1) / p.g;
