@@ -341,6 +341,16 @@ __device__ __forceinline__ i32x8 fp4_digit(const Fp4Lane<SB, R>& L, const char* 
   return i32x8{(int)q0.x, (int)q0.y, (int)q1.x, (int)q1.y, (int)q2.x, (int)q2.y, 0, 0};
 }
 
+// R == 4: the last of a vector's four rows has no digits; not even an infinite scale makes anything of it.
+template <int R>
+__device__ __forceinline__ constexpr bool fp4_empty_row(int e) { return (e % R) * ((kFp4Digits + R - 1) / R) >= kFp4Digits; }
+
+// The block scale that goes with the lane's largest digit in a K step.
+template <int SB, int R>
+__device__ __forceinline__ int fp4_block_scale(const Fp4Params& p, const Fp4Lane<SB, R>& L, const char* lds, int local) {
+  return *reinterpret_cast<const int*>(lds + L.s_at + (uint32_t)local * (uint32_t)(p.vectors * kFp4VecBytes)) - (int)L.s_minus;
+}
+
 // One unit into the sums: acc[b][e] is operand row 4 * lg + e, weight row 4k + b.  The unit's planes are
 // added among themselves first: one addition per unit to the long sums, whose rounding is what the
 // result's error is made of (49152 x 12288 at 16 vectors: 1.4e-7 without, see kFp4MaxRun).  The digits stay in
@@ -351,7 +361,7 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
   constexpr int C = Fp4Lane<SB, R>::C;
   constexpr bool kHold = 6 * C + 2 * (4 * Q + SB * (2 * Q + (ZM != 0 ? 2 : 0))) <= 100;
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  const int scale = *reinterpret_cast<const int*>(lds + L.s_at + (uint32_t)local * (uint32_t)(p.vectors * kFp4VecBytes)) - (int)L.s_minus;
+  const int scale = fp4_block_scale(p, L, lds, local);
   i32x8 held[kHold ? C : 1];
   if (kHold) {
 #pragma unroll
@@ -372,7 +382,8 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
 #pragma unroll
       for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[b][e] = fmaf(half_of(u.zz[(e / R) % SB], b), sx[e], sum[b][e]);
+        for (int e = 0; e < 4; ++e)
+          if (!fp4_empty_row<R>(e)) sum[b][e] = fmaf(half_of(u.zz[(e / R) % SB], b), sx[e], sum[b][e]);
     }
   }
 #pragma unroll
@@ -396,6 +407,7 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+          if (fp4_empty_row<R>(e)) continue;
           float al = half_of(u.al[(e / R) % SB][ZM == 2 ? 0 : i], b);
           if (ZM == 2) al *= (float)(1 << i);   // exact: the per-plane layout's scale bit for bit
           sum[b][e] = fmaf(al, s[b][e], sum[b][e]);
@@ -558,18 +570,22 @@ __device__ __forceinline__ void fp4_items(const Fp4Params& p, const Fp4Lane<SB, 
   }
 }
 
-// Infinities and NaNs of the activations have no digits.  A row they reach is +-inf or NaN whatever else
-// is added, so where there are any their products are formed alone, after the finite sums, and
-// written over those of the rows that they reach.  Rare, and not tuned.
+// Infinities and NaNs of the activations have no digits.  Where there are any, the sums are formed once more with
+// their products among them, after the finite ones, and written over those of the (vector, row)
+// pairs that they reach: those with a product that is not zero (of what is in the operand only the
+// infinities and NaNs give one), whatever the scales are.  Rare, and not tuned: what is written is
+// an infinity or NaN, so that one chain does for the digits.
 template <int Q, int ZM, int SB, int R>
 __device__ __forceinline__ void fp4_overlay_specials(const Fp4Params& p, const Fp4Lane<SB, R>& L, const char* lds, float* part, int wave,
                                                      int waves, int kg, int step0, int steps, int per_unit, int ru0, int units,
                                                      int groups_at) {
+  constexpr int P = SB * R, NR = 4 / P;
   const int* groups = reinterpret_cast<const int*>(lds + groups_at);
   const Fp4Weights kw = fp4_weights();
 #pragma unroll 1
   for (int u = wave; u < units; u += waves) {
     f32x4 acc[4];
+    uint32_t reached = 0;   // bit 4 * b + c: vector c of the lane, row b
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1
@@ -580,6 +596,7 @@ __device__ __forceinline__ void fp4_overlay_specials(const Fp4Params& p, const F
       const uint8_t* keys = p.bits + (int64_t)(step >> 3) * p.RB * (Q * 2048) + (int64_t)rb * (Q * slab_row) +
                             (step & 7) * (one ? 256 : 128) + (one ? L.key_off1 : L.key_off2);
       const i32x8 a = fp4_specials(p, L, step, one);
+      const int scale = fp4_block_scale(p, L, lds, local);
 #pragma unroll 1
       for (int t = (ZM != 0 ? -1 : 0); t < Q; ++t) {   // planes; -1: the offsets, a plane of +1
         uint32_t row[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
@@ -589,6 +606,17 @@ __device__ __forceinline__ void fp4_overlay_specials(const Fp4Params& p, const F
         for (int b = 0; b < 4; ++b)
           dot[b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, fp4_expand(row[b], kw), f32x4{0.0f, 0.0f, 0.0f, 0.0f},
                                                                     1 /* A: e5m2 */, 4, 0, 127, 0, 127);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (!(dot[b][e] == 0.0f)) reached |= 1u << (4 * b + e / P);
+#pragma unroll 1
+        for (int c = Fp4Lane<SB, R>::C - 1; c >= 0; --c) {
+          const i32x8 digit = fp4_digit(L, lds, local, c);
+#pragma unroll
+          for (int b = 0; b < 4; ++b) dot[b] += fp4_mfma(digit, fp4_expand(row[b], kw), f32x4{0.0f, 0.0f, 0.0f, 0.0f}, scale - 5 * c);
+        }
 #pragma unroll
         for (int s = 0; s < SB; ++s) {
           const int64_t pair = (int64_t)rb * p.NG + groups[local * 4 + s * (4 / SB)];
@@ -600,12 +628,11 @@ __device__ __forceinline__ void fp4_overlay_specials(const Fp4Params& p, const F
             for (int e = 0; e < 4; ++e) {
               float al = half_of(sc, b);
               if (ZM == 2 && t >= 0) al *= (float)(1 << t);
-              if ((e / R) % SB == s) acc[b][e] = fmaf(al, dot[b][e], acc[b][e]);
+              if ((e / R) % SB == s && !fp4_empty_row<R>(e)) acc[b][e] = fmaf(al, dot[b][e], acc[b][e]);
             }
         }
       }
     }
-    constexpr int P = SB * R, NR = 4 / P;
 #pragma unroll
     for (int c = 0; c < NR; ++c)
 #pragma unroll
@@ -614,7 +641,7 @@ __device__ __forceinline__ void fp4_overlay_specials(const Fp4Params& p, const F
 #pragma unroll
         for (int e = 1; e < P; ++e) s += acc[b][c * P + e];
         const int v = L.lg * NR + c, row = (ru0 + u) * kFp4UnitRows + 4 * L.row + b;
-        if (v >= p.vectors || s == 0.0f) continue;   // nothing special reaches this row (NaN compares unequal)
+        if (v >= p.vectors || (reached >> (4 * b + c) & 1u) == 0u) continue;
         if (per_unit > 1)
           part[(u * per_unit * p.vectors + v) * kFp4UnitRows + 4 * L.row + b] = s;
         else if (p.KG > 1 && row < p.vec_stride)
@@ -696,7 +723,10 @@ __global__ __launch_bounds__(kFp4Waves * 64) void lutgemm_fp4_kernel(Fp4Params p
     if (any_special != 0u) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the finite sums are where they belong
       __syncthreads();
-      fp4_overlay_specials<Q, ZM, SB, R>(p, L, lds, part, wave, waves, kg, step0, steps, per_unit, ru0, units, groups_at);
+      int lane_again = lane;   // (nothing of this is to stay in registers over the items)
+      asm volatile("" : "+v"(lane_again));
+      const Fp4Lane<SB, R> again = fp4_lane<SB, R>(lane_again, p.vectors, digits_at);
+      fp4_overlay_specials<Q, ZM, SB, R>(p, again, lds, part, wave, waves, kg, step0, steps, per_unit, ru0, units, groups_at);
     }
     if (per_unit > 1) {    // items of a row in step order
       __syncthreads();

@@ -199,3 +199,23 @@ def test_error_with_large_outliers_is_no_larger_than_the_lookups(batch, period):
 
     planes, lookups = error(run(p, X, f32_out=True)), error(np.stack([run(p, x, f32_out=True) for x in X]))
     assert planes <= lookups, f"{planes} against {lookups}"
+
+
+@pytest.mark.parametrize("batch,g", [(3, 128), (7, 128), (13, 128), (6, 64)])
+def test_infinite_scale_beside_infinite_activations(batch, g):
+    # A row with an infinite scale is +inf for finite activations (signs and activations all positive, with
+    # some in every digit), whatever other vectors of the call hold, +inf for a vector with +inf of its
+    # own, and NaN for one with -inf.
+    m, n, q = 70, 512, 3
+    alpha = np.full((q, m, n // g), 0.5, dtype=np.float16)
+    alpha[1, 3, 0] = np.inf
+    packed, _ = L.lutgemm_pack_scales(alpha, None, n, g)
+    p = Packed(L.lutgemm_pack_planes(np.ones((q, m, n), dtype=np.int8)), packed, None, m, n, q, g)
+    X = np.tile(np.float16([1.0 + 2.0 ** -10, 2.0 ** -17, 2.0 ** -24, 1.0]), (batch, n // 4))
+    clean = run(p, X, f32_out=True)
+    assert np.isposinf(clean[:, 3]).all() and np.isfinite(np.delete(clean, 3, axis=1)).all()
+    X[0, n - 5], X[1, n - 3] = -np.inf, np.inf
+    y = run(p, X, f32_out=True)
+    np.testing.assert_array_equal(y[2:], clean[2:])
+    assert np.isposinf(y[1]).all()
+    assert np.isnan(y[0, 3]) and np.isneginf(np.delete(y[0], 3)).all()
