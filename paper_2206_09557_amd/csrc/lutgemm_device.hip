@@ -1615,20 +1615,21 @@ int fp4_lds_bytes(const Fp4Params& p) {
 
 // Grid of one launch: K groups of SPG steps, row ranges (one workgroup per compute unit), K steps per
 // item, row units per stretch.  The least of a cost in microseconds: rounds of items of a workgroup,
-// each as long as its units take with the wavefronts sharing memory and matrix cores, plus the
-// start (digits), the sums of items and the hand-off between K groups.  Constants fitted to 20
-// layers (64 x 38912 to 49152 x 12288, one to six planes, with and without offsets) at 2, 4, 6, 8, 12 and 16 vectors,
-// every K group count and item length timed: the choice is within 2.6 % of the best measured
-// on average, 16 % at worst.  (Constants of such a fit are no physical quantities.)
+// each as long as its units take with the wavefronts sharing the compute unit or alone, plus the
+// start (digits), the sums of items, the restart of a further stretch and the hand-off between K
+// groups.  Constants fitted to 70 layers (0.1 to 604 million weights, 64 rows to 117 and to 45,000, one to
+// six planes, with and without offsets) at 3, 5, 8, 9, 12 and 16 vectors, every K group count and item
+// length timed: the choice is within 2.6 % of the best measured on average, 10 % in nineteen of
+// twenty, 17 % at worst, and its cost within some 12 % of the time of a launch among others.
 void plan_fp4_grid(int cus, int q, bool has_z, int sb, int max_groups, Fp4Params* p) {
   const int r = fp4_rows_per_vector(p->vectors, sb), chain = (kFp4Digits + r - 1) / r, row_units = (p->RB + 3) / 4;
   cus = cus > 256 ? 256 : cus;
   const int step_bytes = fp4_step_bytes(p->vectors);
   const int most = (kLdsBytes - kFp4FixedBytes) / step_bytes;     // K steps whose digits fit
   const int products = 4 * q + (has_z ? 1 : 0);
-  const double matrix = products * (r == 4 ? 0.0077 : (r == 2 ? 0.0060 : 0.0087));   // a unit among others, and ...
-  const double memory = (q * 1024 + 128.0 * (q + (has_z ? 1 : 0)) * sb) / 52800.0;
-  const double alone = 0.80 + 0.0050 * products * chain;                               // ... a wavefront by itself
+  const double among = products * (r == 4 ? 0.0107 : (r == 2 ? 0.0153 : 0.0167));   // a unit among those of other wavefronts, and ...
+  const double alone = 0.777 + products * chain * (r == 1 ? 0.0134 : 0.0172);        // ... a wavefront by itself
+  const auto rounds = [](int items) { return items <= 2 * kFp4Waves ? (items + kFp4Waves - 1) / kFp4Waves : items / (double)kFp4Waves + 0.085; };
   double best = 1e30;
   auto consider = [&](int kg, int pieces) {
     const int spg = (p->steps + kg - 1) / kg;
@@ -1644,16 +1645,15 @@ void plan_fp4_grid(int cus, int q, bool has_z, int sb, int max_groups, Fp4Params
     const int units = (row_units + rs - 1) / rs;
     const int room = per_row ? (kLdsBytes - table) / per_row : units;
     const int stretch = room < units ? room : units;
-    const double workgroups = (double)kg * rs, filled = workgroups < cus ? workgroups / cus : 1.0;
-    const int items = stretch * per_unit;
-    const double rounds = items <= 2 * kFp4Waves ? (items + kFp4Waves - 1) / kFp4Waves : (double)items / kFp4Waves + 0.047;
-    const double shared = matrix > memory * filled ? matrix : memory * filled;
-    const double unit = shared * (items < kFp4Waves ? items : kFp4Waves) > alone ? shared * (items < kFp4Waves ? items : kFp4Waves) : alone;
+    const double workgroups = (double)kg * rs;
+    const int items = stretch * per_unit, waves = items < kFp4Waves ? items : kFp4Waves;
+    const int whole = units / stretch, rest = (units - whole * stretch) * per_unit, restarts = (units + stretch - 1) / stretch - 1;
+    const double unit = among * waves > alone ? among * waves : alone;
     const double tasks = (double)spg * 4 * p->vectors / (64.0 * kFp4Waves);
-    double cost = (workgroups > cus ? workgroups / cus : 1.0) *
-                  (rounds * ((double)units / stretch) * (run * unit + 0.13) + 2.14 * (tasks < 1.0 ? 1.0 : tasks));
-    if (per_unit > 1) cost += 0.62 * ((units + stretch - 1) / stretch) + 0.215 * per_unit * units * p->vectors * 16 / (64.0 * kFp4Waves);
-    if (kg > 1) cost += 0.87 + 1.18 * ((units * ((p->vectors + 3) / 4) + kFp4Waves - 1) / kFp4Waves) * ((kg + 7) / 8);
+    double cost = 3.62 + (workgroups > cus ? workgroups / cus : 1.0) *
+                             ((whole * rounds(items) + rounds(rest)) * run * unit + 0.853 * (tasks < 1.0 ? 1.0 : tasks));
+    if (per_unit > 1) cost += 4.0 * restarts + (r == 1 ? 0.184 : 0.075) * per_unit * units * p->vectors * 16 / (64.0 * kFp4Waves);
+    if (kg > 1) cost += 0.423 + 1.018 * ((units * ((p->vectors + 3) / 4) + kFp4Waves - 1) / kFp4Waves) * ((kg + 7) / 8);
     if (cost < best) {
       best = cost;
       p->KG = kg;
