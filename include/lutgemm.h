@@ -307,6 +307,30 @@ int lutgemm_gemm_dequant_mfma(const void* x, const void* bits, const void* alpha
    LUTGEMM_EINVAL for malformed arguments, LUTGEMM_EHIP if the device cannot be asked.  */
 int lutgemm_plan_grid(int64_t m, int64_t n, int q, int g, int vectors, int compute_units, int* out);
 
+/* HOST.  The kernel launches of lutgemm_gemm for an m x n layer (q planes, group size g, with offsets or
+   not) and `batch` activation vectors; flags as there, LUTGEMM_PATH_AUTO included.  Seven numbers
+   per launch:
+     out[0]   the kernel, LUTGEMM_KERNEL_*,       out[1]   the activation vectors that it computes,
+     out[2]   K groups,                           out[4]   row ranges,
+     out[3]   K tiles per K group as lutgemm_plan_grid counts them; K steps of 128 columns for
+              LUTGEMM_KERNEL_FP4, and for this kernel only (else 0)
+     out[5]   K steps of an item (what one wavefront adds up),
+     out[6]   row units of 64 rows that a workgroup works on at a time.
+   compute_units as in lutgemm_plan_grid, and for the same purpose.  Returns the number of launches;
+   LUTGEMM_EWORKSPACE if there are more than max_launches, LUTGEMM_EINVAL or LUTGEMM_EHIP as there. */
+enum {
+  LUTGEMM_KERNEL_GEMV = 1,   /* lookups, one vector (lutgemm_gemv's), two, four */
+  LUTGEMM_KERNEL_PAIR = 2,
+  LUTGEMM_KERNEL_QUAD = 4,
+  LUTGEMM_KERNEL_FP4 = 16,   /* binary planes on the matrix cores as 4-bit floats */
+  LUTGEMM_KERNEL_FP16 = 32   /* ... as fp16 numbers (lutgemm_gemm_mfma) */
+};
+int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int batch, unsigned flags,
+                      int compute_units, int* out, int max_launches);
+
+/* HOST.  The grid of each layer of a lutgemm_gemv_group call: out[2 i] K groups, out[2 i + 1] row ranges. */
+int lutgemm_plan_group(const int64_t* m, const int64_t* n, int count, int q, int g, int compute_units, int* out);
+
 /* DEVICE pointers.  Measurement aid, no part of the product: reads `bytes` bytes at src
    (bytes % 16 == 0, src 16-byte aligned) exactly once, every workgroup a contiguous share
    front to back, in the access shape of the weight stream of section 3.4's memory-bound

@@ -1459,6 +1459,17 @@ void plan_grid(int cus, int vectors, int q, int64_t g, GemvParams* p) {
   }
 }
 
+// The same for a layer of p->NT tiles: p->NT becomes the tiles (half, quarter tiles) that a kernel of this width walks.
+void plan_lookup_grid(int cus, int vectors, int q, int64_t g, GemvParams* p) {
+  if (vectors == 2) {
+    const int last_chunks = p->nchunks - 128 * (p->NT - 1);
+    p->NT = 2 * (p->NT - 1) + (last_chunks > 64 ? 2 : 1);
+  } else if (vectors == 4) {
+    p->NT = 4 * p->NT;   // quarter ids; those a ragged last tile does not have are skipped by the kernel
+  }
+  plan_grid(cus, vectors, q, g, p);
+}
+
 // Row ranges of the layers of a group launch.  A layer alone is given about one workgroup per compute
 // unit; several such layers in one launch are as many rounds of workgroups, each with its own
 // start (activations, tables, first fetch) and the last of them ragged.  One round for all of
@@ -1573,6 +1584,21 @@ void plan_planes_grid(int cus, int waves, int batch, GemvParams* p) {
   }
 }
 
+int planes_waves(int q) { return q > 4 ? 4 : 8; }
+
+// The grid that is launched: the above, or what a sweep asks for.
+void plan_planes(int cus, int q, int batch, GemvParams* p) {
+  const int waves = planes_waves(q), tpg = tuning().mfma_tpg;
+  plan_planes_grid(cus, waves, batch, p);
+  if (tpg <= 0) return;
+  const int min_rs = (p->RB + kPlanesMaxUnits * waves - 1) / (kPlanesMaxUnits * waves);
+  p->TPG = tpg > p->NT ? p->NT : tpg;
+  p->KG = (p->NT + p->TPG - 1) / p->TPG;
+  int rs = (cus > 256 ? 256 : cus) / p->KG;
+  rs = rs < min_rs ? min_rs : rs;
+  p->row_splits = rs > p->RB ? p->RB : rs;
+}
+
 // ---- planes as 4-bit floats (lutgemm_planes_fp4.h) ----
 
 constexpr int kLdsBytes = 160 * 1024;
@@ -1607,6 +1633,59 @@ int fp4_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
   const int most = 16 / sb;
   return left < most ? left : most;
 }
+
+// Whether the 4-bit-float kernel is what lutgemm_gemm_mfma runs: where it takes the whole batch in one launch,
+// unless the fp16 operands are faster.  Both timed on 330 layers (0.1 to 500 million weights, q = 1 to 6)
+// at 2 to 16 vectors; microseconds, fp16 / this kernel:
+//   * Up to eight vectors only on layers within one K tile, for which the fp16 kernel writes y without
+//     a hand-off: 1363 x 320, q = 2 at 5 vectors 5.0 / 5.8, 1607 x 576, q = 4, g = 64 at 8 6.3 / 7.5, but with
+//     offsets 720 x 512, q = 3 6.5 / 5.9, and 15263 x 512, q = 4 6.9 / 6.1.
+//   * From nine on (six matrix instructions per product instead of three) on more of these: 1024 x 1024,
+//     q = 3 7.5 / 7.9, but 15466 x 1024, q = 4 9.9 / 9.2; on small layers of one or two planes and long groups, where
+//     the scaling of six instructions' sums per group is what costs: 2843 x 4352, q = 2, g = 256 9.9 / 11.2; and
+//     on a few rows that are long, 131 x 31232, q = 3 12.3 / 14.0.
+//   * From thirteen on rows so long that the digits of a K group crowd the sums of its items out of LDS:
+//     12288 x 49152, q = 3, 16 vectors 119 / 143, 12914 x 37248, q = 3, row-wise 106 / 136, but 8192 x 22016, q = 4 59 / 47.
+// What is decided wrongly costs at most a tenth.
+bool matrix_cores_take_fp4(int q, int64_t m, int64_t n, int64_t gg, bool has_z, int batch) {
+  if (fp4_pass(q, m, n, gg, batch) != batch) return false;
+  const int64_t w = m * n;
+  if (m > (int64_t)kPlanesMaxUnits * planes_waves(q) * 16 * 256) return true;   // too tall for the fp16 kernel's arrival counters
+  if (batch <= 8) {
+    if (fp4_scale_groups(n, gg) == 2) return n >= 1024;
+    if (batch > 4 && n > 512 && n <= 768 && w * q <= (int64_t)1 << 22) return false;
+    return !(n < 1024 && q <= 3 && !has_z && w * q <= (int64_t)1 << 22);
+  }
+  if (n <= 1024) return w * q > (int64_t)1 << 23 && gg <= 256;
+  if (q <= 2 && gg >= 256 && w <= (int64_t)24 << 20) return false;
+  if (q <= 4 && !has_z && m < 192 && n >= 4096) return false;
+  return !(batch > 12 && ((q <= 3 && n >= 14336) || (q == 4 && n >= 32768)) && w >= (int64_t)1 << 27);
+}
+
+// What lutgemm_gemm runs next for `left` activation vectors: the kernel (of the lookup kernels the value is the
+// width) and the vectors that it really computes.
+struct GemmPass {
+  int kernel, vectors;
+};
+GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
+  const int pass = fp4_pass(q, m, n, gg, left);
+  if (pass > 0) return {LUTGEMM_KERNEL_FP4, pass};
+  if (left >= 3) return {LUTGEMM_KERNEL_QUAD, left >= 4 ? 4 : 3};
+  return left == 2 ? GemmPass{LUTGEMM_KERNEL_PAIR, 2} : GemmPass{LUTGEMM_KERNEL_GEMV, 1};
+}
+
+// LUTGEMM_PATH_AUTO: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel that gemm_pass takes as
+// well; beyond, the fp16 matrix-core kernel, whose time grows least) for six vectors and more, from
+// five on below 2^28 weights, from three on up to 2^25.  At 17 to some 24 vectors the flag is the slower
+// way on most layers: sixteen of them and the rest in the 4-bit-float kernel take 49152 x 12288, q = 3, at 17 in
+// 140 us where the fp16 kernel takes 165.
+bool auto_takes_matrix_cores(unsigned flags, int64_t m, int64_t n, int64_t gg, int batch) {
+  return (flags & LUTGEMM_PATH_AUTO) != 0 && (flags & LUTGEMM_ALPHA_SHARED) == 0 && gg % 64 == 0 &&
+         (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25));
+}
+
+// K groups whose partial sums a workspace for `batch` vectors holds.
+int fp4_max_groups(int tiles, int batch) { return tiles * (batch >= 3 ? 4 : 2); }
 
 int fp4_lds_bytes(const Fp4Params& p) {
   const int per_unit = (p.SPG + p.run - 1) / p.run;   // items of a row unit; a single one needs no place for its sums
@@ -1880,12 +1959,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   if (m > (int64_t)1 << 30 || n > (int64_t)1 << 30) return LUTGEMM_EUNSUPPORTED;
   const bool shared = (flags & LUTGEMM_ALPHA_SHARED) != 0;
   if (shared && !z) return LUTGEMM_EINVAL;   // the shared-scale form always comes with offsets
-  // The caller lets the library choose: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel
-  // that the loop below takes as well; beyond, the fp16 matrix-core kernel, whose time grows
-  // least: 49152 x 12288 at 32 vectors 167 us against 191 below) for six vectors and more, from five on below 2^28
-  // weights, from three on up to 2^25.
-  if ((flags & LUTGEMM_PATH_AUTO) != 0 && !shared && gg % 64 == 0 &&
-      (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25)))
+  if (auto_takes_matrix_cores(flags, m, n, gg, batch))
     return lutgemm_gemm_mfma(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags & LUTGEMM_Y_F32, workspace,
                              workspace_bytes, hip_stream);
   const size_t need = lutgemm_workspace_bytes(m, n, q, g, mu, batch);
@@ -1923,14 +1997,11 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   GemvKernel quad_kern = nullptr, pair_kern = nullptr;
   auto plan_quad = [&]() {
     if (quad_kern) return;
-    pq.NT = 4 * p.NT;   // quarter ids; those a ragged last tile does not have are skipped by the kernel
-    plan_grid(cus, 4, q, gg, &pq);
+    plan_lookup_grid(cus, 4, q, gg, &pq);
     quad_kern = pick_quad_kernel(q, z != nullptr, shared, gg);
   };
   auto plan_pair = [&]() {
-    const int last_chunks = p.nchunks - 128 * (p.NT - 1);
-    pp.NT = 2 * (p.NT - 1) + (last_chunks > 64 ? 2 : 1);   // half tiles
-    plan_grid(cus, 2, q, gg, &pp);
+    plan_lookup_grid(cus, 2, q, gg, &pp);
     pair_kern = pick_pair_kernel(q, z != nullptr, shared, gg);
   };
   Fp4Params pf = {};
@@ -1941,21 +2012,19 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   pf.vec_stride = m_pad;
   fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
   for (int b = 0; b < batch;) {
-    const int left = batch - b;
-    const int pass = fp4_pass(q, m, n, gg, left);
-    if (pass > 0) {
+    const GemmPass pass = gemm_pass(q, m, n, gg, batch - b);
+    if (pass.kernel == LUTGEMM_KERNEL_FP4) {
       pf.x = static_cast<const __half*>(x) + (int64_t)b * n;
       pf.y = static_cast<char*>(y) + (int64_t)b * m * y_elem;
       pf.partial = partials + (int64_t)b * m_pad;
       pf.counters = counters;
-      pf.vectors = pass;
-      const int rc = launch_fp4(cus, q, shared, gg, p.NT * (batch >= 3 ? 4 : 2), pf, stream);
+      pf.vectors = pass.vectors;
+      const int rc = launch_fp4(cus, q, shared, gg, fp4_max_groups(p.NT, batch), pf, stream);
       if (rc != LUTGEMM_OK) return rc;
-      b += pass;
+      b += pass.vectors;
       continue;
     }
-    const int take = left >= 3 ? 4 : left;          // kernel width: 4, 2 or 1
-    const int live = left >= 4 ? 4 : left;          // vectors it really computes
+    const int take = pass.kernel, live = pass.vectors;
     if (take == 4) plan_quad();
     if (take == 2) plan_pair();
     GemvParams pb = take == 4 ? pq : (take == 2 ? pp : p);
@@ -2007,13 +2076,7 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
   fill_shape(&p, m, n, gg);
   p.batch = batch;
   p.y_f32 = (flags & LUTGEMM_Y_F32) ? 1 : 0;
-  // Small layers of one or two planes whose groups are long, nine vectors and more, stay with the fp16
-  // operands: there the scaling of two times five matrix instructions per group is what costs, and
-  // the weights are few (3061 x 256, q = 2 row-wise, 10 vectors 5.3 us against 5.6; 193 x 10048, q = 2 row-wise, 16
-  // 10.3 / 10.8; 110 x 6144, q = 1, g = 256, 16 8.5 / 9.1; at 10085 x 1792, q = 1, g = 256, 13 9.2 / 8.5, and at g = 128
-  // 776 x 1920, q = 2, 16 9.7 / 8.5).
-  const bool few_scales = batch > 8 && q <= 2 && gg >= 256 && m * n <= (int64_t)1 << 22;
-  if (!dequant && !few_scales && fp4_pass(q, m, n, gg, batch) == batch) {   // one launch
+  if (!dequant && matrix_cores_take_fp4(q, m, n, gg, z != nullptr, batch)) {   // one launch
     Fp4Params pf = {};
     pf.x = p.x;
     pf.bits = p.bits;
@@ -2026,21 +2089,10 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
     pf.counters = static_cast<uint32_t*>(workspace);
     pf.vectors = batch;
     fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
-    return launch_fp4(cus, q, false, gg, p.NT * (batch >= 3 ? 4 : 2), pf, static_cast<hipStream_t>(hip_stream));
+    return launch_fp4(cus, q, false, gg, fp4_max_groups(p.NT, batch), pf, static_cast<hipStream_t>(hip_stream));
   }
-  const int waves = q > 4 ? 4 : 8;
-  plan_planes_grid(cus, waves, batch, &p);
-  {
-    const int tpg = tuning().mfma_tpg;
-    if (tpg > 0) {
-      const int min_rs = (p.RB + kPlanesMaxUnits * waves - 1) / (kPlanesMaxUnits * waves);
-      p.TPG = tpg > p.NT ? p.NT : tpg;
-      p.KG = (p.NT + p.TPG - 1) / p.TPG;
-      int rs = (cus > 256 ? 256 : cus) / p.KG;
-      rs = rs < min_rs ? min_rs : rs;
-      p.row_splits = rs > p.RB ? p.RB : rs;
-    }
-  }
+  const int waves = planes_waves(q);
+  plan_planes(cus, q, batch, &p);
   if (p.row_splits > 256 && p.KG > 1) return LUTGEMM_EUNSUPPORTED;   // 256 arrival counters per call
   const int64_t m_pad = (int64_t)(p.RB + (p.RB & 1)) * 16;
   p.kg_stride = m_pad * batch;
@@ -2083,16 +2135,76 @@ int lutgemm_plan_grid(int64_t m, int64_t n, int q, int g, int vectors, int compu
   p.RB = (int)((m + 15) / 16);
   p.nchunks = (int)(n / 8);
   p.NT = (p.nchunks + 127) / 128;
-  if (vectors == 2) {
-    const int last_chunks = p.nchunks - 128 * (p.NT - 1);
-    p.NT = 2 * (p.NT - 1) + (last_chunks > 64 ? 2 : 1);
-  } else if (vectors == 4) {
-    p.NT = 4 * p.NT;
-  }
-  plan_grid(cus, vectors, q, gg, &p);
+  plan_lookup_grid(cus, vectors, q, gg, &p);
   out[0] = p.KG;
   out[1] = p.TPG;
   out[2] = p.row_splits;
+  return LUTGEMM_OK;
+}
+
+int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int batch, unsigned flags, int compute_units, int* out,
+                      int max_launches) {
+  if (!out || max_launches < 1 || m < 1 || n < 8 || n % 8 != 0 || m > (int64_t)1 << 30 || n > (int64_t)1 << 30) return LUTGEMM_EINVAL;
+  if (q < 1 || q > 8 || g < 0 || batch < 1 || batch > 32 || (flags & ~7u) != 0) return LUTGEMM_EINVAL;
+  const int64_t gg = g == 0 ? n : g;
+  if (gg % 8 != 0 || n % gg != 0) return LUTGEMM_EINVAL;
+  const int cus = compute_units > 0 ? compute_units : compute_units_of_device();
+  if (cus <= 0) return LUTGEMM_EHIP;
+  GemvParams p = {};
+  fill_shape(&p, m, n, gg);
+  const bool matrix = auto_takes_matrix_cores(flags, m, n, gg, batch);
+  const bool fp16 = matrix && !matrix_cores_take_fp4(q, m, n, gg, has_offsets != 0, batch);
+  int launches = 0;
+  for (int b = 0; b < batch; ++launches) {
+    if (launches == max_launches) return LUTGEMM_EWORKSPACE;
+    const GemmPass pass = fp16 ? GemmPass{LUTGEMM_KERNEL_FP16, batch} : gemm_pass(q, m, n, gg, batch - b);
+    int* o = out + 7 * launches;
+    o[0] = pass.kernel;
+    o[1] = pass.vectors;
+    o[5] = o[6] = 0;
+    if (pass.kernel == LUTGEMM_KERNEL_FP4) {
+      Fp4Params pf = {};
+      fill_fp4_shape(&pf, m, n, gg, false);
+      pf.vectors = pass.vectors;
+      fp4_grid(cus, q, has_offsets != 0, fp4_scale_groups(n, gg), fp4_max_groups(p.NT, batch), &pf);
+      o[2] = pf.KG;
+      o[3] = pf.SPG;
+      o[4] = pf.row_splits;
+      o[5] = pf.run;
+      o[6] = pf.stretch;
+    } else {
+      GemvParams pk = p;
+      if (fp16)
+        plan_planes(cus, q, batch, &pk);
+      else
+        plan_lookup_grid(cus, pass.kernel, q, gg, &pk);
+      o[2] = pk.KG;
+      o[3] = pk.TPG;
+      o[4] = pk.row_splits;
+    }
+    b += pass.vectors;
+  }
+  return launches;
+}
+
+int lutgemm_plan_group(const int64_t* m, const int64_t* n, int count, int q, int g, int compute_units, int* out) {
+  if (!m || !n || !out || count < 1 || count > kMaxGroup || q < 1 || q > 8 || g < 0) return LUTGEMM_EINVAL;
+  const int cus = compute_units > 0 ? compute_units : compute_units_of_device();
+  if (cus <= 0) return LUTGEMM_EHIP;
+  GroupParams gp = {};
+  gp.count = count;
+  for (int i = 0; i < count; ++i) {
+    if (m[i] < 1 || n[i] < 8 || n[i] % 8 != 0 || m[i] > (int64_t)1 << 30 || n[i] > (int64_t)1 << 30) return LUTGEMM_EINVAL;
+    const int64_t gg = g == 0 ? n[i] : g;
+    if (gg % 8 != 0 || n[i] % gg != 0) return LUTGEMM_EINVAL;
+    fill_shape(&gp.layer[i], m[i], n[i], gg);
+    plan_grid(cus, 1, q, gg, &gp.layer[i]);
+  }
+  share_compute_units(cus > 256 ? 256 : cus, &gp);
+  for (int i = 0; i < count; ++i) {
+    out[2 * i] = gp.layer[i].KG;
+    out[2 * i + 1] = gp.layer[i].row_splits;
+  }
   return LUTGEMM_OK;
 }
 

@@ -17,6 +17,7 @@ LIB_PATH = os.environ.get("LUTGEMM_LIB") or os.path.join(_PKG, "liblutgemm.so")
 LUTGEMM_OK, LUTGEMM_EINVAL, LUTGEMM_EUNSUPPORTED, LUTGEMM_EWORKSPACE, LUTGEMM_EHIP = 0, -1, -2, -3, -4
 LUTGEMM_Q_GREEDY, LUTGEMM_Q_GREEDY_MEAN_OFFSET, LUTGEMM_Q_UNIFORM_RTN, LUTGEMM_Q_ALTERNATING = 0, 1, 2, 3
 LUTGEMM_Y_F16, LUTGEMM_Y_F32, LUTGEMM_ALPHA_SHARED, LUTGEMM_PATH_AUTO = 0, 1, 2, 4
+LUTGEMM_KERNEL_GEMV, LUTGEMM_KERNEL_PAIR, LUTGEMM_KERNEL_QUAD, LUTGEMM_KERNEL_FP4, LUTGEMM_KERNEL_FP16 = 1, 2, 4, 16, 32
 
 _c = ctypes
 _SIGNATURES = {
@@ -53,6 +54,9 @@ _SIGNATURES = {
                                              _c.c_int, _c.c_int, _c.c_int, _c.c_int64, _c.c_int64, _c.c_int, _c.c_uint,
                                              _c.c_void_p, _c.c_size_t, _c.c_void_p]),
     "lutgemm_plan_grid": (_c.c_int, [_c.c_int64, _c.c_int64, _c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.c_void_p]),
+    "lutgemm_plan_gemm": (_c.c_int, [_c.c_int64, _c.c_int64, _c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.c_uint, _c.c_int,
+                                     _c.c_void_p, _c.c_int]),
+    "lutgemm_plan_group": (_c.c_int, [_c.c_void_p, _c.c_void_p, _c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.c_void_p]),
     "lutgemm_stream_read": (_c.c_int, [_c.c_void_p, _c.c_size_t, _c.c_void_p, _c.c_size_t, _c.c_void_p]),
     "lutgemm_strerror": (_c.c_char_p, [_c.c_int]),
 }
@@ -199,6 +203,26 @@ def lutgemm_plan_grid(m, n, q, g, vectors=1, compute_units=0):
     out = (ctypes.c_int * 3)()
     _check(lib().lutgemm_plan_grid(m, n, q, g, vectors, compute_units, ctypes.addressof(out)), "lutgemm_plan_grid")
     return int(out[0]), int(out[1]), int(out[2])
+
+
+def lutgemm_plan_gemm(m, n, q, g, has_offsets, batch, flags=0, compute_units=0):
+    """One tuple per launch of lutgemm_gemm: (kernel, vectors, K groups, tiles or steps per K group, row ranges, K steps
+    per item, row units per stretch)."""
+    out = (ctypes.c_int * (7 * 32))()
+    done = lib().lutgemm_plan_gemm(m, n, q, g, int(has_offsets), batch, flags, compute_units, ctypes.addressof(out), 32)
+    if done < 0:
+        raise LutGemmError(done, "lutgemm_plan_gemm")
+    return [tuple(out[7 * i:7 * i + 7]) for i in range(done)]
+
+
+def lutgemm_plan_group(shapes, q, g, compute_units=0):
+    """(K groups, row ranges) of every layer of a group launch."""
+    m, n = zip(*shapes)
+    out = (ctypes.c_int * (2 * len(m)))()
+    ms, ns = (ctypes.c_int64 * len(m))(*m), (ctypes.c_int64 * len(n))(*n)
+    _check(lib().lutgemm_plan_group(ctypes.addressof(ms), ctypes.addressof(ns), len(m), q, g, compute_units,
+                                    ctypes.addressof(out)), "lutgemm_plan_group")
+    return [tuple(out[2 * i:2 * i + 2]) for i in range(len(m))]
 
 
 # ---- device --------------------------------------------------------------------------
