@@ -1,6 +1,6 @@
 """GPU parity at the full workload sizes, in the launch configuration bench.py times:
 OPT-175B-shaped layers (q = 3, g = 128; every row of every layer, and the small-batch
-sweep 2..32 on FC1 through the lookup path), OPT-13B-shaped layers (q = 4, g = 128) and
+sweep 2..32 on FC1 as lutgemm_gemm runs it without LUTGEMM_PATH_AUTO), OPT-13B-shaped layers (q = 4, g = 128) and
 LLaMA-65B-shaped layers with per-group offsets over a (q, g) sweep, batch 1.  Where rows are
 sampled, the fp64 oracle computes them one by one (first and last row blocks, block
 boundaries of the row splits, random rows)."""
@@ -115,12 +115,13 @@ def _fc1_packed():
 
 @pytest.mark.parametrize("batch", [2, 3, 4, 8, 16, 32])
 def test_small_batch_sweep_on_fc1_shape_lookup_path(batch):
-    # the small-batch sweep of the workload list (paper section 6) through the lookup path
-    # alone (no LUTGEMM_PATH_AUTO), in the grids bench.py times: every vector, every row
+    # the small-batch sweep of the workload list (paper section 6) without LUTGEMM_PATH_AUTO (lookups
+    # for two vectors, the 4-bit-float kernel beyond), in the grids bench.py times: every vector, every row
     m, n = synth.OPT_175B["fc1"]
     q, g = 3, 128
     p, bound = _fc1_packed()
-    grids = {w: L.lutgemm_plan_grid(m, n, q, g, w) for w in (1, 2, 4)}
+    grids = L.lutgemm_plan_gemm(m, n, q, g, False, batch)
+    assert [k[0] for k in grids] == [L.LUTGEMM_KERNEL_PAIR if batch == 2 else L.LUTGEMM_KERNEL_FP4] * (2 if batch == 32 else 1)
     print(f"case batch fc1 m={m} n={n} batch={batch} grids={grids}", flush=True)
     X = synth.activations_fp16(n, seed=5500 + batch, batch=batch)
     Y = run(p, X, f32_out=True)

@@ -220,21 +220,26 @@ def test_mfma_path_rejects_groups_not_multiple_of_64():
 # ---- shared-scale layout (one scale per group, appendix C) ----
 
 def test_auto_path_is_one_of_the_two():
-    # LUTGEMM_PATH_AUTO: by shape and batch alone, the matrix-core path from five vectors on
-    # (three on small layers) where it applies, else the lookup path; bit for bit that path's y
+    # LUTGEMM_PATH_AUTO: by shape and batch alone, what lutgemm_gemm_mfma runs from five vectors on
+    # (three on small layers) where it applies, else what lutgemm_gemm does without the flag; bit for bit
+    # that path's y.  (At g = 128 both ways run the same kernel from three vectors on; at g = 64 three and
+    # four vectors are fp16 operands with the flag and lookups without.)
     m, n, q = 300, 2048, 3
     W = synth.weights_fp16(m, n, seed=5600)
     for g, batch, want_mfma in [(128, 8, True), (128, 5, True), (128, 4, True), (128, 3, True), (128, 2, False),
-                                (128, 1, False), (32, 8, False), (0, 6, True)]:
+                                (128, 1, False), (32, 8, False), (0, 6, True), (64, 4, True), (64, 3, True), (64, 2, False)]:
         print(f"case g={g} batch={batch}", flush=True)
         p = Packed.from_weights(W, q, g, MODES["greedy_z"])
         X = synth.activations_fp16(n, seed=5601 + batch, batch=batch)
+        if g == 64:
+            kernels = [L.lutgemm_plan_gemm(m, n, q, g, True, batch, flags)[0][0] for flags in (0, L.LUTGEMM_PATH_AUTO)]
+            assert (kernels[0] != kernels[1]) == want_mfma
         y_auto = run(p, X, f32_out=True, auto=True)
         y_want = run(p, X, f32_out=True, mfma=want_mfma)
         np.testing.assert_array_equal(y_auto, y_want)
         for b in range(batch):
             check_parity(y_auto[b], _oracle_full(p, X[b]), X[b], _bound(p), f32_out=True)
-    # shared scales: always the lookup path
+    # shared scales: the flag changes nothing
     p = Packed.from_weights(W, q, 128, MODES["rtn"]).share()
     X = synth.activations_fp16(n, seed=5610, batch=8)
     np.testing.assert_array_equal(run(p, X, f32_out=True, auto=True, shared=True), run(p, X, f32_out=True, shared=True))
@@ -434,12 +439,18 @@ def test_extreme_aspect_ratios(m, n, q, g, batch):
             check_parity(ym[b][rows], yref[b], xs[b], bound[rows], f32_out=True)
 
 
-def test_calls_can_be_captured_in_a_hip_graph_and_replayed():
+@pytest.mark.parametrize("q,g,batch,kernels", [
+    (3, 128, 7, [16]),          # (LUTGEMM_KERNEL_FP4)
+    (5, 64, 6, [4, 2]),         # four vectors and two: the quad and the pair kernel
+    (3, 128, 17, [16, 1]),      # sixteen and one
+])
+def test_calls_can_be_captured_in_a_hip_graph_and_replayed(q, g, batch, kernels):
     # serving loops replay captured work: the entry points enqueue kernels only (no allocation,
     # no synchronisation, counters reset by the kernels themselves), so a captured call must
     # give the eager result on every replay, also after the inputs have changed in place
     import torch
-    m, n, q, g, batch = 1500, 3072, 3, 128, 7          # 4 + 2 + 1 vectors: all three lookup kernels
+    m, n = 1500, 3072
+    assert [k[0] for k in L.lutgemm_plan_gemm(m, n, q, g, False, batch)] == kernels
     W = synth.weights_fp16(m, n, seed=9900)
     p = Packed.from_weights(W, q, g)
     wsb = L.lutgemm_workspace_bytes(m, n, q, g, 8, batch)

@@ -2,9 +2,10 @@
 (a workgroup walks more than one table set and carries row sums from tile to tile) in the
 GEMV, pair and quad kernels, crossed with offsets, more than four planes, every scale
 mode and the shared-scale layout; and row ranges longer than the running sums in LDS cover
-(pair and quad kernels).  Every case first asks the library which grid it plans
-(lutgemm_plan_grid) and asserts that the path meant is the path reached; all rows are then
-compared with the fp64 C oracle."""
+(pair and quad kernels).  Every case first asks the library which kernels it launches
+(lutgemm_plan_gemm) on which grid (lutgemm_plan_grid) and asserts that the path meant is the path
+reached; all rows are then compared with the fp64 C oracle.  Some shapes of the same kind run on the
+matrix cores instead (FP4_CASES)."""
 import numpy as np
 import pytest
 
@@ -79,23 +80,30 @@ def test_gemv_several_tiles_per_k_group(m, n, q, g, mode, shared):
     _check_all_rows(p, x, shared=False)
 
 
+def _kernels(m, n, q, g, mode, batch):
+    return [p[0] for p in L.lutgemm_plan_gemm(m, n, q, g, mode != "greedy", batch)]
+
+
 # m, n, q, g, mode, batch, kernel width the case is about (2: pair kernel, 4: quad kernel)
 BATCH_CASES = [
     (40, 65536, 3, 128, "greedy", 2, 2),
-    (640, 40960, 3, 128, "rtn", 2, 2),         # offsets, several row ranges
+    (640, 40960, 3, 64, "rtn", 2, 2),          # offsets, several row ranges
     (640, 40960, 6, 128, "greedy_z", 2, 2),    # more than four planes
     (300, 49152, 3, 32, "rtn", 2, 2),          # one scale set per slot
     (200, 65536, 2, 8, "greedy_z", 2, 2),      # smallest groups
-    (640, 40960, 3, 128, "rtn", 4, 4),
-    (640, 40960, 5, 128, "greedy_z", 3, 4),    # three vectors through the quad kernel, five planes
+    (640, 40960, 3, 64, "rtn", 4, 4),
+    (640, 40960, 5, 64, "greedy_z", 3, 4),     # three vectors through the quad kernel, five planes
+    (640, 40960, 7, 128, "greedy", 4, 4),
     (300, 49152, 4, 32, "rtn", 4, 4),
     (333, 41480, 2, 8, "greedy", 4, 4),        # ragged rows, last tile of 65 chunks
-    (1000, 32768, 3, 128, "greedy", 7, 4),     # 4 + 2 + 1: all three kernels on one layer
+    (1000, 32768, 5, 64, "greedy", 6, 4),      # 4 + 2
+    (1000, 32768, 3, 32, "greedy", 5, 4),      # 4 + 1
 ]
 
 
 @pytest.mark.parametrize("m,n,q,g,mode,batch,width", BATCH_CASES)
 def test_small_batch_several_tiles_per_k_group(m, n, q, g, mode, batch, width):
+    assert width in _kernels(m, n, q, g, mode, batch), "this shape is meant to reach this kernel"
     kg, tpg, rs = L.lutgemm_plan_grid(m, n, q, g, width)
     print(f"case batch m={m} n={n} q={q} g={g} mode={mode} batch={batch}: width {width} grid KG={kg} TPG={tpg} RS={rs}",
           flush=True)
@@ -111,13 +119,14 @@ def test_small_batch_several_tiles_per_k_group(m, n, q, g, mode, batch, width):
 # tile are walked by different instantiations of the same code, one after the other, on
 # the same running sums).  m, n, q, g, mode, batch, kernel width
 MIXED_TILE_CASES = [
-    (640, 20736, 3, 128, "greedy_z", 4, 4),    # 20 tiles + 256 columns; three quarters per K group
-    (2000, 44288, 3, 128, "greedy", 2, 2),     # 43 tiles + 256 columns; three half tiles per K group
+    (640, 20736, 3, 64, "greedy_z", 4, 4),     # 20 tiles + 256 columns; three quarters per K group
+    (2000, 44288, 3, 64, "greedy", 2, 2),      # 43 tiles + 256 columns; three half tiles per K group
 ]
 
 
 @pytest.mark.parametrize("m,n,q,g,mode,batch,width", MIXED_TILE_CASES)
 def test_small_batch_k_group_across_tile_kinds(m, n, q, g, mode, batch, width):
+    assert width in _kernels(m, n, q, g, mode, batch), "this shape is meant to reach this kernel"
     kg, tpg, rs = L.lutgemm_plan_grid(m, n, q, g, width)
     tiles = (n // 8 + 127) // 128
     assert 0 < n // 8 - 128 * (tiles - 1) <= 64, "the last tile is meant to have one sub-slab"
@@ -138,14 +147,15 @@ def test_small_batch_k_group_across_tile_kinds(m, n, q, g, mode, batch, width):
 LONG_RANGE_CASES = [
     (1000000, 72, 3, 8, "rtn", 2, 2),          # one half tile, two stretches
     (1000000, 72, 3, 8, "rtn", 3, 4),          # one quarter, several stretches, three vectors
-    (130000, 1096, 3, 0, "greedy_z", 4, 4),    # two quarters per K group, one K group of quarters that do not exist
+    (130000, 1096, 3, 8, "greedy_z", 4, 4),    # two quarters per K group, one K group of quarters that do not exist
     (65536, 16384, 2, 128, "greedy", 2, 2),    # two half tiles per K group, two stretches
-    (65536, 16384, 2, 128, "greedy", 4, 4),    # eight quarters per K group, two stretches
+    (65536, 16384, 2, 64, "greedy", 4, 4),     # eight quarters per K group, two stretches
 ]
 
 
 @pytest.mark.parametrize("m,n,q,g,mode,batch,width", LONG_RANGE_CASES)
 def test_small_batch_long_row_ranges(m, n, q, g, mode, batch, width):
+    assert width in _kernels(m, n, q, g, mode, batch), "this shape is meant to reach this kernel"
     kg, tpg, rs = L.lutgemm_plan_grid(m, n, q, g, width)
     rb = (m + 15) // 16
     blocks = -(-rb // rs) if width == 2 else 2 * -(-((rb + 1) // 2) // rs)
@@ -154,6 +164,25 @@ def test_small_batch_long_row_ranges(m, n, q, g, mode, batch, width):
     assert blocks > (240 if width == 2 else 120), "this shape is meant to reach row ranges of several stretches"
     W = synth.weights_fp16(m, n, seed=13000 + n + q)
     X = synth.activations_fp16(n, seed=13500 + n + q, batch=batch)
+    p = Packed.from_weights(W, q, g, MODES[mode])
+    del W
+    _check_all_rows(p, X)
+
+
+# Long rows and long row ranges whose batches the 4-bit-float kernel takes.  m, n, q, g, mode, batch
+FP4_CASES = [
+    (640, 40960, 3, 128, "rtn", 2), (640, 40960, 3, 128, "rtn", 4), (640, 40960, 5, 128, "greedy_z", 3),
+    (1000, 32768, 3, 128, "greedy", 7), (640, 20736, 3, 128, "greedy_z", 4), (2000, 44288, 3, 128, "greedy", 2),
+    (130000, 1096, 3, 0, "greedy_z", 4), (65536, 16384, 2, 128, "greedy", 4),
+]
+
+
+@pytest.mark.parametrize("m,n,q,g,mode,batch", FP4_CASES)
+def test_small_batch_on_the_matrix_cores(m, n, q, g, mode, batch):
+    print(f"case fp4 m={m} n={n} q={q} g={g} mode={mode} batch={batch}", flush=True)
+    assert _kernels(m, n, q, g, mode, batch) == [L.LUTGEMM_KERNEL_FP4]
+    W = synth.weights_fp16(m, n, seed=12000 + m + q)
+    X = synth.activations_fp16(n, seed=12500 + m + q, batch=batch)
     p = Packed.from_weights(W, q, g, MODES[mode])
     del W
     _check_all_rows(p, X)
@@ -174,15 +203,20 @@ def test_plan_grid_reports_what_is_launched():
     assert L.lutgemm_plan_grid(*synth.OPT_175B["out"], 3, 128, 1)[1] == 1
 
 
-@pytest.mark.parametrize("m,n,q,g,batch", [(4096, 16384, 3, 128, 1), (2048, 32768, 3, 128, 1), (4096, 16384, 3, 128, 4)])
-def test_split_k_hand_off_over_many_launches(m, n, q, g, batch):
+@pytest.mark.parametrize("m,n,q,g,batch,kernel", [
+    (4096, 16384, 3, 128, 1, L.LUTGEMM_KERNEL_GEMV), (2048, 32768, 3, 128, 1, L.LUTGEMM_KERNEL_GEMV),
+    (4096, 16384, 3, 64, 4, L.LUTGEMM_KERNEL_QUAD), (4096, 16384, 3, 128, 4, L.LUTGEMM_KERNEL_FP4),
+])
+def test_split_k_hand_off_over_many_launches(m, n, q, g, batch, kernel):
     """The cross-group reduction (partials, arrival counter, last workgroup sums) must give the
     same bits on every one of several hundred back-to-back launches that share one workspace,
     while another stream keeps the memory system busy, and those bits must be the oracle's."""
     from gpu_util import make_workspace, torch_cuda
     torch = torch_cuda()
-    kg, tpg, rs = L.lutgemm_plan_grid(m, n, q, g, batch)
+    plan = L.lutgemm_plan_gemm(m, n, q, g, False, batch)
+    kg, tpg, rs = plan[0][2:5]
     print(f"case hand-off m={m} n={n} q={q} g={g} batch={batch}: grid KG={kg} TPG={tpg} RS={rs}", flush=True)
+    assert [p[0] for p in plan] == [kernel]
     assert kg > 1, "this shape is meant to have several K groups"
     W = synth.weights_fp16(m, n, seed=13000 + n + batch)
     p = Packed.from_weights(W, q, g)

@@ -2,7 +2,8 @@
 (two to sixteen activation vectors): at the edges of its row units (64 rows), K steps (128 columns), tiles
 of one and two sub-slabs and vector counts, for every plane count it takes, all scale layouts, and
 for activations its digits do not hold (infinities, NaNs) or hold only just (subnormals beside the
-largest numbers)."""
+largest numbers); sums that go from the registers to y or to the workspace, and row ranges that are
+worked through in several stretches, with and without infinities."""
 import numpy as np
 import pytest
 
@@ -219,3 +220,63 @@ def test_infinite_scale_beside_infinite_activations(batch, g):
     np.testing.assert_array_equal(y[2:], clean[2:])
     assert np.isposinf(y[1]).all()
     assert np.isnan(y[0, 3]) and np.isneginf(np.delete(y[0], 3)).all()
+
+
+def _random_packed(m, n, q, g, seed):
+    """A layer packed without a quantiser: random keys, scales of about 1 / 100."""
+    rng = np.random.default_rng(seed)
+    bits = rng.integers(0, 256, L.lutgemm_bits_bytes(m, n, q), dtype=np.uint8)
+    alpha = (0.01 + 0.002 * rng.random(L.lutgemm_alpha_bytes(m, n, q, g) // 2)).astype(np.float16)
+    return Packed(bits, alpha, None, m, n, q, g)
+
+
+# m, n, q, g, batch, K groups (1 or several), how a row range is worked through: "direct" (a row unit's whole K
+# group is one item: its sums go from the registers to y, or to the workspace where there are several K
+# groups), "even" or "rest" (stretches, the last one full or not)
+ROW_RANGE_CASES = [
+    (1000, 128, 2, 128, 9, 1, "direct"), (977, 128, 3, 128, 6, 1, "direct"), (996, 128, 4, 0, 4, 1, "direct"),
+    (1069, 128, 4, 64, 8, 1, "direct"),
+    (17213, 1600, 4, 0, 12, 2, "direct"), (16506, 1600, 2, 0, 6, 2, "direct"), (17051, 1280, 4, 256, 3, 2, "direct"),
+    (92109, 1600, 1, 0, 16, 1, "rest"), (91165, 1792, 1, 128, 16, 1, "even"), (142689, 3200, 1, 128, 8, 1, "rest"),
+    (779, 125568, 1, 128, 16, 2, "rest"), (582, 120768, 1, 0, 16, 2, "even"), (4673, 79104, 1, 128, 8, 2, "rest"),
+]
+
+
+@pytest.mark.parametrize("m,n,q,g,batch,groups,kind", ROW_RANGE_CASES)
+def test_row_ranges(m, n, q, g, batch, groups, kind):
+    plan = L.lutgemm_plan_gemm(m, n, q, g, False, batch)
+    print(f"case fp4 rows m={m} n={n} q={q} g={g} batch={batch}: {plan}", flush=True)
+    (kernel, _, kg, steps, ranges, run_steps, stretch), = plan
+    units = -(-(-(-m // 64)) // ranges)
+    assert kernel == L.LUTGEMM_KERNEL_FP4 and (kg > 1) == (groups > 1)
+    assert kind == ("direct" if run_steps >= steps else "even" if units % stretch == 0 else "rest")
+    assert kind == "direct" or stretch < units
+    p = _random_packed(m, n, q, g, seed=18000 + m)
+    X = synth.activations_fp16(n, seed=18100 + n, batch=batch)
+    gg = n if g == 0 else g
+    rng = np.random.default_rng(18200)
+    per_range = 64 * units
+    rows = np.unique(np.concatenate([np.arange(min(m, 70)), np.arange(max(0, m - 70), m), rng.integers(0, m, 100),
+                                     np.minimum(per_range + np.arange(-70, 70), m - 1),          # two ranges ...
+                                     np.minimum(64 * stretch + np.arange(-70, 70), m - 1)]))     # ... and stretches meet
+    rows = rows[rows >= 0]
+    bound = row_l1_bound(O.decode_alpha(p.alpha, m, n // gg, q), None, gg)
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, None, X, m, n, q, g, rows=rows)
+    y = run(p, X, f32_out=True)
+    for b in range(batch):
+        check_parity(y[b][rows], y_ref[b], X[b], bound[rows], f32_out=True)
+    np.testing.assert_array_equal(run(p, X, f32_out=True), y)
+    np.testing.assert_array_equal(run(p, X), y.astype(np.float16))
+    # infinities and NaNs of three vectors, in the first, the last and a middle column: +-inf in the rows where all
+    # planes of the column agree in sign, else NaN, and the other vectors untouched
+    special = X.copy()
+    special[0, 0], special[1, n - 1], special[2, n // 2 + 1] = np.inf, -np.inf, np.nan
+    B = L.lutgemm_unpack_bcq(p.bits, m, n, q)
+    want = np.stack([B[:, :, 0], -B[:, :, n - 1]]).astype(np.float32).sum(axis=1) / q
+    want = np.where(np.abs(want) == 1, np.copysign(np.float32(np.inf), want), np.float32(np.nan))
+    del B
+    for f32_out in (True, False):
+        got, clean = run(p, special, f32_out=f32_out), y if f32_out else y.astype(np.float16)
+        np.testing.assert_array_equal(got[3:], clean[3:])
+        np.testing.assert_array_equal(got[:2], want.astype(got.dtype))
+        assert np.isnan(got[2]).all()
