@@ -879,14 +879,14 @@ __device__ __forceinline__ void accumulate_pair(const Unit<Q, I0, QP, 1, AMODE, 
 
 template <int Q, int I0, int PP, int AMODE, bool HAS_Z>
 __device__ __forceinline__ void pair_passes(const GemvParams& p, int64_t tile_base, int rb, int lane, const int (&grp)[4][1],
-                                            const float* partial, int out_row, int tile_T, int t0,
+                                            int tile_T, int t0,
                                             const uint32_t (&lane_base)[4], const f32x2 (&sum_x)[4], float (&acc)[2][4]) {
   constexpr int QP = (Q - I0 < PP) ? Q - I0 : PP;
   Unit<Q, I0, QP, 1, AMODE, HAS_Z> u;
   load_unit<true>(u, p, tile_base, rb, lane, grp, tile_T, t0);
   accumulate_pair(u, lane_base, sum_x, acc);
   if constexpr (I0 + QP < Q)
-    pair_passes<Q, I0 + QP, PP, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, partial, out_row, tile_T, t0, lane_base, sum_x, acc);
+    pair_passes<Q, I0 + QP, PP, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, tile_T, t0, lane_base, sum_x, acc);
 }
 
 // The activations lane L needs for the table build of half tile h (sub-slab h % 2 of K
@@ -986,7 +986,7 @@ __device__ __forceinline__ void pair_tile_body(const GemvParams& p, float* lut, 
   if constexpr (PP < Q) {
     for (int rb = rb0 + wave; rb < rb1; rb += kWaves) {
       float acc[2][4] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
-      pair_passes<Q, 0, PP, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, nullptr, out_row, tile_T, t0, lane_base, sum_x, acc);
+      pair_passes<Q, 0, PP, AMODE, HAS_Z>(p, tile_base, rb, lane, grp, tile_T, t0, lane_base, sum_x, acc);
       int row_in_block;
       const float s0 = quad_rows_reduce(acc[0], lane, &row_in_block);
       const float s1 = quad_rows_reduce(acc[1], lane, &row_in_block);

@@ -106,14 +106,14 @@ __device__ __forceinline__ void accumulate_quad(const Unit<Q, I0, QP, 1, AMODE, 
 
 template <int Q, int I0, int PP, int AMODE, bool HAS_Z>
 __device__ __forceinline__ void quad_passes(const GemvParams& p, int64_t tile_base, int rb, int slab_lane,
-                                            const int (&grp)[4][1], const float* partial, int out_row, int tile_T, int t0,
+                                            const int (&grp)[4][1], int tile_T, int t0,
                                             const uint32_t (&lane_base)[4], const f32x4v (&sum_x)[4], float (&acc)[4][4]) {
   constexpr int QP = (Q - I0 < PP) ? Q - I0 : PP;
   Unit<Q, I0, QP, 1, AMODE, HAS_Z> u;
   load_unit<true>(u, p, tile_base, rb, slab_lane, grp, tile_T, t0);
   accumulate_quad(u, lane_base, sum_x, acc);
   if constexpr (I0 + QP < Q)
-    quad_passes<Q, I0 + QP, PP, AMODE, HAS_Z>(p, tile_base, rb, slab_lane, grp, partial, out_row, tile_T, t0, lane_base,
+    quad_passes<Q, I0 + QP, PP, AMODE, HAS_Z>(p, tile_base, rb, slab_lane, grp, tile_T, t0, lane_base,
                                               sum_x, acc);
 }
 
@@ -279,7 +279,7 @@ __device__ __forceinline__ void quad_quarters(const GemvParams& p, float* lut, i
         for (int v = 0; v < 4; ++v)
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[v][r] = 0.0f;
-        quad_passes<Q, 0, PP, AMODE, HAS_Z>(p, qq.tile_base, rb, slab_lane, qq.grp, nullptr, out_row, qq.tile_T, qq.t0,
+        quad_passes<Q, 0, PP, AMODE, HAS_Z>(p, qq.tile_base, rb, slab_lane, qq.grp, qq.tile_T, qq.t0,
                                             lane_base, sum_x, acc);
         float sv[4];
 #pragma unroll
