@@ -279,9 +279,11 @@ def main():
                           "grid": {"k_groups": kg, "tiles_per_k_group": tpg, "row_ranges": rs}})
 
     # ---- small batch on the FC1 shape (section 6 of the paper), outside the timed regions:
-    # the lookup path (lutgemm_gemm), the plane-wise matrix-core path (lutgemm_gemm_mfma), the
+    # lutgemm_gemm by itself, the plane-wise matrix-core path (lutgemm_gemm_mfma), the
     # dequantise-to-fp16-then-multiply comparison kernel (lutgemm_gemm_dequant_mfma) and
-    # lutgemm_gemm left to choose between the first two, side by side ----
+    # lutgemm_gemm left to choose between the first two, side by side.  gemm_kernels says what the first
+    # is: lookups for one and two vectors, the 4-bit-float kernel (which the second runs as well up to
+    # sixteen vectors) beyond ----
     fc1 = layers[2]
     batch_sweep = []
     for bsz in (() if args.no_batch_sweep else (1, 2, 4, 8, 16, 32)):
@@ -309,7 +311,10 @@ def main():
         us_mfma = timed(L.lutgemm_gemm_mfma, L.LUTGEMM_Y_F16)
         us_dequant = timed(L.lutgemm_gemm_dequant_mfma, L.LUTGEMM_Y_F16)
         us_auto = timed(L.lutgemm_gemm, L.LUTGEMM_Y_F16 | L.LUTGEMM_PATH_AUTO)
-        batch_sweep.append({"batch": bsz, "lut_us": round(us, 2), "lut_us_per_vector": round(us / bsz, 2),
+        names = {L.LUTGEMM_KERNEL_GEMV: "gemv", L.LUTGEMM_KERNEL_PAIR: "pair", L.LUTGEMM_KERNEL_QUAD: "quad",
+                 L.LUTGEMM_KERNEL_FP4: "fp4", L.LUTGEMM_KERNEL_FP16: "fp16"}
+        kernels = [f"{names[k[0]]} x{k[1]}" for k in L.lutgemm_plan_gemm(fc1["m"], fc1["n"], Q, G, False, bsz)]
+        batch_sweep.append({"batch": bsz, "gemm_us": round(us, 2), "gemm_us_per_vector": round(us / bsz, 2), "gemm_kernels": kernels,
                             "mfma_us": round(us_mfma, 2), "mfma_us_per_vector": round(us_mfma / bsz, 2),
                             "dequant_mfma_us": round(us_dequant, 2), "auto_us": round(us_auto, 2)})
         del xb, yb, wsg

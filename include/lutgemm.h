@@ -115,13 +115,16 @@ enum {
      (buffer of lutgemm_alpha_shared_bytes, written by lutgemm_share_scales).  Requires z.
      Results are bit-for-bit those of the per-plane layout holding the same scales.       */
   LUTGEMM_ALPHA_SHARED = 2,
-  /* lutgemm_gemm only: let the library take the matrix-core path (lutgemm_gemm_mfma) where
-     it measured faster on MI355X and is applicable (group size a multiple of 64, per-plane
-     scales): from six activation vectors on, from five on layers of less than 2^28 weights, and from
-     three on layers of at most 2^25.  Section 6 of the paper: the lookup path pays per
-     vector, the matrix cores do not.  Up to sixteen vectors the two ways mostly run the same
-     kernel anyway (see lutgemm_gemm).  Either path meets the same tolerance; which one ran is
-     decided by shape and batch only, so results stay reproducible.                       */
+  /* lutgemm_gemm only: run what lutgemm_gemm_mfma runs where that is applicable (group size a
+     multiple of 64, per-plane scales), from six activation vectors on, from five on layers of less
+     than 2^28 weights, and from three on layers of at most 2^25.  Section 6 of the paper: the
+     lookup path pays per vector, the matrix cores do not.  Up to sixteen vectors the two
+     ways mostly run the same kernel anyway (see lutgemm_gemm), and where they do not the flag is
+     the faster one or within a tenth of it.  At seventeen to some twenty vectors it is up to a
+     seventh slower on most layers (20480 x 5120, q = 4: 52 us against 46 at
+     seventeen, 56 against 62 at 32), faster on rows of some 20000 columns and more.  Either path
+     meets the same tolerance; which one ran is decided by shape and batch only, so results stay
+     reproducible.                                                                        */
   LUTGEMM_PATH_AUTO = 4
 };
 
@@ -207,10 +210,12 @@ int lutgemm_gemv(const void* x, const void* bits, const void* alpha, const void*
    n; the group sizes must then fall in the same class: all multiples of 64, or of 32, or of
    16, else LUTGEMM_EUNSUPPORTED, as are group sizes that are not multiples of 16).  Workspace of lutgemm_group_workspace_bytes(m, n, count, q,
    g, mu) bytes, prepared like any other (lutgemm_workspace_init once).
-   Every layer runs on the grid it would have alone; the workgroups of layer i + 1 follow those
-   of layer i onto the compute units as these become free, so the end of one product (its
-   stragglers, its cross-tile sums) and the start of the next (activation fetch, table build)
-   overlap with streaming instead of leaving the memory system half idle: on the OPT-175B
+   Every layer has the K groups it would have alone.  Where the layers together are more than one
+   round of workgroups, the row ranges of one round are dealt out to them in proportion to their
+   work, unless that would be too uneven (lutgemm_plan_group); then the workgroups of layer i + 1
+   follow those of layer i onto the compute units as these become free.  Either way the end of
+   one product (its stragglers, its cross-tile sums) and the start of the next (activation fetch, table
+   build) overlap with streaming instead of leaving the memory system half idle: on the OPT-175B
    layers the four products take less time than four launches.  The layers must not depend
    on one another: a layer's x must not be another layer's y.  For dependent layers, call
    lutgemm_gemv once per layer on one stream; they may share one workspace.
@@ -244,9 +249,9 @@ size_t lutgemm_static_scratch_bytes(void);
      the binary planes on the matrix cores as 4-bit floats, up to sixteen vectors per launch, from
      three vectors on (two on layers of 256 rows and more, up to 2^28 weights and five planes); odd
      multiples of 64 columns and up to four planes: the same for five to eight vectors at a
-     time.  Nothing is dequantised and no activation is rounded: each is split into five 6-bit
-     digits of its block of 32 columns, of which it needs no more unless it is 2^14 times
-     smaller than the largest there.
+     time.  Nothing is dequantised.  An activation is held as six 6-bit digits of its block of 32
+     columns: exactly, unless it is more than 2^18 times smaller than the largest there, and else to
+     2^-29 of that one (an fp32 sum that holds the largest resolves 2^-24 of it).
    - Else lookups: the vectors are taken four at a time; two or one left over have kernels of
      their own, three left over run as four (the fourth table set repeats the third vector, its
      results are dropped).  One table set per activation vector, each fetched key looked up in
@@ -254,7 +259,10 @@ size_t lutgemm_static_scratch_bytes(void);
      small-batch case discussed in section 6).
    A vector's result does not depend on the values of the other vectors of the call, only on how
    many are processed with it; between these it agrees to the documented tolerance, not bit for
-   bit.  Bitwise reproducible from run to run.                                             */
+   bit.  Bitwise reproducible from run to run.  Infinities and NaNs among the activations reach the
+   rows of their own vector only (and may be NaN where the exact result is an infinity); the
+   same holds for a scale that is not finite and its row.  lutgemm_plan_gemm says which kernels a
+   call launches; there is no way to ask for lookups where the library takes the other kind. */
 int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void* z, void* y,
                  int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,
                  void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -263,8 +271,11 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
    tables of partial sums: each plane's B_i . X runs on the matrix cores, fp32 accumulation, one
    multiplication by the scale per group (section 3.2: y = sum_i A_i o (B_i . x); offset term
    of eq. 3).  Where lutgemm_gemm takes the whole batch to the 4-bit-float kernel in one launch,
-   this is that kernel; else every key byte is expanded to eight fp16 values of +-1, in a
-   kernel whose time does not grow with batch up to 16 vectors.  Requires a group size that is a
+   this is that kernel, except on layers that fp16 operands are faster on (small ones within one K
+   tile; from nine vectors on more of those, small layers of one or two planes and long groups,
+   and few long rows; from thirteen on large layers of very long rows).  Else every key byte is
+   expanded to eight fp16 values of +-1, in a kernel whose time does not grow with batch up to
+   16 vectors.  Requires a group size that is a
    multiple of 64 columns (g == 0, row-wise, included when n % 64 == 0):
    LUTGEMM_EUNSUPPORTED otherwise, as is LUTGEMM_ALPHA_SHARED or LUTGEMM_PATH_AUTO.
    Bitwise reproducible.                                                                  */
@@ -281,7 +292,7 @@ int lutgemm_gemm_mfma(const void* x, const void* bits, const void* alpha, const 
    product to a relative L2 error of about 3e-4 (bound asked of it: 1e-3), not to the 1e-5
    of the other paths' fp32 outputs.  Same restrictions as lutgemm_gemm_mfma.  Bitwise
    reproducible.  Measured beside the plane-wise form on MI355X (49152 x 12288, q = 3): 157 us
-   up to 16 activation vectors against 69 at 8 and 97 at 16, 185 against 167 at 32: rebuilding fp16
+   up to 16 activation vectors against 67 at 8 and 102 at 16, 180 against 168 at 32: rebuilding fp16
    weights buys nothing over multiplying the planes, and costs accuracy.                  */
 int lutgemm_gemm_dequant_mfma(const void* x, const void* bits, const void* alpha, const void* z, void* y,
                               int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,

@@ -1474,7 +1474,7 @@ void plan_lookup_grid(int cus, int vectors, int q, int64_t g, GemvParams* p) {
 // unit; several such layers in one launch are as many rounds of workgroups, each with its own
 // start (activations, tables, first fetch) and the last of them ragged.  One round for all of
 // them together is faster where it can be dealt out evenly, every layer with its share of the
-// compute units: three layers of 5120 x 5120 at q = 4 21.7 -> 12.4 us, of 4096 x 4096 at q = 3 13.7 -> 9.5, of 12288 x
+// compute units: three layers of 5120 x 5120 at q = 4 21.1 -> 11.7 us, of 4096 x 4096 at q = 3 13.7 -> 9.5, of 12288 x
 // 12288 38.6 -> 35.9, eight of 5120 x 5120 at q = 2 39.5 -> 13.5, the four layers of a block of 12288 columns
 // (764 MB) 120.6 -> 115.6.  The K groups stay as
 // planned (a row's sum is the one lutgemm_gemv computes, bit for bit); only the row ranges get
@@ -1614,16 +1614,16 @@ int fp4_rows_per_vector(int vectors, int sb) { return sb > 1 || vectors > 8 ? 1 
 // (or not for it).  Where the lines lie, old path / this kernel in microseconds (MI355X, weights in no
 // cache):
 //   * One scale group per K step, up to six planes: from three vectors on.  49152 x 12288, q = 3:
-//     75 / 57 at 3 and 4 vectors, 113 / 69 at 8, 123 / 97 at 16; 5120 x 5120, q = 4: 15.1 / 10.1, 14.4 / 11.7,
-//     15.7 / 13.9; 8192 x 8192, q = 6 with offsets: 27 / 19, 48 / 23, 50 / 36.  (The old paths there: lookups
-//     up to four or five vectors, fp16 matrix cores above; the lookups, where asked for, are
-//     2 to 5 times slower from five vectors on.)  At seven and eight planes two units do not fit the
-//     registers: 31 / 42 at q = 8.
-//   * Two vectors: 12288 x 12288 19.7 / 18.7, 15360 x 5120 15.8 / 13.2, 1024 x 1024 7.8 / 6.3, but 36864 x 12288
+//     75 / 53 at 3 and 4 vectors, 113 / 67 at 8, 118 / 102 at 16; 5120 x 5120, q = 4: 15.1 / 10.1, 14.4 / 12.1,
+//     15.7 / 14.4; 8192 x 8192, q = 6 with offsets: 27 / 18, 48 / 21, 50 / 31.  (The old paths there: lookups
+//     up to four or five vectors, fp16 matrix cores above, which a few layers go back to where the
+//     caller leaves the choice, see matrix_cores_take_fp4; the lookups are 2 to 5 times slower from
+//     five vectors on.)  At seven and eight planes two units do not fit the registers: 31 / 42 at q = 8.
+//   * Two vectors: 12288 x 12288 20.7 / 17.7, 15360 x 5120, q = 4 15.8 / 13.2, 1024 x 1024 7.8 / 5.5, but 36864 x 12288
 //     40.0 / 42.8, 64 x 5120 6.7 / 7.3, 8192 x 8192 with six planes 18 / 23: layers of 256 rows up to
 //     2^28 weights, up to five planes.
 //   * Two scale groups per step take an operand row per vector and group: from five vectors on
-//     (8192 x 22016, q = 3, g = 64: 62 / 36 at 6, 69 / 39 at 8; at four 36 / 41), up to four planes.
+//     (8192 x 22016, q = 3, g = 64: 62 / 32 at 6, 69 / 32 at 8; at four 33 / 41), up to four planes.
 // The offsets formed inside the four row blocks of a unit are 32-bit, hence the bound on groups.
 int fp4_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
   const int sb = fp4_scale_groups(n, gg);
@@ -1635,25 +1635,26 @@ int fp4_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
 }
 
 // Whether the 4-bit-float kernel is what lutgemm_gemm_mfma runs: where it takes the whole batch in one launch,
-// unless the fp16 operands are faster.  Both timed on 330 layers (0.1 to 500 million weights, q = 1 to 6)
-// at 2 to 16 vectors; microseconds, fp16 / this kernel:
+// unless the fp16 operands are faster.  Both timed on 330 layers (0.1 to 600 million weights, q = 1 to 6)
+// at 3 to 16 vectors; microseconds, fp16 / this kernel:
 //   * Up to eight vectors only on layers within one K tile, for which the fp16 kernel writes y without
-//     a hand-off: 1363 x 320, q = 2 at 5 vectors 5.0 / 5.8, 1607 x 576, q = 4, g = 64 at 8 6.3 / 7.5, but with
-//     offsets 720 x 512, q = 3 6.5 / 5.9, and 15263 x 512, q = 4 6.9 / 6.1.
-//   * From nine on (six matrix instructions per product instead of three) on more of these: 1024 x 1024,
-//     q = 3 7.5 / 7.9, but 15466 x 1024, q = 4 9.9 / 9.2; on small layers of one or two planes and long groups, where
-//     the scaling of six instructions' sums per group is what costs: 2843 x 4352, q = 2, g = 256 9.9 / 11.2; and
-//     on a few rows that are long, 131 x 31232, q = 3 12.3 / 14.0.
+//     a hand-off: 1363 x 320, q = 2 at 5 vectors 5.1 / 5.4, 1607 x 576, q = 4, g = 64 at 8 6.8 / 8.1, but with
+//     offsets 720 x 512, q = 3 6.1 / 5.6, and 15263 x 512, q = 4 7.0 / 6.3.
+//   * From nine on (six matrix instructions per product instead of three) on more of these: 2299 x 896, q = 3
+//     at 12 7.0 / 8.4, but 15466 x 1024, q = 4 9.4 / 8.9; on small layers of one or two planes and long
+//     groups, where the scaling of six instructions' sums per group is what costs: 2843 x 4352, q = 2, g = 256
+//     9.5 / 10.8; and on a few rows that are long, 131 x 31232, q = 3 at 13 12.9 / 14.5.
 //   * From thirteen on rows so long that the digits of a K group crowd the sums of its items out of LDS:
-//     12288 x 49152, q = 3, 16 vectors 119 / 143, 12914 x 37248, q = 3, row-wise 106 / 136, but 8192 x 22016, q = 4 59 / 47.
-// What is decided wrongly costs at most a tenth.
+//     12288 x 49152, q = 3, 16 vectors 120 / 141, 12914 x 37248, q = 3, row-wise 106 / 136, but 8192 x 22016, q = 4 61 / 48.
+// What it chooses takes at most 1.1 times as long as the fp16 kernel, 1.2 times as long as the better one, and
+// 1.005 times as long as that on average.
 bool matrix_cores_take_fp4(int q, int64_t m, int64_t n, int64_t gg, bool has_z, int batch) {
   if (fp4_pass(q, m, n, gg, batch) != batch) return false;
   const int64_t w = m * n;
   if (m > (int64_t)kPlanesMaxUnits * planes_waves(q) * 16 * 256) return true;   // too tall for the fp16 kernel's arrival counters
   if (batch <= 8) {
     if (fp4_scale_groups(n, gg) == 2) return n >= 1024;
-    if (batch > 4 && n > 512 && n <= 768 && w * q <= (int64_t)1 << 22) return false;
+    if (batch > 4 && q <= 4 && n > 512 && n <= 768 && w * q <= (int64_t)1 << 22) return false;
     return !(n < 1024 && q <= 3 && !has_z && w * q <= (int64_t)1 << 22);
   }
   if (n <= 1024) return w * q > (int64_t)1 << 23 && gg <= 256;
@@ -1676,9 +1677,10 @@ GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
 
 // LUTGEMM_PATH_AUTO: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel that gemm_pass takes as
 // well; beyond, the fp16 matrix-core kernel, whose time grows least) for six vectors and more, from
-// five on below 2^28 weights, from three on up to 2^25.  At 17 to some 24 vectors the flag is the slower
-// way on most layers: sixteen of them and the rest in the 4-bit-float kernel take 49152 x 12288, q = 3, at 17 in
-// 140 us where the fp16 kernel takes 165.
+// five on below 2^28 weights, from three on up to 2^25.  At 17 to some 20 vectors the flag is the slower
+// way on most layers: without it (sixteen vectors in the 4-bit-float kernel, then the rest) 20480 x 5120, q = 4
+// takes 46 / 50 / 53 / 62 us at 17 / 20 / 24 / 32 vectors, with it 52 / 53 / 54 / 56; 12288 x 12288, q = 3 51 / 54 / 58 / 73 and
+// 55 / 56 / 57 / 61; but 12288 x 49152 181 / 186 / 206 / 274 and 161 / 162 / 164 / 172.
 bool auto_takes_matrix_cores(unsigned flags, int64_t m, int64_t n, int64_t gg, int batch) {
   return (flags & LUTGEMM_PATH_AUTO) != 0 && (flags & LUTGEMM_ALPHA_SHARED) == 0 && gg % 64 == 0 &&
          (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25));

@@ -41,14 +41,15 @@
 // not depend on who computed what.
 //
 // What bounds it (MI355X, 49152 x 12288, q = 3, g = 128, weights in no cache; microseconds, before: lookups
-// at 4 vectors, fp16 matrix cores beyond): 57 at 4 vectors (before 72), 69 at 8 (113), 97 at 16 (118).
-// Up to eight vectors mostly the weight stream (255 MB, 38 us at the 6.7 TB/s of a read loop), with
+// at 4 vectors, fp16 matrix cores beyond): 53 at 4 vectors (before 72), 67 at 8 (113), 102 at 16 (118).
+// Up to four vectors mostly the weight stream (255 MB, 38 us at the 6.7 TB/s of a read loop), with
 // 2 to 3 us until the digits stand and 2 to 8 for the hand-off around it.  At 16 the matrix and the
-// vector units together: 4320 matrix instructions per SIMD (10 to 11 ns each with random operands, 7.4
-// with zeros: 45 us) and 20,000 vector instructions, on two wavefronts that hide the one
+// vector units together: 5184 matrix instructions per SIMD (10 to 11 ns each with random operands, 7.4
+// with zeros: 54 us) and 24,500 vector instructions, on two wavefronts that hide the one
 // behind the other only in part; the hand-off, 3 MB of partial sums per K group, is most of the
-// rest.  Eight wavefronts at 256 registers: with twelve or sixteen the accumulators spill or it
-// measured slower.
+// rest.  The sixth digit and the second chain are 4 us of the 67 and 9 of the 102.  Eight wavefronts at
+// 256 registers: with twelve or sixteen the accumulators spill or it measured slower; both
+// chains of a plane in flight together measured equal.
 #pragma once
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));

@@ -18,6 +18,7 @@ LDS = 160 * 1024
     (8192, 22016, 4, 128, False, 16, FP4), (12288, 12288, 3, 128, False, 16, FP4),
     (704, 704, 4, 0, False, 12, FP16), (15466, 1024, 4, 128, False, 12, FP4),
     (1363, 320, 2, 0, False, 5, FP16), (720, 512, 3, 128, True, 5, FP4), (15263, 512, 4, 128, False, 5, FP4),
+    (813, 640, 3, 0, True, 5, FP16), (107, 768, 5, 256, False, 8, FP4),
     (1607, 576, 4, 64, False, 8, FP16), (8192, 22016, 2, 64, False, 8, FP4),
     (2843, 4352, 2, 256, False, 12, FP16), (22812, 6144, 2, 256, False, 12, FP4),
     (100000, 16384, 3, 128, False, 16, FP4),     # (too tall for the fp16 kernel, which would refuse it)
