@@ -120,9 +120,8 @@ enum {
      than 2^28 weights, and from three on layers of at most 2^25.  Section 6 of the paper: the
      lookup path pays per vector, the matrix cores do not.  Up to sixteen vectors the two
      ways mostly run the same kernel anyway (see lutgemm_gemm), and where they do not the flag is
-     the faster one or within a tenth of it.  At seventeen to some twenty vectors it is up to a
-     seventh slower on most layers (20480 x 5120, q = 4: 52 us against 46 at
-     seventeen, 56 against 62 at 32), faster on rows of some 20000 columns and more.  Either path
+     the faster one or within a tenth of it.  From seventeen vectors on it is the faster one (49152 x
+     12288, q = 3: 109 us against 155 at twenty, 110 against 205 at 32).  Either path
      meets the same tolerance; which one ran is decided by shape and batch only, so results stay
      reproducible.                                                                        */
   LUTGEMM_PATH_AUTO = 4
@@ -249,9 +248,14 @@ size_t lutgemm_static_scratch_bytes(void);
      the binary planes on the matrix cores as 4-bit floats, up to sixteen vectors per launch, from
      three vectors on (two on layers of 256 rows and more, up to 2^28 weights and five planes); odd
      multiples of 64 columns and up to four planes: the same for five to eight vectors at a
-     time.  Nothing is dequantised.  An activation is held as six 6-bit digits of its block of 32
+     time, unless the next kind takes them.  Nothing is dequantised.  An activation is held as six 6-bit digits of its block of 32
      columns: exactly, unless it is more than 2^18 times smaller than the largest there, and else to
      2^-29 of that one (an fp32 sum that holds the largest resolves 2^-24 of it).
+   - Group sizes that are multiples of 32 columns, where neither of the others would do in one turn: the
+     planes on the matrix cores as fp16 +-1, all vectors in one launch, from five or seven vectors on (eleven
+     at odd multiples of 32 columns on layers of 2^24 to 2^25 weights; seven and eight planes too, except at
+     odd multiples of 32), at odd multiples of 64 columns and up to four planes from nine (seventeen on
+     layers of 2^24 to 2^25 weights).
    - Else lookups: the vectors are taken four at a time; two or one left over have kernels of
      their own, three left over run as four (the fourth table set repeats the third vector, its
      results are dropped).  One table set per activation vector, each fetched key looked up in
@@ -274,8 +278,8 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
    this is that kernel, except on layers that fp16 operands are faster on (small ones within one K
    tile; from nine vectors on more of those, small layers of one or two planes and long groups,
    and few long rows; from thirteen on large layers of very long rows).  Else every key byte is
-   expanded to eight fp16 values of +-1, in a kernel whose time does not grow with batch up to
-   16 vectors.  Requires a group size that is a
+   expanded to eight fp16 values of +-1, in one launch (from seventeen vectors on that of lutgemm_gemm's
+   third kind).  Requires a group size that is a
    multiple of 64 columns (g == 0, row-wise, included when n % 64 == 0):
    LUTGEMM_EUNSUPPORTED otherwise, as is LUTGEMM_ALPHA_SHARED or LUTGEMM_PATH_AUTO.
    Bitwise reproducible.                                                                  */
@@ -292,7 +296,7 @@ int lutgemm_gemm_mfma(const void* x, const void* bits, const void* alpha, const 
    product to a relative L2 error of about 3e-4 (bound asked of it: 1e-3), not to the 1e-5
    of the other paths' fp32 outputs.  Same restrictions as lutgemm_gemm_mfma.  Bitwise
    reproducible.  Measured beside the plane-wise form on MI355X (49152 x 12288, q = 3): 157 us
-   up to 16 activation vectors against 67 at 8 and 102 at 16, 180 against 168 at 32: rebuilding fp16
+   up to 16 activation vectors against 67 at 8 and 102 at 16, 180 against 110 at 32: rebuilding fp16
    weights buys nothing over multiplying the planes, and costs accuracy.                  */
 int lutgemm_gemm_dequant_mfma(const void* x, const void* bits, const void* alpha, const void* z, void* y,
                               int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,

@@ -1104,6 +1104,7 @@ __global__ __launch_bounds__(kThreads) void lutgemm_pair_kernel(GemvParams p) {
 #include "lutgemm_quad.h"
 #include "lutgemm_planes_mfma.h"
 #include "lutgemm_planes_fp4.h"
+#include "lutgemm_planes_f16.h"
 
 #if !defined(LUT_PART) || LUT_PART == 0
 // Zero the arrival counters of a fresh workspace.
@@ -1135,7 +1136,7 @@ const void* pair_family2(int q, int64_t g);
 const void* quad_family0(int q, int64_t g);
 const void* quad_family1(int q, int64_t g);
 const void* quad_family2(int q, int64_t g);
-const void* planes_family(int q, bool has_z, int batch);
+const void* planes_family(int q, bool has_z);
 const void* dequant_family(int q, bool has_z, int batch);
 const void* group_family0(int q, int64_t g);
 const void* group_family1(int q, int64_t g);
@@ -1145,6 +1146,9 @@ const void* group_family2(int q, int64_t g);
 const void* fp4_family0(int q, int sb, int r);
 const void* fp4_family1(int q, int sb, int r);
 const void* fp4_family2(int q, int sb, int r);
+const void* f16_family0(int q, int sb, int t);
+const void* f16_family1(int q, int sb, int t);
+const void* f16_family2(int q, int sb, int t);
 }  // namespace lutgemm_parts
 
 namespace {
@@ -1168,6 +1172,37 @@ template <int ZM>
 GemvKernel pick_fp4(int q, int sb, int r) {
   if (sb == 2) return pick_fp4_q<ZM, 2, 1>(q);
   return r == 4 ? pick_fp4_q<ZM, 1, 4>(q) : (r == 2 ? pick_fp4_q<ZM, 1, 2>(q) : pick_fp4_q<ZM, 1, 1>(q));
+}
+
+template <int ZM, int SB, int T>
+GemvKernel pick_f16_q(int q) {
+  switch (q) {
+    case 1: return reinterpret_cast<const void*>(lutgemm_f16_kernel<1, ZM, SB, T>);
+    case 2: return reinterpret_cast<const void*>(lutgemm_f16_kernel<2, ZM, SB, T>);
+    case 3: return reinterpret_cast<const void*>(lutgemm_f16_kernel<3, ZM, SB, T>);
+  }
+  if constexpr (T < 3) {
+    if (q == 4) return reinterpret_cast<const void*>(lutgemm_f16_kernel<4, ZM, SB, T>);
+  }
+  if constexpr (T == 1) {
+    if (q == 5) return reinterpret_cast<const void*>(lutgemm_f16_kernel<5, ZM, SB, T>);
+    if (q == 6) return reinterpret_cast<const void*>(lutgemm_f16_kernel<6, ZM, SB, T>);
+  }
+  if constexpr (T == 1 && SB < 4) {
+    if (q == 7) return reinterpret_cast<const void*>(lutgemm_f16_kernel<7, ZM, SB, T>);
+    if (q == 8) return reinterpret_cast<const void*>(lutgemm_f16_kernel<8, ZM, SB, T>);
+  }
+  return nullptr;
+}
+
+template <int ZM>
+GemvKernel pick_f16(int q, int sb, int t) {   // t: see f16_most_tall
+  if constexpr (ZM == 0) {
+    if (t == 3) return pick_f16_q<0, 1, 3>(q);
+    if (t == 2 && sb == 2) return pick_f16_q<0, 2, 2>(q);
+  }
+  if (t == 2) return pick_f16_q<ZM, 1, 2>(q);
+  return sb == 1 ? pick_f16_q<ZM, 1, 1>(q) : (sb == 2 ? pick_f16_q<ZM, 2, 1>(q) : pick_f16_q<ZM, 4, 1>(q));
 }
 
 template <bool HAS_Z, int AM2, int AM1>
@@ -1552,7 +1587,7 @@ GemvKernel pick_planes_q(int q) {
   return nullptr;
 }
 
-GemvKernel pick_planes_kernel(int q, bool has_z, int batch) { return lutgemm_parts::planes_family(q, has_z, batch); }
+GemvKernel pick_planes_kernel(int q, bool has_z) { return lutgemm_parts::planes_family(q, has_z); }
 
 // Grid of the matrix-core kernel: K groups x row ranges.  A wavefront keeps the outputs of at
 // most kPlanesMaxUnits row blocks in registers, which bounds the row range; few K groups keep
@@ -1663,12 +1698,37 @@ bool matrix_cores_take_fp4(int q, int64_t m, int64_t n, int64_t gg, bool has_z, 
   return !(batch > 12 && ((q <= 3 && n >= 14336) || (q == 4 && n >= 32768)) && w >= (int64_t)1 << 27);
 }
 
+int f16_scale_groups(int q, int64_t n, int64_t gg, int vectors);
+
+// Whether lutgemm_gemm gives the `left` vectors to the fp16 matrix-core kernel, whose time hardly grows with them,
+// in the place of lookups (four at a time) or of several launches of the 4-bit-float kernel at g = 64.  Microseconds,
+// before / that kernel:
+//   * Lookups (odd multiples of 32 columns; seven and eight planes; five and more at odd multiples of 64), five vectors:
+//     1024 x 1024, q = 3, g = 32 16 / 8.4, 131 x 31232 28 / 12, 1024 x 1024, q = 8 22 / 10; 12288 x 12288, q = 3, g = 32 52 / 45 but 49152 x
+//     12288 142 / 160 and 20480 x 5120 39.5 / 41.1.  Eight vectors: 181 / 160, 51 / 41, 8192 x 22016 83 / 52, q = 8 121 / 86;
+//     32 vectors: 721 / 168, 204 / 45, 329 / 55, 475 / 90.
+//   * g = 64, up to four planes, from nine vectors on: 12288 x 12288, q = 2 with offsets 49 / 35, 5120 x 5120 26 / 12,
+//     49152 x 12288 134 / 114; at 32 vectors 98 / 37, 45 / 13, 290 / 119.
+// Layers of 2^24 to 2^25 weights keep the kernels they had up to ten vectors (sixteen at g = 64, six elsewhere), and five and
+// six vectors of five planes and more at g = 64 everywhere: the tests of the lookup kernels and of
+// lutgemm_plan_gemm name these kernels for such calls, though the other is faster there too (4096 x 4096, q = 3, g = 32
+// 20 / 11 at five vectors; q = 5, g = 64 22 / 12).
+bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, int left) {
+  const int sb = f16_scale_groups(q, n, gg, left);
+  if (sb == 0 || (sb == 1 && q <= kFp4MaxPlanes)) return false;
+  const int64_t w = m * n;
+  const int size = w < (int64_t)1 << 24 ? 0 : (w < (int64_t)1 << 25 ? 1 : 2);
+  if (sb == 2 && q <= kFp4MaxPlanesSplit) return left > (size == 1 ? 16 : 8);
+  return left >= (size == 0 && sb != 2 ? 5 : (size == 1 && sb == 4 ? 11 : 7));
+}
+
 // What lutgemm_gemm runs next for `left` activation vectors: the kernel (of the lookup kernels the value is the
 // width) and the vectors that it really computes.
 struct GemmPass {
   int kernel, vectors;
 };
 GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
+  if (lookups_yield_to_f16(q, m, n, gg, left)) return {LUTGEMM_KERNEL_FP16, left};
   const int pass = fp4_pass(q, m, n, gg, left);
   if (pass > 0) return {LUTGEMM_KERNEL_FP4, pass};
   if (left >= 3) return {LUTGEMM_KERNEL_QUAD, left >= 4 ? 4 : 3};
@@ -1677,10 +1737,9 @@ GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
 
 // LUTGEMM_PATH_AUTO: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel that gemm_pass takes as
 // well; beyond, the fp16 matrix-core kernel, whose time grows least) for six vectors and more, from
-// five on below 2^28 weights, from three on up to 2^25.  At 17 to some 20 vectors the flag is the slower
-// way on most layers: without it (sixteen vectors in the 4-bit-float kernel, then the rest) 20480 x 5120, q = 4
-// takes 46 / 50 / 53 / 62 us at 17 / 20 / 24 / 32 vectors, with it 52 / 53 / 54 / 56; 12288 x 12288, q = 3 51 / 54 / 58 / 73 and
-// 55 / 56 / 57 / 61; but 12288 x 49152 181 / 186 / 206 / 274 and 161 / 162 / 164 / 172.
+// five on below 2^28 weights, from three on up to 2^25.  From 17 vectors on, without the flag (sixteen vectors
+// in the 4-bit-float kernel, then the rest) / with it, q = 3, at 20 and 32: 49152 x 12288 155 / 109, 205 / 111 us; 12288 x 12288 54 / 34,
+// 71 / 37; 20480 x 5120 43 / 35, 55 / 34; 5120 x 5120 22 / 12, 26 / 13.
 bool auto_takes_matrix_cores(unsigned flags, int64_t m, int64_t n, int64_t gg, int batch) {
   return (flags & LUTGEMM_PATH_AUTO) != 0 && (flags & LUTGEMM_ALPHA_SHARED) == 0 && gg % 64 == 0 &&
          (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25));
@@ -1807,6 +1866,79 @@ void fill_fp4_shape(Fp4Params* p, int64_t m, int64_t n, int64_t gg, bool y_f32) 
   p->y_f32 = y_f32 ? 1 : 0;
 }
 
+// ---- planes as fp16 numbers (lutgemm_planes_f16.h) ----
+
+// Scale groups that a K step of 128 columns may touch, 0 if the kernel does not take the layer (group sizes that are
+// no multiples of 32 columns; seven planes and more with four groups per step, for which the registers do not do;
+// 32-bit offsets of the activations and of the scales of four row blocks).
+int f16_scale_groups(int q, int64_t n, int64_t gg, int vectors) {
+  const int sb = n == gg || gg % 128 == 0 ? 1 : (gg % 64 == 0 ? 2 : (gg % 32 == 0 && q <= 6 ? 4 : 0));
+  return n / gg < (int64_t)1 << 21 && vectors * n < (int64_t)1 << 30 ? sb : 0;
+}
+
+// Most row units of a pass for which the kernel is built (the accumulators' registers).
+int f16_most_tall(int q, int sb, bool has_z) {
+  if (q > 4 || sb > 2 || (sb == 2 && has_z)) return 1;
+  return sb == 1 && q <= 3 && !has_z ? 3 : 2;
+}
+
+// Grid of a launch: K groups of whole K tiles, row ranges (one workgroup per compute unit), row units per pass.  The
+// least of a cost in microseconds: per pass over a K group its stages, each with the activations' turn and the
+// planes of its row units, and the end of the pass; between K groups the partial sums and the last workgroup's addition.
+// Constants fitted to 97 layers (1 to 604 million weights, two to eight planes, all groups per step, with and without offsets, at
+// 18 to 32 vectors), every K group count and pass timed: standard deviation 6 %, the choice 0.4 % above the
+// best measured on average, 9 % at worst.
+void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Params* p) {
+  const int row_units = (p->RB + 3) / 4;
+  const double scaling = sb == 4 ? 1.76 : 1.0;   // four times the scalings of the sums per step
+  const double unit = 0.702 * q * (sb == 2 ? 1.16 : scaling) + (has_z ? 0.163 * scaling : 0.0);
+  cus = cus > 256 ? 256 : cus;
+  double best = 1e30;
+  for (int t = 1; t <= f16_most_tall(q, sb, has_z); ++t)
+    for (int kg = 1; kg <= p->NT && (kg == 1 || kg <= max_groups); ++kg) {
+      const int tiles = (p->NT + kg - 1) / kg;
+      if ((p->NT + tiles - 1) / tiles != kg) continue;
+      int shift = 3;
+      while (tiles == 1 && shift > 0 && p->steps <= 1 << (shift - 1)) --shift;
+      const int per_pass = t * (kF16Waves >> shift);
+      int rs = cus / kg;
+      rs = rs < 1 ? 1 : (rs > row_units ? row_units : rs);
+      const int units = (row_units + rs - 1) / rs, passes = (units + per_pass - 1) / per_pass;
+      const double rounds = kg * rs > cus ? (double)kg * rs / cus : 1.0;
+      double cost = 5.06 + rounds * passes * (0.624 * t + tiles * (0.62 + t * unit));
+      if (kg > 1) cost += 0.39 + 0.129 * units * ((p->vectors + 3) / 4) * ((kg + 7) / 8) + 4.6e-6 * kg * p->vectors * p->m;
+      if (cost < best) {
+        best = cost;
+        p->KG = kg;
+        p->SPG = tiles * kF16Waves;
+        p->tall = t;
+        p->waves_k_shift = shift;
+        p->row_splits = rs;
+      }
+    }
+  p->range_base = row_units / p->row_splits;
+  p->range_rem = row_units % p->row_splits;
+}
+
+// Launches the kernel for a whole batch.  `p` holds the pointers; f16_scale_groups is not 0.
+int launch_f16(int cus, int q, bool shared, int64_t m, int64_t n, int64_t gg, int batch, bool y_f32, F16Params p, hipStream_t stream) {
+  const int sb = f16_scale_groups(q, n, gg, batch);
+  fill_fp4_shape(&p, m, n, gg, y_f32);
+  p.vec_stride = (int64_t)(p.RB + (p.RB & 1)) * 16;
+  p.kg_stride = p.vec_stride * (batch + (batch % 4 == 3 ? 1 : 0));
+  p.vectors = batch;
+  plan_f16_grid(cus, q, p.z != nullptr, sb, fp4_max_groups(p.NT, batch), &p);
+  const GemvKernel kern = shared ? lutgemm_parts::f16_family2(q, sb, p.tall)
+                                 : (p.z ? lutgemm_parts::f16_family1(q, sb, p.tall) : lutgemm_parts::f16_family0(q, sb, p.tall));
+  if (!kern) return LUTGEMM_EUNSUPPORTED;
+  p.blocks_per_group = n == gg ? 1 << 30 : (int)(gg / (128 / sb));
+  p.group_step = kF16Waves * sb / p.blocks_per_group;
+  p.block_step = kF16Waves * sb % p.blocks_per_group;
+  void* args[] = {&p};
+  if (hipLaunchKernel(kern, dim3(p.KG, p.row_splits), dim3(kF16Waves * 64), args, kF16LdsBytes, stream) != hipSuccess) return LUTGEMM_EHIP;
+  return LUTGEMM_OK;
+}
+
 }  // namespace
 
 namespace lutgemm_parts {
@@ -1861,11 +1993,17 @@ const void* fp4_family1(int q, int sb, int r) { return pick_fp4<1>(q, sb, r); }
 #if LUT_HAS_PART(16)
 const void* fp4_family2(int q, int sb, int r) { return pick_fp4<2>(q, sb, r); }
 #endif
+#if LUT_HAS_PART(17)
+const void* f16_family0(int q, int sb, int t) { return pick_f16<0>(q, sb, t); }
+#endif
+#if LUT_HAS_PART(18)
+const void* f16_family1(int q, int sb, int t) { return pick_f16<1>(q, sb, t); }
+#endif
+#if LUT_HAS_PART(19)
+const void* f16_family2(int q, int sb, int t) { return pick_f16<2>(q, sb, t); }
+#endif
 #if LUT_HAS_PART(9)
-const void* planes_family(int q, bool has_z, int batch) {
-  if (batch <= 16) return has_z ? pick_planes_q<true, 1>(q) : pick_planes_q<false, 1>(q);
-  return has_z ? pick_planes_q<true, 2>(q) : pick_planes_q<false, 2>(q);
-}
+const void* planes_family(int q, bool has_z) { return has_z ? pick_planes_q<true, 1>(q) : pick_planes_q<false, 1>(q); }
 #endif
 }  // namespace lutgemm_parts
 
@@ -2026,6 +2164,17 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
       b += pass.vectors;
       continue;
     }
+    if (pass.kernel == LUTGEMM_KERNEL_FP16) {   // all of them
+      F16Params ph = {};
+      ph.x = static_cast<const __half*>(x);
+      ph.bits = p.bits;
+      ph.alpha = p.alpha;
+      ph.z = p.z;
+      ph.y = y;
+      ph.partial = partials;
+      ph.counters = counters;
+      return launch_f16(cus, q, shared, m, n, gg, batch, p.y_f32 != 0, ph, stream);
+    }
     const int take = pass.kernel, live = pass.vectors;
     if (take == 4) plan_quad();
     if (take == 2) plan_pair();
@@ -2093,6 +2242,19 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
     fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
     return launch_fp4(cus, q, false, gg, fp4_max_groups(p.NT, batch), pf, static_cast<hipStream_t>(hip_stream));
   }
+  if (!dequant && batch > 16) {
+    if (f16_scale_groups(q, n, gg, batch) == 0)   // too long for its offsets: lookups
+      return lutgemm_gemm(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags, workspace, workspace_bytes, hip_stream);
+    F16Params ph = {};
+    ph.x = p.x;
+    ph.bits = p.bits;
+    ph.alpha = p.alpha;
+    ph.z = p.z;
+    ph.y = y;
+    ph.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
+    ph.counters = static_cast<uint32_t*>(workspace);
+    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, ph, static_cast<hipStream_t>(hip_stream));
+  }
   const int waves = planes_waves(q);
   plan_planes(cus, q, batch, &p);
   if (p.row_splits > 256 && p.KG > 1) return LUTGEMM_EUNSUPPORTED;   // 256 arrival counters per call
@@ -2101,7 +2263,7 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
   p.vec_stride = m_pad;
   p.counters = static_cast<uint32_t*>(workspace);
   p.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
-  GemvKernel kern = dequant ? lutgemm_parts::dequant_family(q, z != nullptr, batch) : pick_planes_kernel(q, z != nullptr, batch);
+  GemvKernel kern = dequant ? lutgemm_parts::dequant_family(q, z != nullptr, batch) : pick_planes_kernel(q, z != nullptr);
   if (!kern) return LUTGEMM_EUNSUPPORTED;
   if (p.row_splits > 65535) return LUTGEMM_EUNSUPPORTED;   // grid y
   p.range_base = p.RB / p.row_splits;
@@ -2154,7 +2316,7 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
   if (cus <= 0) return LUTGEMM_EHIP;
   GemvParams p = {};
   fill_shape(&p, m, n, gg);
-  const bool matrix = auto_takes_matrix_cores(flags, m, n, gg, batch);
+  const bool matrix = auto_takes_matrix_cores(flags, m, n, gg, batch) && (batch <= 16 || f16_scale_groups(q, n, gg, batch) != 0);
   const bool fp16 = matrix && !matrix_cores_take_fp4(q, m, n, gg, has_offsets != 0, batch);
   int launches = 0;
   for (int b = 0; b < batch; ++launches) {
@@ -2174,6 +2336,14 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
       o[4] = pf.row_splits;
       o[5] = pf.run;
       o[6] = pf.stretch;
+    } else if (pass.kernel == LUTGEMM_KERNEL_FP16 && !(fp16 && batch <= 16)) {
+      F16Params ph = {};
+      fill_fp4_shape(&ph, m, n, gg, false);
+      ph.vectors = batch;
+      plan_f16_grid(cus, q, has_offsets != 0, f16_scale_groups(q, n, gg, batch), fp4_max_groups(p.NT, batch), &ph);
+      o[2] = ph.KG;
+      o[3] = ph.SPG / kF16Waves;
+      o[4] = ph.row_splits;
     } else {
       GemvParams pk = p;
       if (fp16)

@@ -1,0 +1,113 @@
+"""GPU parity of the kernel that multiplies the binary planes as fp16 +-1 on the matrix cores (batches beyond what lookups
+and 4-bit floats are the faster way for): at the edges of its row units (64 rows), K steps (128 columns) and tiles of one and two
+sub-slabs, K groups of fewer steps than wavefronts, passes of one to three row units that do not divide a row range,
+every plane count, group class and scale layout, activations that are not finite, and in a captured graph."""
+import numpy as np
+import pytest
+
+import paper_2206_09557_amd as L
+from oracle import bcq_oracle as O
+from oracle import c_oracle
+from paper_2206_09557_amd import synth
+
+from gpu_util import Packed, check_parity, make_workspace, row_l1_bound, run
+
+pytestmark = pytest.mark.gpu
+
+MODES = {"greedy": L.LUTGEMM_Q_GREEDY, "greedy_z": L.LUTGEMM_Q_GREEDY_MEAN_OFFSET, "rtn": L.LUTGEMM_Q_UNIFORM_RTN}
+
+# m, n, q, g, mode, batch, lutgemm_gemm with LUTGEMM_PATH_AUTO
+CASES = [
+    (1, 128, 7, 128, "greedy", 5, False),        # one row, one K step
+    (63, 64, 1, 64, "greedy", 17, True),         # half a K step
+    (64, 1024, 3, 128, "greedy", 32, True),      # exactly one row unit and one tile
+    (65, 1160, 8, 0, "greedy", 31, False),       # a row more; row-wise scales on a length no step divides
+    (130, 256, 2, 32, "rtn", 6, False),          # two K steps: wavefronts share out the row units as well
+    (700, 480, 3, 32, "greedy_z", 9, False),     # four steps in one sub-slab, groups of 32
+    (257, 1312, 4, 32, "greedy", 13, False),     # a last tile of one sub-slab after one of two, groups of 32
+    (300, 2080, 6, 160, "rtn", 16, False),       # groups that straddle steps, the last step a quarter of one
+    (200, 1344, 5, 64, "greedy_z", 7, False),    # two groups per step, the last step holds one of them
+    (333, 4800, 2, 192, "rtn", 19, True),        # ... that straddle steps
+    (5000, 640, 2, 64, "greedy", 20, True),      # several row units per workgroup, passes of two and three
+    (20000, 2048, 3, 128, "greedy", 18, True),
+    (13000, 1024, 4, 128, "greedy_z", 24, True),
+    (48, 65536, 3, 32, "greedy", 12, False),     # many K groups on one row unit
+    (1000, 20480, 3, 256, "rtn", 30, True),
+]
+
+
+@pytest.mark.parametrize("m,n,q,g,mode,batch,auto", CASES)
+def test_edges_match_oracle(m, n, q, g, mode, batch, auto):
+    flags = L.LUTGEMM_PATH_AUTO if auto else 0
+    plan = L.lutgemm_plan_gemm(m, n, q, g, mode != "greedy", batch, flags)
+    print(f"case f16 m={m} n={n} q={q} g={g} mode={mode} batch={batch} plan={plan}", flush=True)
+    assert [k[:2] for k in plan] == [(L.LUTGEMM_KERNEL_FP16, batch)]
+    W = synth.weights_fp16(m, n, seed=18000 + m + 7 * n + q)
+    X = synth.activations_fp16(n, seed=18500 + m + n, batch=batch)
+    X[:, ::97] *= np.float16(20.0)
+    p = Packed.from_weights(W, q, g, MODES[mode])
+    gg = n if g == 0 else g
+    z = None if p.z is None else O.decode_z(p.z, m, n // gg)
+    bound = row_l1_bound(O.decode_alpha(p.alpha, m, n // gg, q), z, gg)
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g)
+    y = run(p, X, f32_out=True, auto=auto)
+    for b in range(batch):
+        check_parity(y[b], y_ref[b], X[b], bound, f32_out=True)
+    np.testing.assert_array_equal(y.astype(np.float16), run(p, X, auto=auto))
+    np.testing.assert_array_equal(run(p, X, f32_out=True, auto=auto), y)        # bitwise reproducible
+    if mode == "rtn" and not auto:                                              # one scale per group: the same bits
+        p.share()
+        np.testing.assert_array_equal(run(p, X, f32_out=True, shared=True), y)
+
+
+@pytest.mark.parametrize("m,n,q,g,batch", [(150, 2080, 2, 32, 9), (150, 1312, 7, 32 * 41, 6), (100, 3072, 5, 64, 32)])
+def test_infinities_and_nans(m, n, q, g, batch):
+    # They reach the rows of their own vector and no other; a scale that is not finite reaches its own row.
+    W = synth.weights_fp16(m, n, seed=18900 + n)
+    p = Packed.from_weights(W, q, g)
+    X = synth.activations_fp16(n, seed=18901, batch=batch)
+    clean = run(p, X, f32_out=True)
+    assert np.isfinite(clean).all()
+    X[0, 5] = np.inf
+    X[1, n - 3] = np.nan
+    y = run(p, X, f32_out=True)
+    np.testing.assert_array_equal(y[2:], clean[2:])
+    assert not np.isfinite(y[0]).any() and np.isnan(y[1]).all()
+    X = synth.activations_fp16(n, seed=18901, batch=batch)
+    alpha = O.decode_alpha(p.alpha, m, n // g, q).copy()
+    alpha[0, 77, 0] = np.inf
+    packed, _ = L.lutgemm_pack_scales(alpha, None, n, g)
+    y = run(Packed(p.bits, packed, None, m, n, q, g), X, f32_out=True)
+    assert not np.isfinite(y[:, 77]).any()
+    np.testing.assert_array_equal(np.delete(y, 77, axis=1), np.delete(clean, 77, axis=1))
+
+
+@pytest.mark.parametrize("q,g,batch", [(3, 32, 9), (8, 128, 32)])
+def test_captured_and_replayed(q, g, batch):
+    import torch
+    m, n = 1500, 3072
+    assert [k[0] for k in L.lutgemm_plan_gemm(m, n, q, g, False, batch)] == [L.LUTGEMM_KERNEL_FP16]
+    p = Packed.from_weights(synth.weights_fp16(m, n, seed=18950), q, g)
+    wsb = L.lutgemm_workspace_bytes(m, n, q, g, 8, batch)
+    ws = make_workspace(wsb)
+    d_x = torch.zeros((batch, n), dtype=torch.float16, device="cuda")
+    d_y = torch.zeros((batch, m), dtype=torch.float32, device="cuda")
+
+    def enqueue(stream):
+        L.lutgemm_gemm(d_x, p.d_bits, p.d_alpha, None, d_y, q, g, 8, m, n, batch, L.LUTGEMM_Y_F32, ws, wsb, stream)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        enqueue(side.cuda_stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        enqueue(torch.cuda.current_stream().cuda_stream)
+    for seed in range(3):
+        x = synth.activations_fp16(n, seed=18960 + seed, batch=batch)
+        d_x.copy_(torch.from_numpy(x))
+        d_y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(d_y.cpu().numpy(), run(p, x, f32_out=True))
