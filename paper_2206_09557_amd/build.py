@@ -6,6 +6,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -14,6 +15,8 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "liblutgemm.so")
 HOST_SOURCE = os.path.join(PKG, "csrc", "lutgemm_host.cpp")
 DEVICE_SOURCE = os.path.join(PKG, "csrc", "lutgemm_device.hip")
+BINDING = os.path.join(PKG, "_binding.so")
+BINDING_SOURCE = os.path.join(PKG, "csrc", "lutgemm_binding.cpp")
 PARTS = 20   # kernel families of lutgemm_device.hip (LUT_PART = 0 .. 19)
 
 HIPCC_FLAGS = [
@@ -77,7 +80,18 @@ def build_library(verbose: bool = True, jobs: int | None = None, report: bool = 
         if verbose:
             print(" ".join(link), flush=True)
         subprocess.run(link, check=True)
+    build_binding(verbose)
     return LIB
+
+
+def build_binding(verbose: bool = True) -> str:
+    """The CPython marshalling of the device calls (no HIP in it)."""
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-o", BINDING, BINDING_SOURCE]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return BINDING
 
 
 if __name__ == "__main__":

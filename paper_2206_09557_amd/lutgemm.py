@@ -1,4 +1,4 @@
-"""ctypes binding of liblutgemm.so: same names as include/lutgemm.h, argument marshalling
+"""Binding of liblutgemm.so (ctypes; the device calls compiled): same names as include/lutgemm.h, argument marshalling
 only.  Host entry points take and return numpy arrays; device entry points take anything
 with a `.data_ptr()` (torch tensors on the GPU) or a raw integer address.  There is no
 fallback: if the built library is absent, loading raises."""
@@ -63,6 +63,7 @@ _SIGNATURES = {
 EXPORTS = tuple(_SIGNATURES)
 
 _lib = None
+_binding = None   # the compiled marshalling of the device calls, see the end of this file
 
 
 class LutGemmError(RuntimeError):
@@ -91,6 +92,9 @@ def lib():
             fn = getattr(handle, name)
             fn.restype, fn.argtypes = res, args
         _lib = handle
+        if _binding is not None:
+            _binding.load({name: ctypes.cast(getattr(handle, name), ctypes.c_void_p).value
+                           for name in _DEVICE_CALLS if hasattr(handle, name)})
     return _lib
 
 
@@ -284,3 +288,17 @@ def lutgemm_gemm_dequant_mfma(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags
     _check(lib().lutgemm_gemm_dequant_mfma(_addr(x), _addr(bits), _addr(alpha), _addr(z), _addr(y), q, g, mu, m, n,
                                            batch, flags, _addr(workspace), workspace_bytes, stream or None),
            "lutgemm_gemm_dequant_mfma")
+
+
+# The calls of a serving loop are bound by this marshalling where the layer is small: csrc/lutgemm_binding.cpp does it
+# for the usual arguments and hands everything else to the functions above.  Before it is built (when this package
+# is imported to build it) they are the entry points themselves: the same calls, 1.1 us slower each.
+_DEVICE_CALLS = ("lutgemm_gemv", "lutgemm_gemm", "lutgemm_gemm_mfma", "lutgemm_gemm_dequant_mfma", "lutgemm_gemv_static",
+                 "lutgemm_gemv_group")
+try:
+    from . import _binding
+except ImportError:
+    _binding = None
+else:
+    _binding.set_up({name: globals()[name] for name in _DEVICE_CALLS}, _check)
+    globals().update({name: getattr(_binding, name) for name in _DEVICE_CALLS})
