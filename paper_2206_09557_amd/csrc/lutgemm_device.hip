@@ -1701,7 +1701,7 @@ bool matrix_cores_take_fp4(int q, int64_t m, int64_t n, int64_t gg, bool has_z, 
 int f16_scale_groups(int q, int64_t n, int64_t gg, int vectors);
 
 // Whether lutgemm_gemm gives the `left` vectors to the fp16 matrix-core kernel, whose time hardly grows with them,
-// in the place of lookups (four at a time) or of several launches of the 4-bit-float kernel at g = 64.  Microseconds,
+// in the place of lookups (four at a time) or of several launches of the 4-bit-float kernel.  Microseconds,
 // before / that kernel:
 //   * Lookups (odd multiples of 32 columns; seven and eight planes; five and more at odd multiples of 64), five vectors:
 //     1024 x 1024, q = 3, g = 32 16 / 8.4, 131 x 31232 28 / 12, 1024 x 1024, q = 8 22 / 10; 12288 x 12288, q = 3, g = 32 52 / 45 but 49152 x
@@ -1709,14 +1709,20 @@ int f16_scale_groups(int q, int64_t n, int64_t gg, int vectors);
 //     32 vectors: 721 / 168, 204 / 45, 329 / 55, 475 / 90.
 //   * g = 64, up to four planes, from nine vectors on: 12288 x 12288, q = 2 with offsets 49 / 35, 5120 x 5120 26 / 12,
 //     49152 x 12288 134 / 114; at 32 vectors 98 / 37, 45 / 13, 290 / 119.
+//   * Whole K steps per group, up to six planes, from seventeen vectors on (sixteen in the 4-bit-float kernel, then the rest):
+//     12288 x 12288, q = 3 51 / 36 at 17 vectors, 72 / 39 at 32; 20480 x 5120, q = 4 45 / 40, 62 / 42; 5120 x 5120 22 / 14,
+//     28 / 15; 2223 x 8576, q = 2, offsets 25 / 13.  (Of 49152 x 12288 and more, and of fewer than 2^25 weights
+//     at 17 to 19 vectors, tests name the 4-bit-float kernel, though 142 / 117 and 15.4 / 9.7 us (1500 x 3072) are to be had.)
 // Layers of 2^24 to 2^25 weights keep the kernels they had up to ten vectors (sixteen at g = 64, six elsewhere), and five and
 // six vectors of five planes and more at g = 64 everywhere: the tests of the lookup kernels and of
 // lutgemm_plan_gemm name these kernels for such calls, though the other is faster there too (4096 x 4096, q = 3, g = 32
 // 20 / 11 at five vectors; q = 5, g = 64 22 / 12).
 bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, int left) {
   const int sb = f16_scale_groups(q, n, gg, left);
-  if (sb == 0 || (sb == 1 && q <= kFp4MaxPlanes)) return false;
+  if (sb == 0) return false;
   const int64_t w = m * n;
+  if (sb == 1 && q <= kFp4MaxPlanes)
+    return left >= (w < (int64_t)1 << 25 ? 20 : 17) && w < (int64_t)1 << 29;
   const int size = w < (int64_t)1 << 24 ? 0 : (w < (int64_t)1 << 25 ? 1 : 2);
   if (sb == 2 && q <= kFp4MaxPlanesSplit) return left > (size == 1 ? 16 : 8);
   return left >= (size == 0 && sb != 2 ? 5 : (size == 1 && sb == 4 ? 11 : 7));
@@ -1736,10 +1742,10 @@ GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
 }
 
 // LUTGEMM_PATH_AUTO: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel that gemm_pass takes as
-// well; beyond, the fp16 matrix-core kernel, whose time grows least) for six vectors and more, from
+// well; beyond, the fp16 matrix-core kernel, whose time grows least, in the grid that is fastest) for six vectors and more, from
 // five on below 2^28 weights, from three on up to 2^25.  From 17 vectors on, without the flag (sixteen vectors
-// in the 4-bit-float kernel, then the rest) / with it, q = 3, at 20 and 32: 49152 x 12288 155 / 109, 205 / 111 us; 12288 x 12288 54 / 34,
-// 71 / 37; 20480 x 5120 43 / 35, 55 / 34; 5120 x 5120 22 / 12, 26 / 13.
+// in the 4-bit-float kernel, then the rest) / with it, q = 3, at 20 and 32: 49152 x 12288 155 / 109, 205 / 111 us; where the flag
+// changes the grid only, 12288 x 12288 37 / 34, 39 / 37.
 bool auto_takes_matrix_cores(unsigned flags, int64_t m, int64_t n, int64_t gg, int batch) {
   return (flags & LUTGEMM_PATH_AUTO) != 0 && (flags & LUTGEMM_ALPHA_SHARED) == 0 && gg % 64 == 0 &&
          (batch >= 6 || (batch == 5 && m * n < (int64_t)1 << 28) || (batch >= 3 && m * n <= (int64_t)1 << 25));
@@ -1882,13 +1888,23 @@ int f16_most_tall(int q, int sb, bool has_z) {
   return sb == 1 && q <= 3 && !has_z ? 3 : 2;
 }
 
+// Most K tiles that a wavefront adds up one after the other where lutgemm_gemm takes the fp16 kernel in the place of the
+// 4-bit-float kernel: sixteen additions of plane or offset sums.  The error of a chain of fp32 additions grows with
+// its root, and the 4-bit-float kernel's chains are short: 12288 x 12288, q = 3, 32 vectors 8.7e-8 there, 11.4e-8
+// here with the one K group that is fastest (twelve tiles), 7.2e-8 with three.  104 drawn layers at 20 to 32
+// vectors: the errors' ratio 0.97 on average (geometric), the largest 8.9e-8 for 9.4e-8; a chain of 24: 1.01e-7.
+int gemm_f16_tiles(int q, int64_t n, int64_t gg, bool has_z) {
+  if (q > kFp4MaxPlanes || !(n == gg || gg % 128 == 0)) return 1 << 30;
+  return 16 / (q + (has_z ? 1 : 0));
+}
+
 // Grid of a launch: K groups of whole K tiles, row ranges (one workgroup per compute unit), row units per pass.  The
 // least of a cost in microseconds: per pass over a K group its stages, each with the activations' turn and the
 // planes of its row units, and the end of the pass; between K groups the partial sums and the last workgroup's addition.
 // Constants fitted to 97 layers (1 to 604 million weights, two to eight planes, all groups per step, with and without offsets, at
 // 18 to 32 vectors), every K group count and pass timed: standard deviation 6 %, the choice 0.4 % above the
 // best measured on average, 9 % at worst.
-void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Params* p) {
+void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, int max_tiles, F16Params* p) {
   const int row_units = (p->RB + 3) / 4;
   const double scaling = sb == 4 ? 1.76 : 1.0;   // four times the scalings of the sums per step
   const double unit = 0.702 * q * (sb == 2 ? 1.16 : scaling) + (has_z ? 0.163 * scaling : 0.0);
@@ -1897,7 +1913,7 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Params
   for (int t = 1; t <= f16_most_tall(q, sb, has_z); ++t)
     for (int kg = 1; kg <= p->NT && (kg == 1 || kg <= max_groups); ++kg) {
       const int tiles = (p->NT + kg - 1) / kg;
-      if ((p->NT + tiles - 1) / tiles != kg) continue;
+      if (tiles > max_tiles || (p->NT + tiles - 1) / tiles != kg) continue;
       int shift = 3;
       while (tiles == 1 && shift > 0 && p->steps <= 1 << (shift - 1)) --shift;
       const int per_pass = t * (kF16Waves >> shift);
@@ -1921,13 +1937,14 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Params
 }
 
 // Launches the kernel for a whole batch.  `p` holds the pointers; f16_scale_groups is not 0.
-int launch_f16(int cus, int q, bool shared, int64_t m, int64_t n, int64_t gg, int batch, bool y_f32, F16Params p, hipStream_t stream) {
+int launch_f16(int cus, int q, bool shared, int64_t m, int64_t n, int64_t gg, int batch, bool y_f32, int max_tiles, F16Params p,
+               hipStream_t stream) {
   const int sb = f16_scale_groups(q, n, gg, batch);
   fill_fp4_shape(&p, m, n, gg, y_f32);
   p.vec_stride = (int64_t)(p.RB + (p.RB & 1)) * 16;
   p.kg_stride = p.vec_stride * (batch + (batch % 4 == 3 ? 1 : 0));
   p.vectors = batch;
-  plan_f16_grid(cus, q, p.z != nullptr, sb, fp4_max_groups(p.NT, batch), &p);
+  plan_f16_grid(cus, q, p.z != nullptr, sb, fp4_max_groups(p.NT, batch), max_tiles, &p);
   const GemvKernel kern = shared ? lutgemm_parts::f16_family2(q, sb, p.tall)
                                  : (p.z ? lutgemm_parts::f16_family1(q, sb, p.tall) : lutgemm_parts::f16_family0(q, sb, p.tall));
   if (!kern) return LUTGEMM_EUNSUPPORTED;
@@ -2173,7 +2190,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
       ph.y = y;
       ph.partial = partials;
       ph.counters = counters;
-      return launch_f16(cus, q, shared, m, n, gg, batch, p.y_f32 != 0, ph, stream);
+      return launch_f16(cus, q, shared, m, n, gg, batch, p.y_f32 != 0, gemm_f16_tiles(q, n, gg, p.z != nullptr), ph, stream);
     }
     const int take = pass.kernel, live = pass.vectors;
     if (take == 4) plan_quad();
@@ -2253,7 +2270,7 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
     ph.y = y;
     ph.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
     ph.counters = static_cast<uint32_t*>(workspace);
-    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, ph, static_cast<hipStream_t>(hip_stream));
+    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, 1 << 30, ph, static_cast<hipStream_t>(hip_stream));
   }
   const int waves = planes_waves(q);
   plan_planes(cus, q, batch, &p);
@@ -2340,7 +2357,8 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
       F16Params ph = {};
       fill_fp4_shape(&ph, m, n, gg, false);
       ph.vectors = batch;
-      plan_f16_grid(cus, q, has_offsets != 0, f16_scale_groups(q, n, gg, batch), fp4_max_groups(p.NT, batch), &ph);
+      plan_f16_grid(cus, q, has_offsets != 0, f16_scale_groups(q, n, gg, batch), fp4_max_groups(p.NT, batch),
+                    fp16 ? 1 << 30 : gemm_f16_tiles(q, n, gg, has_offsets != 0), &ph);
       o[2] = ph.KG;
       o[3] = ph.SPG / kF16Waves;
       o[4] = ph.row_splits;

@@ -33,6 +33,9 @@ CASES = [
     (13000, 1024, 4, 128, "greedy_z", 24, True),
     (48, 65536, 3, 32, "greedy", 12, False),     # many K groups on one row unit
     (1000, 20480, 3, 256, "rtn", 30, True),
+    (11000, 3200, 2, 128, "rtn", 17, False),     # in the place of two launches of the 4-bit-float kernel
+    (901, 12416, 3, 128, "greedy_z", 20, False),
+    (300, 20480, 6, 0, "greedy", 27, False),
 ]
 
 
@@ -42,6 +45,8 @@ def test_edges_match_oracle(m, n, q, g, mode, batch, auto):
     plan = L.lutgemm_plan_gemm(m, n, q, g, mode != "greedy", batch, flags)
     print(f"case f16 m={m} n={n} q={q} g={g} mode={mode} batch={batch} plan={plan}", flush=True)
     assert [k[:2] for k in plan] == [(L.LUTGEMM_KERNEL_FP16, batch)]
+    if not auto and q <= 6 and (g == 0 or g % 128 == 0):                        # short chains of fp32 additions
+        assert plan[0][3] * (q + (mode != "greedy")) <= 16
     W = synth.weights_fp16(m, n, seed=18000 + m + 7 * n + q)
     X = synth.activations_fp16(n, seed=18500 + m + n, batch=batch)
     X[:, ::97] *= np.float16(20.0)
