@@ -1728,13 +1728,14 @@ bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, int left) {
   return left >= (size == 0 && sb != 2 ? 5 : (size == 1 && sb == 4 ? 11 : 7));
 }
 
-// What lutgemm_gemm runs next for `left` activation vectors: the kernel (of the lookup kernels the value is the
-// width) and the vectors that it really computes.
+// What lutgemm_gemm runs next for the `left` last activation vectors of `batch`: the kernel (of the lookup kernels
+// the value is the width) and the vectors that it really computes.  The fp16 kernel is launched for whole batches: of a
+// batch that is beyond its offsets the last vectors might not be.
 struct GemmPass {
   int kernel, vectors;
 };
-GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int left) {
-  if (lookups_yield_to_f16(q, m, n, gg, left)) return {LUTGEMM_KERNEL_FP16, left};
+GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int batch, int left) {
+  if (left == batch && lookups_yield_to_f16(q, m, n, gg, left)) return {LUTGEMM_KERNEL_FP16, left};
   const int pass = fp4_pass(q, m, n, gg, left);
   if (pass > 0) return {LUTGEMM_KERNEL_FP4, pass};
   if (left >= 3) return {LUTGEMM_KERNEL_QUAD, left >= 4 ? 4 : 3};
@@ -2169,7 +2170,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   pf.vec_stride = m_pad;
   fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
   for (int b = 0; b < batch;) {
-    const GemmPass pass = gemm_pass(q, m, n, gg, batch - b);
+    const GemmPass pass = gemm_pass(q, m, n, gg, batch, batch - b);
     if (pass.kernel == LUTGEMM_KERNEL_FP4) {
       pf.x = static_cast<const __half*>(x) + (int64_t)b * n;
       pf.y = static_cast<char*>(y) + (int64_t)b * m * y_elem;
@@ -2338,7 +2339,7 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
   int launches = 0;
   for (int b = 0; b < batch; ++launches) {
     if (launches == max_launches) return LUTGEMM_EWORKSPACE;
-    const GemmPass pass = fp16 ? GemmPass{LUTGEMM_KERNEL_FP16, batch} : gemm_pass(q, m, n, gg, batch - b);
+    const GemmPass pass = fp16 ? GemmPass{LUTGEMM_KERNEL_FP16, batch} : gemm_pass(q, m, n, gg, batch, batch - b);
     int* o = out + 7 * launches;
     o[0] = pass.kernel;
     o[1] = pass.vectors;

@@ -86,3 +86,13 @@ def test_plan_group_shares_one_round():
     few = [(1024, 1024), (2048, 1024)]
     assert [(kg, rs) for kg, rs in L.lutgemm_plan_group(few, 3, 128, 256)] == \
         [L.lutgemm_plan_grid(m, n, 3, 128, 1, 256)[::2] for m, n in few]
+
+
+# The fp16 kernel's offsets reach 2^30 activations.  What is left of a batch beyond them after some lookups would fit, but
+# the kernel is launched for whole batches.
+@pytest.mark.parametrize("q,g", [(3, 96), (7, 192), (5, 192)])
+def test_batches_beyond_the_offsets_of_the_fp16_kernel(q, g):
+    n = g * (2 ** 26 // g)
+    assert [p[:2] for p in L.lutgemm_plan_gemm(16, n, q, g, False, 15, 0, 256)] == [(FP16, 15)]
+    plan = L.lutgemm_plan_gemm(16, n, q, g, False, 17, 0, 256)
+    assert sum(p[1] for p in plan) == 17 and FP16 not in [p[0] for p in plan]
