@@ -280,8 +280,9 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
    this is that kernel, except on layers that fp16 operands are faster on (small ones within one K
    tile; from nine vectors on more of those, small layers of one or two planes and long groups,
    and few long rows; from thirteen on large layers of very long rows).  Else every key byte is
-   expanded to eight fp16 values of +-1, in one launch (from seventeen vectors on that of lutgemm_gemm's
-   third kind).  Requires a group size that is a
+   expanded to eight fp16 values of +-1, in one launch: in registers, as lutgemm_gemm's fp16 kind is, from
+   seventeen vectors on, of five planes and more on rows of more than 1024 columns, and from nine vectors on of one or two planes
+   without offsets on layers of 2^27 weights and more and at least 14336 columns; from a table elsewhere.  Requires a group size that is a
    multiple of 64 columns (g == 0, row-wise, included when n % 64 == 0):
    LUTGEMM_EUNSUPPORTED otherwise, as is LUTGEMM_ALPHA_SHARED or LUTGEMM_PATH_AUTO.
    Bitwise reproducible.                                                                  */
@@ -319,7 +320,7 @@ int lutgemm_gemm_dequant_mfma(const void* x, const void* bits, const void* alpha
    Tests use it to show which code path a shape reaches; tuning scripts to explain a time.
    The choice can be overridden for sweeps by environment variables read once per process
    (LUTGEMM_TPG / LUTGEMM_RS for vectors = 1, LUTGEMM_PAIR_TPG / _RS, LUTGEMM_QUAD_TPG / _RS,
-   LUTGEMM_MFMA_TPG: tiles per K group, row ranges); results do not depend on the grid
+   LUTGEMM_MFMA_TPG, of the kernels that expand keys from a table: tiles per K group, row ranges); results do not depend on the grid
    beyond the order of the additions.
    LUTGEMM_EINVAL for malformed arguments, LUTGEMM_EHIP if the device cannot be asked.  */
 int lutgemm_plan_grid(int64_t m, int64_t n, int q, int g, int vectors, int compute_units, int* out);

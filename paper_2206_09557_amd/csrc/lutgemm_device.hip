@@ -1742,6 +1742,29 @@ GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int batch, int left)
   return left == 2 ? GemmPass{LUTGEMM_KERNEL_PAIR, 2} : GemmPass{LUTGEMM_KERNEL_GEMV, 1};
 }
 
+// Whether lutgemm_gemm_mfma, where it does not run the 4-bit-float kernel, makes the fp16 operands in registers
+// (lutgemm_planes_f16.h) and not from the table in LDS.  Beyond sixteen vectors always.  Up to sixteen, table / registers in
+// microseconds (200 layers of 0.1 to 600 million weights, 1 to 16 vectors):
+//   * Five planes and more, whose workgroups have only four wavefronts in the table's kernel: 12288 x 12288, q = 8, 8 vectors 104 / 83,
+//     4096 x 4096, q = 8 19.6 / 16.2, 833 x 42496, q = 7 50 / 28, 5594 x 2432, q = 7, g = 64 29 / 21, 89 x 5312, q = 5 12.6 / 11.2, the
+//     least gain 48323 x 1152, q = 7 56.5 / 56.1.  But within one K tile, where the table's kernel starts faster, 6646 x 320
+//     9.0 / 14.0, 2474 x 384 9.2 / 11.6.
+//   * One or two planes without offsets, large layers of long rows, from nine vectors on: 7344 x 29696, q = 1, g = 64 38 / 33,
+//     7852 x 23360, q = 2 48 / 40, 13335 x 19008, q = 1, row-wise 40 / 37; but with offsets 5576 x 43648 46 / 52, and
+//     of three and four planes 8449 x 18240 57 / 67 (though 9799 x 16640 66 / 65).
+bool matrix_cores_take_f16(int q, int64_t m, int64_t n, int64_t gg, bool has_z, int batch) {
+  if (f16_scale_groups(q, n, gg, batch) == 0) return false;
+  if (batch > 16) return true;
+  if (q >= 5) return n > 1024;
+  return q <= 2 && !has_z && batch >= 9 && n >= 14336 && m * n >= (int64_t)1 << 27;
+}
+
+// Most K tiles that a wavefront adds up one after the other there: beyond sixteen vectors any number, below so many
+// that the error against 64 bits stays below the table's kernel's, 96 additions (12288 x 12288, q = 8, row-wise 1.1e-7 for
+// 1.3e-7; but 7446 x 27264, q = 7, row-wise in one chain of 189 1.9e-7 for 1.4e-7, in three
+// 1.4e-7).  60 layers: 0.48 of that error on average, 1.9e-7 for 4.3e-7 at worst.
+int matrix_f16_tiles(int q, bool has_z, int batch) { return batch > 16 ? 1 << 30 : 96 / (q + (has_z ? 1 : 0)); }
+
 // LUTGEMM_PATH_AUTO: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel that gemm_pass takes as
 // well; beyond, the fp16 matrix-core kernel, whose time grows least, in the grid that is fastest) for six vectors and more, from
 // five on below 2^28 weights, from three on up to 2^25.  From 17 vectors on, without the flag (sixteen vectors
@@ -2260,9 +2283,9 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
     fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
     return launch_fp4(cus, q, false, gg, fp4_max_groups(p.NT, batch), pf, static_cast<hipStream_t>(hip_stream));
   }
-  if (!dequant && batch > 16) {
-    if (f16_scale_groups(q, n, gg, batch) == 0)   // too long for its offsets: lookups
-      return lutgemm_gemm(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags, workspace, workspace_bytes, hip_stream);
+  if (!dequant && batch > 16 && f16_scale_groups(q, n, gg, batch) == 0)   // too long for its offsets: lookups
+    return lutgemm_gemm(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags, workspace, workspace_bytes, hip_stream);
+  if (!dequant && matrix_cores_take_f16(q, m, n, gg, z != nullptr, batch)) {
     F16Params ph = {};
     ph.x = p.x;
     ph.bits = p.bits;
@@ -2271,7 +2294,8 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
     ph.y = y;
     ph.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
     ph.counters = static_cast<uint32_t*>(workspace);
-    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, 1 << 30, ph, static_cast<hipStream_t>(hip_stream));
+    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, matrix_f16_tiles(q, z != nullptr, batch), ph,
+                      static_cast<hipStream_t>(hip_stream));
   }
   const int waves = planes_waves(q);
   plan_planes(cus, q, batch, &p);
@@ -2354,12 +2378,12 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
       o[4] = pf.row_splits;
       o[5] = pf.run;
       o[6] = pf.stretch;
-    } else if (pass.kernel == LUTGEMM_KERNEL_FP16 && !(fp16 && batch <= 16)) {
+    } else if (pass.kernel == LUTGEMM_KERNEL_FP16 && (!fp16 || matrix_cores_take_f16(q, m, n, gg, has_offsets != 0, batch))) {
       F16Params ph = {};
       fill_fp4_shape(&ph, m, n, gg, false);
       ph.vectors = batch;
       plan_f16_grid(cus, q, has_offsets != 0, f16_scale_groups(q, n, gg, batch), fp4_max_groups(p.NT, batch),
-                    fp16 ? 1 << 30 : gemm_f16_tiles(q, n, gg, has_offsets != 0), &ph);
+                    fp16 ? matrix_f16_tiles(q, has_offsets != 0, batch) : gemm_f16_tiles(q, n, gg, has_offsets != 0), &ph);
       o[2] = ph.KG;
       o[3] = ph.SPG / kF16Waves;
       o[4] = ph.row_splits;

@@ -8,7 +8,8 @@
 // accumulation is fp32), and the group's scale multiplies the accumulator once per group
 // (section 3.2 rule 2).  This is the alternative the paper's discussion of batch points to
 // (section 6: with growing batch the table lookups become the limit): its cost does not grow
-// with batch up to 16 vectors, which is what is left to it (lutgemm_planes_f16.h takes more).
+// with batch up to 16 vectors, which is what is left to it, and mostly of up to four planes (lutgemm_planes_f16.h
+// takes the others).
 //
 // Work split: a workgroup owns a row range and a K group (a run of K tiles) and keeps the
 // outputs of its row blocks in registers across the tiles of the group; K groups are combined

@@ -36,6 +36,10 @@ CASES = [
     (11000, 3200, 2, 128, "rtn", 17, False),     # in the place of two launches of the 4-bit-float kernel
     (901, 12416, 3, 128, "greedy_z", 20, False),
     (300, 20480, 6, 0, "greedy", 27, False),
+    (65, 1088, 5, 64, "greedy", 6, True),        # up to sixteen vectors of the matrix-core path: many planes ...
+    (50, 2176, 8, 128, "rtn", 16, True),
+    (130, 1280, 7, 0, "greedy_z", 3, True),
+    (8200, 16448, 1, 64, "greedy", 13, True),    # ... and large layers of long rows
 ]
 
 
@@ -63,6 +67,20 @@ def test_edges_match_oracle(m, n, q, g, mode, batch, auto):
     if mode == "rtn" and not auto:                                              # one scale per group: the same bits
         p.share()
         np.testing.assert_array_equal(run(p, X, f32_out=True, shared=True), y)
+
+
+# lutgemm_gemm_mfma below three vectors, where a workspace holds the fewest K groups.
+@pytest.mark.parametrize("m,n,q,g,batch", [(65, 1088, 5, 64, 1), (17, 20480, 8, 128, 1), (130, 9280, 6, 64, 2), (1, 1280, 7, 0, 2)])
+def test_one_and_two_vectors(m, n, q, g, batch):
+    p = Packed.from_weights(synth.weights_fp16(m, n, seed=18800 + n), q, g)
+    X = synth.activations_fp16(n, seed=18801 + n, batch=batch)
+    gg = n if g == 0 else g
+    bound = row_l1_bound(O.decode_alpha(p.alpha, m, n // gg, q), None, gg)
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, None, X, m, n, q, g)
+    y = run(p, X, f32_out=True, mfma=True)
+    for b in range(batch):
+        check_parity(y[b], y_ref[b], X[b], bound, f32_out=True)
+    np.testing.assert_array_equal(run(p, X, f32_out=True, mfma=True), y)
 
 
 @pytest.mark.parametrize("m,n,q,g,batch", [(150, 2080, 2, 32, 9), (150, 1312, 7, 32 * 41, 6), (100, 3072, 5, 64, 32)])
