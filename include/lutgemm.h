@@ -331,9 +331,10 @@ int lutgemm_plan_grid(int64_t m, int64_t n, int q, int g, int vectors, int compu
      out[0]   the kernel, LUTGEMM_KERNEL_*,       out[1]   the activation vectors that it computes,
      out[2]   K groups,                           out[4]   row ranges,
      out[3]   K tiles per K group as lutgemm_plan_grid counts them; K steps of 128 columns for
-              LUTGEMM_KERNEL_FP4, and for this kernel only (else 0)
-     out[5]   K steps of an item (what one wavefront adds up),
-     out[6]   row units of 64 rows that a workgroup works on at a time.
+              LUTGEMM_KERNEL_FP4
+     out[5]   what a wavefront adds up one after the other in fp32: K steps of an item for LUTGEMM_KERNEL_FP4, K
+              tiles for LUTGEMM_KERNEL_FP16 in registers (see lutgemm_gemm_mfma), else 0
+     out[6]   for these two, row units of 64 rows that a workgroup works on at a time, else 0
    compute_units as in lutgemm_plan_grid, and for the same purpose.  Returns the number of launches;
    LUTGEMM_EWORKSPACE if there are more than max_launches, LUTGEMM_EINVAL or LUTGEMM_EHIP as there. */
 enum {

@@ -1637,6 +1637,7 @@ void plan_planes(int cus, int q, int batch, GemvParams* p) {
 // ---- planes as 4-bit floats (lutgemm_planes_fp4.h) ----
 
 constexpr int kLdsBytes = 160 * 1024;
+static_assert(kF16LdsBytes + 2 * kF16RunningBytes <= kLdsBytes, "sums of the chains of two row units");
 constexpr int kFp4MaxPlanes = 6, kFp4MaxPlanesSplit = 4;   // planes of layers with one and two scale groups per K step
 
 // Scale groups that a K step of 128 columns may touch, 0 if the kernel does not take the group size.
@@ -1758,12 +1759,6 @@ bool matrix_cores_take_f16(int q, int64_t m, int64_t n, int64_t gg, bool has_z, 
   if (q >= 5) return n > 1024;
   return q <= 2 && !has_z && batch >= 9 && n >= 14336 && m * n >= (int64_t)1 << 27;
 }
-
-// Most K tiles that a wavefront adds up one after the other there: beyond sixteen vectors any number, below so many
-// that the error against 64 bits stays below the table's kernel's, 96 additions (12288 x 12288, q = 8, row-wise 1.1e-7 for
-// 1.3e-7; but 7446 x 27264, q = 7, row-wise in one chain of 189 1.9e-7 for 1.4e-7, in three
-// 1.4e-7).  60 layers: 0.48 of that error on average, 1.9e-7 for 4.3e-7 at worst.
-int matrix_f16_tiles(int q, bool has_z, int batch) { return batch > 16 ? 1 << 30 : 96 / (q + (has_z ? 1 : 0)); }
 
 // LUTGEMM_PATH_AUTO: what lutgemm_gemm_mfma runs (up to 16 vectors mostly the kernel that gemm_pass takes as
 // well; beyond, the fp16 matrix-core kernel, whose time grows least, in the grid that is fastest) for six vectors and more, from
@@ -1912,14 +1907,43 @@ int f16_most_tall(int q, int sb, bool has_z) {
   return sb == 1 && q <= 3 && !has_z ? 3 : 2;
 }
 
-// Most K tiles that a wavefront adds up one after the other where lutgemm_gemm takes the fp16 kernel in the place of the
-// 4-bit-float kernel: sixteen additions of plane or offset sums.  The error of a chain of fp32 additions grows with
-// its root, and the 4-bit-float kernel's chains are short: 12288 x 12288, q = 3, 32 vectors 8.7e-8 there, 11.4e-8
-// here with the one K group that is fastest (twelve tiles), 7.2e-8 with three.  104 drawn layers at 20 to 32
-// vectors: the errors' ratio 0.97 on average (geometric), the largest 8.9e-8 for 9.4e-8; a chain of 24: 1.01e-7.
-int gemm_f16_tiles(int q, int64_t n, int64_t gg, bool has_z) {
-  if (q > kFp4MaxPlanes || !(n == gg || gg % 128 == 0)) return 1 << 30;
-  return 16 / (q + (has_z ? 1 : 0));
+// Most K tiles that a wavefront of the fp16 kernel adds up one after the other in fp32 (a chain; behind it sums are 64 bits),
+// and most of a K group.  A tile is one addition per plane and offset and scale group of a K step.  The error against
+// 64-bit sums (relative, 2-norm) of chains of N additions is about sqrt(20 + 3.2 N) 1e-8: 0.85e-7 at 16, 1.0 at 24, 1.2 at 36 to
+// 48, 1.9 at 98, 3.3 at 352.  A chain is no longer than keeps it at what the call had from the kernel before:
+//   * Planes of up to six and whole K steps per group, once the 4-bit-float kernel's: sixteen, by K groups (12288 x 12288, q = 3, 32
+//     vectors 0.87e-7 there, 1.14 in one chain of 36, 0.72 with three K groups).  104 drawn layers at 20 to 32 vectors: 0.97 of that
+//     kernel's error on average.
+//   * Two scale groups per step and up to four planes, also once the 4-bit-float kernel's: twelve.  1e-7 there / in one chain per
+//     K group / so: 16384 x 12288, q = 4 0.98 / 1.74 / 0.72, 12288 x 12288, q = 2, offsets, 32 vectors 0.69 / 1.48 / 0.59 (us 101 /
+//     41 / 46.5), 5793 x 7040, q = 2 0.69 / 0.85 / 0.68.
+//   * Once lookups: 24, with offsets 32 (their terms are small), sixteen on rows of up to 4096 columns, which the lookups add up in
+//     short chains as well.  16384 x 22016, q = 3, g = 32, offsets, 8 vectors 1.19 / 3.29 / 0.90 (us 160 / 121 / 127), 16384 x 12288, q = 6,
+//     g = 32, offsets 1.10 / 3.23 / 0.57 (239 / 113 / 124), 7446 x 27264, q = 7, row-wise 1.26 / 1.88 / 1.04 (133 / 93 / 95), 16384 x
+//     15360, q = 8, offsets 1.04 / 2.10 / 0.85 (161 / 122 / 123).  Within one tile the chain is what it is: 1710 x 640, q = 6, g = 64
+//     0.80 / 0.87 / 0.87.
+//   * Matrix-core path, once the kernel that expands keys from a table: 48, which leaves whole K groups to most layers; 24 with
+//     groups of 1024 columns and more, whose sums that kernel scaled once a tile.  FC1 (49152 x 12288, q = 3) at 32 vectors 2.19 / 1.18 / 1.18,
+//     7446 x 27264, q = 7, row-wise at 24 1.50 / 1.87 / 1.03, 8192 x 22016, q = 6, row-wise 1.34 / 1.55 / 1.03.
+// 280 drawn layers (0.3 to 200 million weights, all routes): 0.53 to 0.93 of the error before on average of a route, 1.11 at most (1455 x 12288,
+// q = 4, g = 128, offsets 0.57 / 0.63 / 0.63); time 0.98 to 1.00 of the unbounded kernel's on average of a route, 1.16 at most.
+struct F16Tiles {
+  int chain, group;
+};
+F16Tiles f16_tiles(int additions, int most) {   // additions: of a tile
+  return {most < additions ? 1 : most / additions, 1 << 30};
+}
+F16Tiles gemm_f16_tiles(int q, int64_t n, int64_t gg, bool has_z, int vectors) {
+  const int sb = f16_scale_groups(q, n, gg, vectors), additions = sb * (q + (has_z ? 1 : 0));
+  if (sb == 1 && q <= kFp4MaxPlanes) {
+    F16Tiles t = f16_tiles(additions, 16);
+    t.group = t.chain;
+    return t;
+  }
+  return f16_tiles(additions, sb == 2 && q <= kFp4MaxPlanesSplit ? 12 : (n <= 4096 ? 16 : (has_z ? 32 : 24)));
+}
+F16Tiles matrix_f16_tiles(int q, int64_t n, int64_t gg, bool has_z, int vectors) {
+  return f16_tiles(f16_scale_groups(q, n, gg, vectors) * (q + (has_z ? 1 : 0)), gg >= 1024 ? 24 : 48);
 }
 
 // Grid of a launch: K groups of whole K tiles, row ranges (one workgroup per compute unit), row units per pass.  The
@@ -1927,8 +1951,8 @@ int gemm_f16_tiles(int q, int64_t n, int64_t gg, bool has_z) {
 // planes of its row units, and the end of the pass; between K groups the partial sums and the last workgroup's addition.
 // Constants fitted to 97 layers (1 to 604 million weights, two to eight planes, all groups per step, with and without offsets, at
 // 18 to 32 vectors), every K group count and pass timed: standard deviation 6 %, the choice 0.4 % above the
-// best measured on average, 9 % at worst.
-void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, int max_tiles, F16Params* p) {
+// best measured on average, 9 % at worst.  The end of a chain within a pass: 0.5 us at 8 vectors, 0.6 to 0.8 at 16, 1 to 2 at 32.
+void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Tiles most, F16Params* p) {
   const int row_units = (p->RB + 3) / 4;
   const double scaling = sb == 4 ? 1.76 : 1.0;   // four times the scalings of the sums per step
   const double unit = 0.702 * q * (sb == 2 ? 1.16 : scaling) + (has_z ? 0.163 * scaling : 0.0);
@@ -1937,7 +1961,9 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, int max_t
   for (int t = 1; t <= f16_most_tall(q, sb, has_z); ++t)
     for (int kg = 1; kg <= p->NT && (kg == 1 || kg <= max_groups); ++kg) {
       const int tiles = (p->NT + kg - 1) / kg;
-      if (tiles > max_tiles || (p->NT + tiles - 1) / tiles != kg) continue;
+      if (tiles > most.group || (p->NT + tiles - 1) / tiles != kg) continue;
+      const int chains = (tiles + most.chain - 1) / most.chain;
+      if (chains > 1 && t > 2) continue;   // (LDS has no room for their sums)
       int shift = 3;
       while (tiles == 1 && shift > 0 && p->steps <= 1 << (shift - 1)) --shift;
       const int per_pass = t * (kF16Waves >> shift);
@@ -1945,12 +1971,14 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, int max_t
       rs = rs < 1 ? 1 : (rs > row_units ? row_units : rs);
       const int units = (row_units + rs - 1) / rs, passes = (units + per_pass - 1) / per_pass;
       const double rounds = kg * rs > cus ? (double)kg * rs / cus : 1.0;
-      double cost = 5.06 + rounds * passes * (0.624 * t + tiles * (0.62 + t * unit));
+      const double end = 0.624 * t + (chains - 1) * t * (0.2 + 0.03 * p->vectors);   // of a pass, and of its chains
+      double cost = 5.06 + rounds * passes * (end + tiles * (0.62 + t * unit));
       if (kg > 1) cost += 0.39 + 0.129 * units * ((p->vectors + 3) / 4) * ((kg + 7) / 8) + 4.6e-6 * kg * p->vectors * p->m;
       if (cost < best) {
         best = cost;
         p->KG = kg;
         p->SPG = tiles * kF16Waves;
+        p->chain = (tiles + chains - 1) / chains;
         p->tall = t;
         p->waves_k_shift = shift;
         p->row_splits = rs;
@@ -1961,22 +1989,24 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, int max_t
 }
 
 // Launches the kernel for a whole batch.  `p` holds the pointers; f16_scale_groups is not 0.
-int launch_f16(int cus, int q, bool shared, int64_t m, int64_t n, int64_t gg, int batch, bool y_f32, int max_tiles, F16Params p,
+int launch_f16(int cus, int q, bool shared, int64_t m, int64_t n, int64_t gg, int batch, bool y_f32, F16Tiles most, F16Params p,
                hipStream_t stream) {
   const int sb = f16_scale_groups(q, n, gg, batch);
   fill_fp4_shape(&p, m, n, gg, y_f32);
   p.vec_stride = (int64_t)(p.RB + (p.RB & 1)) * 16;
   p.kg_stride = p.vec_stride * (batch + (batch % 4 == 3 ? 1 : 0));
   p.vectors = batch;
-  plan_f16_grid(cus, q, p.z != nullptr, sb, fp4_max_groups(p.NT, batch), max_tiles, &p);
+  p.set_magic = 0xffffffffu / (uint32_t)(16 * batch) + 1u;
+  plan_f16_grid(cus, q, p.z != nullptr, sb, fp4_max_groups(p.NT, batch), most, &p);
   const GemvKernel kern = shared ? lutgemm_parts::f16_family2(q, sb, p.tall)
                                  : (p.z ? lutgemm_parts::f16_family1(q, sb, p.tall) : lutgemm_parts::f16_family0(q, sb, p.tall));
   if (!kern) return LUTGEMM_EUNSUPPORTED;
   p.blocks_per_group = n == gg ? 1 << 30 : (int)(gg / (128 / sb));
   p.group_step = kF16Waves * sb / p.blocks_per_group;
   p.block_step = kF16Waves * sb % p.blocks_per_group;
+  const int lds_bytes = kF16LdsBytes + (p.chain * kF16Waves < p.SPG ? p.tall * kF16RunningBytes : 0);
   void* args[] = {&p};
-  if (hipLaunchKernel(kern, dim3(p.KG, p.row_splits), dim3(kF16Waves * 64), args, kF16LdsBytes, stream) != hipSuccess) return LUTGEMM_EHIP;
+  if (hipLaunchKernel(kern, dim3(p.KG, p.row_splits), dim3(kF16Waves * 64), args, lds_bytes, stream) != hipSuccess) return LUTGEMM_EHIP;
   return LUTGEMM_OK;
 }
 
@@ -2214,7 +2244,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
       ph.y = y;
       ph.partial = partials;
       ph.counters = counters;
-      return launch_f16(cus, q, shared, m, n, gg, batch, p.y_f32 != 0, gemm_f16_tiles(q, n, gg, p.z != nullptr), ph, stream);
+      return launch_f16(cus, q, shared, m, n, gg, batch, p.y_f32 != 0, gemm_f16_tiles(q, n, gg, p.z != nullptr, batch), ph, stream);
     }
     const int take = pass.kernel, live = pass.vectors;
     if (take == 4) plan_quad();
@@ -2294,7 +2324,7 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
     ph.y = y;
     ph.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
     ph.counters = static_cast<uint32_t*>(workspace);
-    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, matrix_f16_tiles(q, z != nullptr, batch), ph,
+    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, matrix_f16_tiles(q, n, gg, z != nullptr, batch), ph,
                       static_cast<hipStream_t>(hip_stream));
   }
   const int waves = planes_waves(q);
@@ -2383,10 +2413,12 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
       fill_fp4_shape(&ph, m, n, gg, false);
       ph.vectors = batch;
       plan_f16_grid(cus, q, has_offsets != 0, f16_scale_groups(q, n, gg, batch), fp4_max_groups(p.NT, batch),
-                    fp16 ? matrix_f16_tiles(q, has_offsets != 0, batch) : gemm_f16_tiles(q, n, gg, has_offsets != 0), &ph);
+                    fp16 ? matrix_f16_tiles(q, n, gg, has_offsets != 0, batch) : gemm_f16_tiles(q, n, gg, has_offsets != 0, batch), &ph);
       o[2] = ph.KG;
       o[3] = ph.SPG / kF16Waves;
       o[4] = ph.row_splits;
+      o[5] = ph.chain;
+      o[6] = ph.tall * (kF16Waves >> ph.waves_k_shift);
     } else {
       GemvParams pk = p;
       if (fp16)

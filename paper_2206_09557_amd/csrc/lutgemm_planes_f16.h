@@ -17,7 +17,9 @@
 //
 // Work split.  A workgroup owns a row range and a K group.  It walks a row range in passes of T row units per wavefront:
 // a pass goes through the K tiles of the group, each wavefront with one of a tile's eight K steps, and keeps its sums in
-// registers; then the wavefronts' sums are added through LDS, in their order and in 64 bits.  Sums between
+// registers, a chain of fp32 additions; at its end the wavefronts' sums are added through LDS, in their order and in 64 bits.
+// Where a K group would be too long a chain for the error that its calls had before (the rule: F16Tiles), there are several,
+// and their sums stay in LDS, in 64 bits.  Sums between
 // K groups, where there are several, are the only ones that go through memory.  The activations of a tile come
 // by way of the registers into one half of LDS while the other half is in use: one barrier per tile.  A plane's keys and scales
 // give way to those of the next unit as soon as they are used up.  A pass of several row units shares the
@@ -30,8 +32,8 @@
 // weights and activations of zeros the same launch takes 84 us.  The products and the vector instructions that feed them are
 // interleaved by hand, one product to a group of eight (left to the compiler: 116).  One row unit per pass 119,
 // K groups of half the columns 115.
-// Error against 64-bit sums (2-norm; N(0, 1) activations, one in 1024 columns ten to thirty times larger): 0.4 to 1.2e-7, the
-// kernel before 0.7 to 1.4e-7, lookups 0.4 to 1.2e-7.
+// Error against 64-bit sums (2-norm; N(0, 1) activations, one in 1024 columns ten to thirty times larger): 0.4 to 1.3e-7 over 280 drawn
+// layers of all routes.
 #pragma once
 
 typedef _Float16 f16x8v __attribute__((ext_vector_type(8)));
@@ -44,6 +46,8 @@ struct F16Params : Fp4Params {   // SPG: K steps of a K group, whole K tiles
   int tall;                      // row units of a wavefront's pass (the kernel's T)
   int waves_k_shift;             // log2 of the wavefronts among which the K steps of a row unit are dealt out: all eight, or,
                                  // where a K group has fewer steps, that many
+  uint32_t set_magic;            // number / (16 * vectors) of up to 8 * 16 * vectors numbers: the upper half of their product with it
+  int chain;                     // K tiles that a wavefront adds up one after the other in fp32 (several chains: T < 3)
 };
 
 constexpr int kF16Waves = 8;
@@ -52,6 +56,7 @@ constexpr int kF16StageBytes = kF16Waves * kF16StepBytes;      // a K tile, one 
 constexpr int kF16PartBytes = 32 * kFp4UnitRows * 4;           // a wavefront's sums of a row unit
 static_assert(kF16Waves * kF16PartBytes <= kF16StageBytes, "the sums take the place of a tile's activations");
 constexpr int kF16LdsBytes = 2 * kF16StageBytes;
+constexpr int kF16RunningBytes = 32 * kFp4UnitRows * 8;        // ... and behind these, of a row unit, the 64-bit sums of its chains so far
 
 // Keys, scales and offsets of a unit (row unit, K step) as a lane has them.
 template <int Q, int ZM, int SB>
@@ -438,16 +443,13 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
     ++turn;
   };
 
-#pragma unroll 1
-  for (int ru = range0; ru < range0 + range_units; ru += pass_units) {
-#pragma unroll 1
-    for (int stage = 0; stage < stages; ++stage) stage_body(stage);
+  // ---- the end of a chain: the wavefronts' sums of a row unit, in their order, where the last stage's activations
+  // were.  Sums of several chains meet in 64 bits, in a place of LDS that only the thread that adds them up knows.
+  auto finish_chain = [&](int ru, bool first, bool last) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[T - 1][1][q] = fmaf(-pend_al, pend[q], acc[T - 1][1][q]);
     pend_al = 0.0f;
     pend = f32x16{};
-
-    // ---- the wavefronts' sums of a row unit, in their order, where the last stage's activations were
     float* part = reinterpret_cast<float*>(lds + ((turn - 1) & 1) * kF16StageBytes);
     const int lane_again = f16_lane_number();   // (nothing of this is to stay in registers over the stages)
     const int tid = wave * 64 + lane_again;
@@ -458,21 +460,37 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
 #pragma unroll
       for (int tile = 0; tile < 2; ++tile) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) dst[(8 * (q >> 2) + (q & 3)) * kFp4UnitRows + 2 * tile] = acc[t][tile][q];
+        for (int q = 0; q < 16; ++q)
+          if (T > 2 || 8 * (q >> 2) < p.vectors) dst[(8 * (q >> 2) + (q & 3)) * kFp4UnitRows + 2 * tile] = acc[t][tile][q];
         acc[t][tile] = f32x16{};
       }
       __syncthreads();
       for (int i = tid; i < sets * p.vectors * 16; i += kF16Waves * 64) {   // (row unit, vector, four rows)
-        const int set = i / (p.vectors * 16), vec = (i >> 4) - set * p.vectors, unit = ru + set * T + t;
+        const int set = (int)__umulhi((uint32_t)i, p.set_magic), vec = (i >> 4) - set * p.vectors, unit = ru + set * T + t;
         const int row = unit * kFp4UnitRows + 4 * (i & 15);
         if (unit >= range0 + range_units) continue;
         const f32x4* src = reinterpret_cast<const f32x4*>(part + (set << p.waves_k_shift) * (kF16PartBytes / 4) + vec * kFp4UnitRows) + (i & 15);
+        f32x4 q[kF16Waves];
+#pragma unroll
+        for (int k = 0; k < kF16Waves; ++k) q[k] = src[min(k, waves_k - 1) * (kF16PartBytes / 16)];
         double sum[4] = {0.0, 0.0, 0.0, 0.0};   // few additions, and the last ones: 64 bits cost nothing here
 #pragma unroll
-        for (int k = 0; k < kF16Waves; ++k) {
-          const f32x4 q = src[min(k, waves_k - 1) * (kF16PartBytes / 16)];
+        for (int k = 0; k < kF16Waves; ++k)
+          if (k < waves_k) {
 #pragma unroll
-          for (int b = 0; b < 4; ++b) sum[b] += k < waves_k ? q[b] : 0.0f;
+            for (int b = 0; b < 4; ++b) sum[b] += q[k][b];
+          }
+        if (T < 3 && !(first && last)) {   // (several K tiles, so one set: i < 512)
+          double* running = reinterpret_cast<double*>(lds + kF16LdsBytes + t * kF16RunningBytes) + 4 * i;
+          if (!first) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) sum[b] += running[b];
+          }
+          if (!last) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) running[b] = sum[b];
+            continue;
+          }
         }
         const float s[4] = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
         if (p.KG == 1) {
@@ -483,6 +501,17 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
           fp4_store_pair(q + 2, s[2], s[3]);
         }
       }
+    }
+  };
+
+#pragma unroll 1
+  for (int ru = range0; ru < range0 + range_units; ru += pass_units) {
+#pragma unroll 1
+    for (int stage = 0; stage < stages;) {
+      const int first = stage, end = min(stage + p.chain, stages);
+#pragma unroll 1
+      for (; stage < end; ++stage) stage_body(stage);
+      finish_chain(ru, first == 0, end == stages);
     }
   }
   if (p.KG == 1) return;

@@ -211,7 +211,7 @@ def lutgemm_plan_grid(m, n, q, g, vectors=1, compute_units=0):
 
 def lutgemm_plan_gemm(m, n, q, g, has_offsets, batch, flags=0, compute_units=0):
     """One tuple per launch of lutgemm_gemm: (kernel, vectors, K groups, tiles or steps per K group, row ranges, K steps
-    per item, row units per stretch)."""
+    per item or K tiles per chain, row units at a time)."""
     out = (ctypes.c_int * (7 * 32))()
     done = lib().lutgemm_plan_gemm(m, n, q, g, int(has_offsets), batch, flags, compute_units, ctypes.addressof(out), 32)
     if done < 0:

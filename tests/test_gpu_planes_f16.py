@@ -134,3 +134,40 @@ def test_captured_and_replayed(q, g, batch):
         graph.replay()
         torch.cuda.synchronize()
         np.testing.assert_array_equal(d_y.cpu().numpy(), run(p, x, f32_out=True))
+
+
+def _synthetic(m, n, q, g, with_z, seed):
+    """A layer packed without a quantiser: random keys, scales halving from plane to plane, small offsets."""
+    rng = np.random.default_rng(seed)
+    gg = n if g == 0 else g
+    bits = rng.integers(0, 256, L.lutgemm_bits_bytes(m, n, q), dtype=np.uint8)
+    spread = 1.0 + 0.1 * rng.standard_normal((m, n // gg), dtype=np.float32).clip(-4, 4)
+    alpha = np.stack([(0.016 * 0.5 ** k * spread).astype(np.float16) for k in range(q)])
+    z = (0.004 * rng.standard_normal((m, n // gg), dtype=np.float32)).astype(np.float16) if with_z else None
+    alpha, z = L.lutgemm_pack_scales(alpha, z, n, gg)
+    return Packed(bits, alpha, z, m, n, q, g)
+
+
+# Long rows on few K groups: with all tiles of one in a single fp32 chain the error was up to 3.3e-7.  `additions`: the most
+# that a wavefront makes one after the other there now.  Each rounds by 2.4e-8 of its sum (2^-24 of a number
+# between two powers of two, spread evenly), and with scales that halve from plane to plane the sum has about its size from
+# the first terms on: sqrt(additions) * 2.4e-8 for a chain, and as much for the sum of such chains.  What is left of short ones
+# (the matrix instructions' own sums, the result) measured 4.5e-8.
+@pytest.mark.parametrize("m,n,q,g,with_z,batch,auto,additions", [
+    (16384, 22016, 3, 32, True, 8, False, 32), (16384, 8256, 6, 96, False, 9, False, 24), (16384, 12288, 4, 64, False, 16, False, 12),
+    (12288, 12288, 2, 64, True, 32, False, 12), (16384, 15360, 8, 128, True, 8, False, 32), (7446, 27264, 7, 0, False, 8, False, 24),
+    (7446, 27264, 7, 0, False, 24, True, 24), (8192, 22016, 4, 64, True, 32, True, 48), (7446, 27264, 7, 0, False, 8, True, 24),
+])
+def test_error_of_long_rows(m, n, q, g, with_z, batch, auto, additions):
+    plan = L.lutgemm_plan_gemm(m, n, q, g, with_z, batch, L.LUTGEMM_PATH_AUTO if auto else 0)
+    print(f"case f16 error m={m} n={n} q={q} g={g} z={with_z} batch={batch} auto={auto}: {plan}", flush=True)
+    assert [k[:2] for k in plan] == [(L.LUTGEMM_KERNEL_FP16, batch)]
+    p = _synthetic(m, n, q, g, with_z, seed=19000 + n)
+    X = synth.activations_fp16(n, seed=19001 + n, batch=batch)
+    rows = np.sort(np.random.default_rng(19002).choice(m, 300, replace=False))
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g, rows=rows)
+    y = run(p, X, f32_out=True, auto=auto)[:, rows]
+    error = np.linalg.norm(y - y_ref) / np.linalg.norm(y_ref)
+    limit = np.sqrt(additions * 2.4e-8 ** 2 + 4.5e-8 ** 2)
+    print(f"error {error:.2e} limit {limit:.2e}", flush=True)
+    assert error <= limit

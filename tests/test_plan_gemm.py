@@ -96,3 +96,34 @@ def test_batches_beyond_the_offsets_of_the_fp16_kernel(q, g):
     assert [p[:2] for p in L.lutgemm_plan_gemm(16, n, q, g, False, 15, 0, 256)] == [(FP16, 15)]
     plan = L.lutgemm_plan_gemm(16, n, q, g, False, 17, 0, 256)
     assert sum(p[1] for p in plan) == 17 and FP16 not in [p[0] for p in plan]
+
+
+def test_chains_of_the_fp16_kernel_are_bounded():
+    # Additions of a wavefront one after the other in fp32, whose number the error grows with: one per plane and offset and
+    # scale group of a K step, over the K tiles of a chain.  Within a tile they are what they are.
+    rng = random.Random(6)
+    seen = {True: 0, False: 0}
+    for _ in range(6000):
+        q, g, z = rng.randint(1, 8), rng.choice([0, 32, 32, 64, 64, 96, 128, 192, 256, 1024, 2048]), rng.random() < 0.5
+        m = int(2 ** rng.uniform(5, 16))
+        unit = g or 64
+        n = unit * max(1, int(2 ** rng.uniform(6, 16) / unit))
+        gg = g or n
+        batch, auto = rng.randint(5, 32), rng.random() < 0.4
+        for kernel, _, _, tiles, _, chain, rows in L.lutgemm_plan_gemm(m, n, q, g, z, batch, L.LUTGEMM_PATH_AUTO if auto else 0, 256):
+            matrix = auto and gg % 64 == 0 and (batch >= 6 or (batch == 5 and m * n < 1 << 28))
+            if kernel != FP16 or (matrix and batch <= 16 and chain == 0):      # (expanded from a table)
+                continue
+            per_step = 1 if gg == n or gg % 128 == 0 else 2 if gg % 64 == 0 else 4
+            most = 32 if z and n > 4096 else 24 if n > 4096 else 16
+            if matrix:
+                most = 24 if gg >= 1024 else 48
+            elif per_step == 1 and q <= 6:
+                most = 16
+            elif per_step == 2 and q <= 4:
+                most = 12
+            additions = per_step * (q + z)
+            assert 1 <= chain <= tiles and (chain == 1 or chain * additions <= most), (m, n, q, g, z, batch, auto)
+            assert rows >= 1 and (chain == tiles or rows <= 2)                 # (whose sums LDS has room for)
+            seen[chain < tiles] += 1
+    assert min(seen.values()) > 200
