@@ -2367,10 +2367,8 @@ int lutgemm_plan_grid(int64_t m, int64_t n, int q, int g, int vectors, int compu
   if (vectors != 1 && vectors != 2 && vectors != 4) return LUTGEMM_EINVAL;
   const int cus = compute_units > 0 ? compute_units : compute_units_of_device();
   if (cus <= 0) return LUTGEMM_EHIP;
-  GemvParams p;
-  p.RB = (int)((m + 15) / 16);
-  p.nchunks = (int)(n / 8);
-  p.NT = (p.nchunks + 127) / 128;
+  GemvParams p = {};
+  fill_shape(&p, m, n, gg);
   plan_lookup_grid(cus, vectors, q, gg, &p);
   out[0] = p.KG;
   out[1] = p.TPG;

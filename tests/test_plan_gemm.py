@@ -127,3 +127,13 @@ def test_chains_of_the_fp16_kernel_are_bounded():
             assert rows >= 1 and (chain == tiles or rows <= 2)                 # (whose sums LDS has room for)
             seen[chain < tiles] += 1
     assert min(seen.values()) > 200
+
+
+@pytest.mark.parametrize("m,n,q,g", [(3001, 5160, 5, 24), (8192, 8200, 3, 8), (3001, 5160, 5, 40), (4096, 528, 2, 24)])
+def test_grid_of_one_vector_is_the_one_launched(m, n, q, g):
+    # Groups with a scale set per chunk: the choice looks at the row length.
+    launched, = L.lutgemm_plan_gemm(m, n, q, g, True, 1, 0, 256)
+    for other in (8, 512, 520, 1 << 20):      # (whatever an earlier call has left on the stack)
+        L.lutgemm_plan_group([(16, other)] * 8, q, 8, 256)
+        L.lutgemm_plan_gemm(16, other, 1, 0, False, 1, 0, 256)
+        assert L.lutgemm_plan_grid(m, n, q, g, 1, 256) == launched[2:5]
