@@ -331,6 +331,11 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
     const int x_stage = stage + 1 < stages ? stage + 1 : 0;
     const int x_to = place_x(x_stage, turn + 1);
     const int local = stage * kF16Waves + wk;
+    // A scale or offset counts where its segment of the K step has columns: behind the last one sums are zero, which an
+    // infinity would turn into a NaN.
+    int scale_bits[SB];
+#pragma unroll
+    for (int s = 0; s < SB; ++s) scale_bits[s] = 16 * (step0 + local) + s * (16 / SB) < p.nchunks ? 16 : 0;
     f16x8v a[2][4];
     {
       const char* xs = lds + (turn & 1) * kF16StageBytes + wk * kF16StepBytes + L.s * 512;
@@ -348,12 +353,12 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
     for (int t = 0; t < T; ++t) {
       const F16Source<Q, ZM, SB> src = t + 1 < T ? source(here, t + 1) : source(ahead, 0);
       __builtin_amdgcn_sched_barrier(0);
-      uint32_t al[2][SB];   // scale of the lane's row in either tile (lower half)
+      uint32_t al[2][SB];   // scale of the lane's row in either tile (its 16 bits)
       auto take_scales = [&](int i) {
 #pragma unroll
         for (int s = 0; s < SB; ++s) {
-          al[0][s] = u.al[s][i].x >> al_shift;
-          al[1][s] = u.al[s][i].y >> al_shift;
+          al[0][s] = __builtin_amdgcn_ubfe(u.al[s][i].x, al_shift, scale_bits[s]);
+          al[1][s] = __builtin_amdgcn_ubfe(u.al[s][i].y, al_shift, scale_bits[s]);
           asm volatile("" : "+v"(al[0][s]), "+v"(al[1][s]));   // (now: their place is asked for)
         }
       };
@@ -361,8 +366,8 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
         uint32_t zz[2][SB];
 #pragma unroll
         for (int s = 0; s < SB; ++s) {
-          zz[0][s] = u.zz[s].x >> al_shift;
-          zz[1][s] = u.zz[s].y >> al_shift;
+          zz[0][s] = __builtin_amdgcn_ubfe(u.zz[s].x, al_shift, scale_bits[s]);
+          zz[1][s] = __builtin_amdgcn_ubfe(u.zz[s].y, al_shift, scale_bits[s]);
           asm volatile("" : "+v"(zz[0][s]), "+v"(zz[1][s]));
         }
         if (ZM == 2) take_scales(0);

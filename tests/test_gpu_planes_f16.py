@@ -171,3 +171,23 @@ def test_error_of_long_rows(m, n, q, g, with_z, batch, auto, additions):
     limit = np.sqrt(additions * 2.4e-8 ** 2 + 4.5e-8 ** 2)
     print(f"error {error:.2e} limit {limit:.2e}", flush=True)
     assert error <= limit
+
+
+@pytest.mark.parametrize("m,n,q,g,with_z,batch,auto", [
+    (70, 1152, 3, 128, False, 24, False), (70, 1152, 3, 128, True, 24, True), (70, 1088, 3, 64, False, 24, True), (70, 1096, 7, 0, False, 8, False),
+    (70, 1088, 5, 64, False, 7, False), (70, 640, 3, 32, True, 9, False), (70, 1056, 2, 32, True, 9, False), (70, 200, 8, 40 * 5, True, 6, False),
+])
+def test_infinite_scale_of_the_last_group(m, n, q, g, with_z, batch, auto):
+    # The last K step of a row has no columns for all its segments, and a K tile fewer steps than wavefronts: what has none
+    # is zero whatever the scale.  Signs and activations are all positive.
+    gg = g or n
+    X = np.tile(np.float16([1.0 + 2.0 ** -10, 2.0 ** -17, 2.0 ** -24, 1.0]), (batch, n // 4))
+    flags = L.LUTGEMM_PATH_AUTO if auto else 0
+    assert [k[0] for k in L.lutgemm_plan_gemm(m, n, q, g, with_z, batch, flags)] == [L.LUTGEMM_KERNEL_FP16]
+    for which in range(2 if with_z else 1):
+        alpha = np.full((q, m, n // gg), 0.5, dtype=np.float16)
+        z = np.full((m, n // gg), 0.25, dtype=np.float16) if with_z else None
+        (z if which else alpha[q - 1])[[3, 67], -1] = np.inf
+        pa, pz = L.lutgemm_pack_scales(alpha, z, n, gg)
+        y = run(Packed(L.lutgemm_pack_planes(np.ones((q, m, n), dtype=np.int8)), pa, pz, m, n, q, g), X, f32_out=True, auto=auto)
+        assert np.isposinf(y[:, [3, 67]]).all() and np.isfinite(np.delete(y, [3, 67], axis=1)).all()
