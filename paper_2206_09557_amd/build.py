@@ -15,7 +15,7 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "liblutgemm.so")
 HOST_SOURCE = os.path.join(PKG, "csrc", "lutgemm_host.cpp")
 DEVICE_SOURCE = os.path.join(PKG, "csrc", "lutgemm_device.hip")
-BINDING = os.path.join(PKG, "_binding.so")
+BINDING = os.path.join(PKG, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))   # of this Python alone
 BINDING_SOURCE = os.path.join(PKG, "csrc", "lutgemm_binding.cpp")
 PARTS = 20   # kernel families of lutgemm_device.hip (LUT_PART = 0 .. 19)
 
@@ -86,6 +86,9 @@ def build_library(verbose: bool = True, jobs: int | None = None, report: bool = 
 
 def build_binding(verbose: bool = True) -> str:
     """The CPython marshalling of the device calls (no HIP in it)."""
+    for old in (BINDING, os.path.join(PKG, "_binding.so")):   # (without a tag any Python would take it)
+        if os.path.exists(old):
+            os.remove(old)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
            "-o", BINDING, BINDING_SOURCE]
     if verbose:

@@ -2,6 +2,7 @@
 what it does not take itself ends as the ctypes functions end it."""
 import ctypes
 import os
+import sysconfig
 
 import numpy as np
 import pytest
@@ -107,3 +108,7 @@ def test_the_rest_ends_as_with_ctypes(caught):
     assert outcome(by_ctypes, *{**good, "q": np.int64(3)}.values())[2] == L.LUTGEMM_EINVAL
     assert outcome(by_ctypes, *{**good, "q": 3.0}.values())[0] is ctypes.ArgumentError
     assert outcome(by_ctypes, *{**good, "x": "text"}.values())[:2] == (TypeError, "cannot take the address of <class 'str'>")
+
+
+def test_is_built_for_this_python_alone():
+    assert M._binding.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
