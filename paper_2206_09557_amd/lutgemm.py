@@ -1,11 +1,14 @@
 """Binding of liblutgemm.so (ctypes; the device calls compiled): same names as include/lutgemm.h, argument marshalling
 only.  Host entry points take and return numpy arrays; device entry points take anything
 with a `.data_ptr()` (torch tensors on the GPU) or a raw integer address.  There is no
-fallback: if the built library is absent, loading raises."""
+fallback: if the built library is absent, loading raises.  (The compiled marshalling is not the library: without it
+ctypes makes the same calls.)"""
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 
 import numpy as np
 
@@ -291,14 +294,16 @@ def lutgemm_gemm_dequant_mfma(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags
 
 
 # The calls of a serving loop are bound by this marshalling where the layer is small: csrc/lutgemm_binding.cpp does it
-# for the usual arguments and hands everything else to the functions above.  Before it is built (when this package
-# is imported to build it) they are the entry points themselves: the same calls, 1.1 us slower each.
+# for the usual arguments and hands everything else to the functions above.  Where it is not built (when this package
+# is imported to build it, or for want of Python's headers) they are the entry points themselves: the same calls, 1.1 us
+# slower each.
 _DEVICE_CALLS = ("lutgemm_gemv", "lutgemm_gemm", "lutgemm_gemm_mfma", "lutgemm_gemm_dequant_mfma", "lutgemm_gemv_static",
                  "lutgemm_gemv_group")
 try:
-    from . import _binding
-except ImportError:
-    _binding = None
+    _binding = importlib.import_module(__package__ + "._binding")
+except ImportError as e:
+    if not isinstance(e, ModuleNotFoundError):   # built, but not for this process
+        warnings.warn(f"the compiled marshalling of the device calls does not load, ctypes does it: {e}")
 else:
     _binding.set_up({name: globals()[name] for name in _DEVICE_CALLS}, _check)
     globals().update({name: getattr(_binding, name) for name in _DEVICE_CALLS})

@@ -2,6 +2,9 @@
 what it does not take itself ends as the ctypes functions end it."""
 import ctypes
 import os
+import shutil
+import subprocess
+import sys
 import sysconfig
 
 import numpy as np
@@ -112,3 +115,21 @@ def test_the_rest_ends_as_with_ctypes(caught):
 
 def test_is_built_for_this_python_alone():
     assert M._binding.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def _import_of_a_copy(tmp_path, code):
+    """Output of `code` in a package `lutgemm_copy` of the Python files, in a process of its own."""
+    pkg = tmp_path / "lutgemm_copy"
+    pkg.mkdir(exist_ok=True)
+    for name in ("__init__.py", "lutgemm.py", "build.py"):
+        shutil.copy(os.path.join(os.path.dirname(M.__file__), name), pkg / name)
+    return subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, check=True)
+
+
+def test_one_that_does_not_load_is_reported(tmp_path):
+    code = "from lutgemm_copy import lutgemm as M; print(M._binding, type(M.lutgemm_gemv).__name__)"
+    absent = _import_of_a_copy(tmp_path, code)
+    assert absent.stdout.split() == ["None", "function"] and "marshalling" not in absent.stderr
+    (tmp_path / "lutgemm_copy" / ("_binding" + sysconfig.get_config_var("EXT_SUFFIX"))).write_bytes(b"no shared object")
+    broken = _import_of_a_copy(tmp_path, code)
+    assert broken.stdout.split() == ["None", "function"] and "marshalling of the device calls does not load" in broken.stderr
