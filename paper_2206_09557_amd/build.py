@@ -4,6 +4,7 @@ The device source is compiled once per kernel family (-DLUT_PART=k) in parallel,
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -84,13 +85,18 @@ def build_library(verbose: bool = True, jobs: int | None = None, report: bool = 
     return LIB
 
 
-def build_binding(verbose: bool = True) -> str:
-    """The CPython marshalling of the device calls (no HIP in it)."""
+def build_binding(verbose: bool = True) -> str | None:
+    """The CPython marshalling of the device calls (no HIP in it).  Where this Python has no headers there is none, and the
+    ctypes functions, which it stands in front of, are the entry points."""
     for old in (BINDING, os.path.join(PKG, "_binding.so")):   # (without a tag any Python would take it)
         if os.path.exists(old):
             os.remove(old)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
-           "-o", BINDING, BINDING_SOURCE]
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"no Python.h in {include}: device calls go through ctypes", flush=True)
+        return None
+    compiler = os.environ.get("CXX") or shutil.which("g++") or os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    cmd = [compiler, "-x", "c++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", include, "-o", BINDING, BINDING_SOURCE]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

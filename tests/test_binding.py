@@ -133,3 +133,14 @@ def test_one_that_does_not_load_is_reported(tmp_path):
     (tmp_path / "lutgemm_copy" / ("_binding" + sysconfig.get_config_var("EXT_SUFFIX"))).write_bytes(b"no shared object")
     broken = _import_of_a_copy(tmp_path, code)
     assert broken.stdout.split() == ["None", "function"] and "marshalling of the device calls does not load" in broken.stderr
+
+
+def test_a_python_without_headers_builds_none(tmp_path, monkeypatch, capsys):
+    from paper_2206_09557_amd import build
+    built = tmp_path / "_binding.so"
+    built.write_bytes(b"of before")
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setattr(build, "BINDING", str(built))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_binding() is None
+    assert "ctypes" in capsys.readouterr().out and not built.exists()
