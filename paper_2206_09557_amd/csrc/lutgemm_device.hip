@@ -1719,7 +1719,7 @@ int f16_scale_groups(int q, int64_t n, int64_t gg, int vectors);
 // lutgemm_plan_gemm name these kernels for such calls, though the other is faster there too (4096 x 4096, q = 3, g = 32
 // 20 / 11 at five vectors; q = 5, g = 64 22 / 12).
 bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, int left) {
-  const int sb = f16_scale_groups(q, n, gg, left);
+  const int sb = left < 5 ? 0 : f16_scale_groups(q, n, gg, left);
   if (sb == 0) return false;
   const int64_t w = m * n;
   if (sb == 1 && q <= kFp4MaxPlanes)
@@ -1959,9 +1959,9 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Tiles 
   cus = cus > 256 ? 256 : cus;
   double best = 1e30;
   for (int t = 1; t <= f16_most_tall(q, sb, has_z); ++t)
-    for (int kg = 1; kg <= p->NT && (kg == 1 || kg <= max_groups); ++kg) {
-      const int tiles = (p->NT + kg - 1) / kg;
-      if (tiles > most.group || (p->NT + tiles - 1) / tiles != kg) continue;
+    for (int kg = 1, tiles = p->NT, next; kg == 1 || kg <= max_groups; kg = next, tiles = (p->NT + kg - 1) / kg) {
+      next = tiles > 1 ? (p->NT + tiles - 2) / (tiles - 1) : max_groups + 1;   // fewest groups of fewer tiles
+      if (tiles > most.group) continue;
       const int chains = (tiles + most.chain - 1) / most.chain;
       if (chains > 1 && t > 2) continue;   // (LDS has no room for their sums)
       int shift = 3;
@@ -1986,6 +1986,18 @@ void plan_f16_grid(int cus, int q, bool has_z, int sb, int max_groups, F16Tiles 
     }
   p->range_base = row_units / p->row_splits;
   p->range_rem = row_units % p->row_splits;
+}
+
+F16Params f16_buffers(const void* x, const void* bits, const void* alpha, const void* z, void* y, void* workspace) {
+  F16Params p = {};
+  p.x = static_cast<const __half*>(x);
+  p.bits = static_cast<const uint8_t*>(bits);
+  p.alpha = static_cast<const __half*>(alpha);
+  p.z = static_cast<const __half*>(z);
+  p.y = y;
+  p.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
+  p.counters = static_cast<uint32_t*>(workspace);
+  return p;
 }
 
 // Launches the kernel for a whole batch.  `p` holds the pointers; f16_scale_groups is not 0.
@@ -2181,6 +2193,10 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   if (cus <= 0) return LUTGEMM_EHIP;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
+  if (lookups_yield_to_f16(q, m, n, gg, batch))   // (the whole batch: see gemm_pass)
+    return launch_f16(cus, q, shared, m, n, gg, batch, (flags & LUTGEMM_Y_F32) != 0, gemm_f16_tiles(q, n, gg, z != nullptr, batch),
+                      f16_buffers(x, bits, alpha, z, y, workspace), stream);
+
   GemvParams p;
   p.bits = static_cast<const uint8_t*>(bits);
   p.alpha = static_cast<const __half*>(alpha);
@@ -2234,17 +2250,6 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
       if (rc != LUTGEMM_OK) return rc;
       b += pass.vectors;
       continue;
-    }
-    if (pass.kernel == LUTGEMM_KERNEL_FP16) {   // all of them
-      F16Params ph = {};
-      ph.x = static_cast<const __half*>(x);
-      ph.bits = p.bits;
-      ph.alpha = p.alpha;
-      ph.z = p.z;
-      ph.y = y;
-      ph.partial = partials;
-      ph.counters = counters;
-      return launch_f16(cus, q, shared, m, n, gg, batch, p.y_f32 != 0, gemm_f16_tiles(q, n, gg, p.z != nullptr, batch), ph, stream);
     }
     const int take = pass.kernel, live = pass.vectors;
     if (take == 4) plan_quad();
@@ -2315,18 +2320,9 @@ static int gemm_matrix_cores(bool dequant, const void* x, const void* bits, cons
   }
   if (!dequant && batch > 16 && f16_scale_groups(q, n, gg, batch) == 0)   // too long for its offsets: lookups
     return lutgemm_gemm(x, bits, alpha, z, y, q, g, mu, m, n, batch, flags, workspace, workspace_bytes, hip_stream);
-  if (!dequant && matrix_cores_take_f16(q, m, n, gg, z != nullptr, batch)) {
-    F16Params ph = {};
-    ph.x = p.x;
-    ph.bits = p.bits;
-    ph.alpha = p.alpha;
-    ph.z = p.z;
-    ph.y = y;
-    ph.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
-    ph.counters = static_cast<uint32_t*>(workspace);
-    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, matrix_f16_tiles(q, n, gg, z != nullptr, batch), ph,
-                      static_cast<hipStream_t>(hip_stream));
-  }
+  if (!dequant && matrix_cores_take_f16(q, m, n, gg, z != nullptr, batch))
+    return launch_f16(cus, q, false, m, n, gg, batch, p.y_f32 != 0, matrix_f16_tiles(q, n, gg, z != nullptr, batch),
+                      f16_buffers(x, bits, alpha, z, y, workspace), static_cast<hipStream_t>(hip_stream));
   const int waves = planes_waves(q);
   plan_planes(cus, q, batch, &p);
   if (p.row_splits > 256 && p.KG > 1) return LUTGEMM_EUNSUPPORTED;   // 256 arrival counters per call

@@ -2,6 +2,7 @@
 lutgemm_plan_group): the kernel a call gets, and that every planned grid covers the layer within the workspace and
 the LDS it was sized for."""
 import random
+import time
 
 import pytest
 
@@ -137,3 +138,17 @@ def test_grid_of_one_vector_is_the_one_launched(m, n, q, g):
         L.lutgemm_plan_group([(16, other)] * 8, q, 8, 256)
         L.lutgemm_plan_gemm(16, other, 1, 0, False, 1, 0, 256)
         assert L.lutgemm_plan_grid(m, n, q, g, 1, 256) == launched[2:5]
+
+
+def test_long_rows_are_planned_in_no_time():
+    # The grid of the fp16 kernel is chosen anew for every call: with every K group count looked at, 2^15 K tiles took 120 times
+    # as long as eight, 150 us, more than the launch.
+    def best(n):
+        times = []
+        for _ in range(30):
+            start = time.perf_counter()
+            plan = L.lutgemm_plan_gemm(16, n, 3, 32, False, 8, 0, 256)
+            times.append(time.perf_counter() - start)
+            assert plan[0][0] == FP16
+        return min(times)
+    assert best(1 << 25) < 8 * best(1 << 13)
