@@ -1,7 +1,8 @@
 """GPU parity of the kernel that multiplies the binary planes as fp16 +-1 on the matrix cores (batches beyond what lookups
 and 4-bit floats are the faster way for): at the edges of its row units (64 rows), K steps (128 columns) and tiles of one and two
-sub-slabs, K groups of fewer steps than wavefronts, passes of one to three row units that do not divide a row range,
-every plane count, group class and scale layout, activations that are not finite, and in a captured graph."""
+sub-slabs, K groups of fewer steps than wavefronts, row ranges of several passes of one to three row units, several chains of
+fp32 additions, every plane count, group class and scale layout, numbers that are not finite, the error of long rows, and in
+a captured graph."""
 import numpy as np
 import pytest
 
@@ -28,7 +29,7 @@ CASES = [
     (300, 2080, 6, 160, "rtn", 16, False),       # groups that straddle steps, the last step a quarter of one
     (200, 1344, 5, 64, "greedy_z", 7, False),    # two groups per step, the last step holds one of them
     (333, 4800, 2, 192, "rtn", 19, True),        # ... that straddle steps
-    (5000, 640, 2, 64, "greedy", 20, True),      # several row units per workgroup, passes of two and three
+    (5000, 640, 2, 64, "greedy", 20, True),      # one row unit per workgroup, then two in one pass
     (20000, 2048, 3, 128, "greedy", 18, True),
     (13000, 1024, 4, 128, "greedy_z", 24, True),
     (48, 65536, 3, 32, "greedy", 12, False),     # many K groups on one row unit
@@ -136,13 +137,14 @@ def test_captured_and_replayed(q, g, batch):
         np.testing.assert_array_equal(d_y.cpu().numpy(), run(p, x, f32_out=True))
 
 
-def _synthetic(m, n, q, g, with_z, seed):
-    """A layer packed without a quantiser: random keys, scales halving from plane to plane, small offsets."""
+def _synthetic(m, n, q, g, with_z, seed, factor=0.5):
+    """A layer packed without a quantiser: random keys, scales halving from plane to plane (or times `factor`), small
+    offsets."""
     rng = np.random.default_rng(seed)
     gg = n if g == 0 else g
     bits = rng.integers(0, 256, L.lutgemm_bits_bytes(m, n, q), dtype=np.uint8)
     spread = 1.0 + 0.1 * rng.standard_normal((m, n // gg), dtype=np.float32).clip(-4, 4)
-    alpha = np.stack([(0.016 * 0.5 ** k * spread).astype(np.float16) for k in range(q)])
+    alpha = np.stack([(0.016 * spread).astype(np.float16) * np.float16(factor ** k) for k in range(q)])
     z = (0.004 * rng.standard_normal((m, n // gg), dtype=np.float32)).astype(np.float16) if with_z else None
     alpha, z = L.lutgemm_pack_scales(alpha, z, n, gg)
     return Packed(bits, alpha, z, m, n, q, g)
@@ -191,3 +193,58 @@ def test_infinite_scale_of_the_last_group(m, n, q, g, with_z, batch, auto):
         pa, pz = L.lutgemm_pack_scales(alpha, z, n, gg)
         y = run(Packed(L.lutgemm_pack_planes(np.ones((q, m, n), dtype=np.int8)), pa, pz, m, n, q, g), X, f32_out=True, auto=auto)
         assert np.isposinf(y[:, [3, 67]]).all() and np.isfinite(np.delete(y, [3, 67], axis=1)).all()
+
+
+# Row ranges of several passes.  m, n, q, g, offsets, batch, LUTGEMM_PATH_AUTO; then row units of a wavefront's pass, wavefronts'
+# shares of the row units (of a K group with fewer K steps than wavefronts), passes of a workgroup, K groups and
+# chains (one or several).
+PASS_CASES = [
+    (33300, 1088, 5, 64, False, 17, False, 1, 1, 3, 1, 2),
+    (16470, 2176, 1, 32, True, 17, False, 1, 1, 2, 1, 2),
+    (18422, 1152, 8, 128, True, 32, False, 1, 1, 2, 1, 2),
+    (8597, 2336, 2, 32, False, 13, False, 1, 1, 2, 2, 1),
+    (8446, 5184, 3, 192, True, 18, False, 1, 1, 2, 2, 2),
+    (98351, 576, 1, 0, False, 24, False, 2, 1, 4, 1, 1),       # seven row units in passes of two
+    (98780, 640, 1, 0, True, 18, True, 2, 1, 4, 1, 1),
+    (65000, 896, 3, 128, True, 24, False, 2, 1, 2, 1, 1),
+    (52206, 1216, 4, 64, False, 24, False, 2, 1, 2, 1, 2),
+    (19589, 4288, 4, 64, False, 13, False, 2, 1, 2, 2, 2),
+    (73527, 576, 1, 0, False, 18, False, 3, 1, 2, 1, 1),       # five in passes of three
+    (97000, 896, 3, 128, False, 32, False, 3, 1, 2, 1, 1),
+    (32810, 288, 1, 32, False, 9, False, 1, 2, 2, 1, 1),       # three in passes of two shares, ...
+    (133654, 320, 1, 0, False, 17, False, 3, 2, 2, 1, 1),
+    (66131, 192, 2, 64, True, 13, False, 1, 4, 2, 1, 1),
+    (132915, 64, 1, 32, False, 17, False, 1, 8, 2, 1, 1),      # ... nine in passes of eight
+    (138934, 32, 5, 32, True, 24, False, 1, 8, 2, 1, 1),
+]
+
+
+@pytest.mark.parametrize("m,n,q,g,with_z,batch,auto,tall,shares,passes,groups,chains", PASS_CASES)
+def test_row_ranges_of_several_passes(m, n, q, g, with_z, batch, auto, tall, shares, passes, groups, chains):
+    (kernel, vectors, kg, tiles, ranges, chain, rows), = L.lutgemm_plan_gemm(m, n, q, g, with_z, batch, L.LUTGEMM_PATH_AUTO if auto else 0)
+    print(f"case f16 passes m={m} n={n} q={q} g={g} z={with_z} batch={batch}: {(kg, tiles, ranges, chain, rows)}", flush=True)
+    blocks = -(-m // 64)
+    units = -(-blocks // ranges)
+    assert (kernel, vectors) == (L.LUTGEMM_KERNEL_FP16, batch) and rows == tall * shares and -(-units // rows) == passes
+    assert shares == (1 if tiles > 1 or n > 512 else 8 // min(8, 1 << (-(-n // 128) - 1).bit_length()))
+    assert (kg > 1) == (groups > 1) and (chain < tiles) == (chains > 1)
+    p = _synthetic(m, n, q, g, with_z, seed=20000 + m, factor=2.0 if with_z else 0.5)
+    X = synth.activations_fp16(n, seed=20001 + n, batch=batch)
+    gg = n if g == 0 else g
+    z = None if p.z is None else O.decode_z(p.z, m, n // gg)
+    # where row units meet in the first two row ranges and the last, and others
+    first = np.arange(0, min(2 * units, blocks) + 1) * 64
+    check = np.concatenate([(first[:, None] + np.arange(-2, 2)).ravel(), np.arange(m - 130, m),
+                            (m - 64 * np.arange(1, units + 1)[:, None] + np.arange(-2, 2)).ravel(),
+                            np.random.default_rng(20002).integers(0, m, 150)])
+    check = np.unique(check[(check >= 0) & (check < m)])
+    bound = row_l1_bound(O.decode_alpha(p.alpha, m, n // gg, q), z, gg)[check]
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g, rows=check)
+    y = run(p, X, f32_out=True, auto=auto)
+    for b in range(batch):
+        check_parity(y[b][check], y_ref[b], X[b], bound, f32_out=True)
+    np.testing.assert_array_equal(y.astype(np.float16), run(p, X, auto=auto))
+    np.testing.assert_array_equal(run(p, X, f32_out=True, auto=auto), y)
+    if with_z and not auto:                                                     # one scale per group: the same bits
+        p.share()
+        np.testing.assert_array_equal(run(p, X, f32_out=True, shared=True), y)
