@@ -1572,17 +1572,17 @@ GemvKernel pick_dequant_q(int q) {
   return nullptr;
 }
 
-template <bool HAS_Z, int NB>
+template <bool HAS_Z>
 GemvKernel pick_planes_q(int q) {
   switch (q) {
-    case 1: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<1, HAS_Z, NB>);
-    case 2: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<2, HAS_Z, NB>);
-    case 3: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<3, HAS_Z, NB>);
-    case 4: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<4, HAS_Z, NB>);
-    case 5: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<5, HAS_Z, NB>);
-    case 6: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<6, HAS_Z, NB>);
-    case 7: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<7, HAS_Z, NB>);
-    case 8: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<8, HAS_Z, NB>);
+    case 1: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<1, HAS_Z, 1>);
+    case 2: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<2, HAS_Z, 1>);
+    case 3: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<3, HAS_Z, 1>);
+    case 4: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<4, HAS_Z, 1>);
+    case 5: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<5, HAS_Z, 1>);
+    case 6: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<6, HAS_Z, 1>);
+    case 7: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<7, HAS_Z, 1>);
+    case 8: return reinterpret_cast<const void*>(lutgemm_planes_mfma_kernel<8, HAS_Z, 1>);
   }
   return nullptr;
 }
@@ -2086,7 +2086,7 @@ const void* f16_family1(int q, int sb, int t) { return pick_f16<1>(q, sb, t); }
 const void* f16_family2(int q, int sb, int t) { return pick_f16<2>(q, sb, t); }
 #endif
 #if LUT_HAS_PART(9)
-const void* planes_family(int q, bool has_z) { return has_z ? pick_planes_q<true, 1>(q) : pick_planes_q<false, 1>(q); }
+const void* planes_family(int q, bool has_z) { return has_z ? pick_planes_q<true>(q) : pick_planes_q<false>(q); }
 #endif
 }  // namespace lutgemm_parts
 

@@ -4,8 +4,9 @@
 // What it computes is what the lookup kernels compute, plane by plane and group by group:
 // y_r = sum_i alpha_i[r][G] * (B_i . x)_G + z[r][G] * (sum of x over G), with B_i . x on
 // v_mfma_f32_32x32x16_f16: products +-x are exact, sums fp32.  Its time hardly depends on the number of vectors
-// (up to sixteen of the thirty-two rows of the operand may be repeats), so it is for batches that the lookups
-// would take in several turns and the 4-bit-float kernel in two launches, or not at all.
+// (the operand has thirty-two rows whatever it is; those beyond the last vector repeat it, and nobody reads what comes of
+// them), so it is for batches that the lookups would take in several turns and the 4-bit-float kernel in two launches, or not
+// at all; of the matrix-core path, which would else expand keys from a table, from one vector on.
 //
 // Weights.  A lane has 16 key bytes of a K step (128 columns) and row unit (64 rows) per plane, rows 4k..4k+3 of four
 // chunks; a byte transpose and an exchange between lanes 16 apart make words of 32 weights of one row of
@@ -23,9 +24,9 @@
 // K groups, where there are several, are the only ones that go through memory.  The activations of a tile come
 // by way of the registers into one half of LDS while the other half is in use: one barrier per tile.  A plane's keys and scales
 // give way to those of the next unit as soon as they are used up.  A pass of several row units shares the
-// activations' turn and the barrier, as many as the accumulators leave registers for (f16_most_tall).
+// activations' turn and the barrier, as many as the accumulators leave registers for (f16_most_tall; several chains: two).
 //
-// What bounds it (MI355X, 49152 x 12288, q = 3, g = 128, 32 vectors, weights in no cache): 110 us (1.05 PFLOP/s), where the
+// What bounds it (MI355X, 49152 x 12288, q = 3, g = 128, 32 vectors, weights in no cache): 109 us (1.06 PFLOP/s; 108 to 116 on several devices), where the
 // kernel before (+-1 from a table in LDS, half the vectors per product) took 167.  3456 matrix instructions per SIMD, 32
 // cycles each, are 46 us at full clock; 9 vector instructions to each of them, four of these conversions, take 40 cycles
 // of issue, of which the matrix instruction hides 24 or so.  The device also lowers its clock under this load: with
@@ -205,7 +206,9 @@ __global__ __launch_bounds__(kF16Waves * 64) void lutgemm_f16_kernel(F16Params p
 
   // ---- activations of a stage, one K tile, by way of the registers: a wavefront takes four vectors' part of every K
   // step, a lane one chunk of them.  A step lies in LDS as [product][half of K][vector]; the vectors of a piece of 512
-  // bytes are exchanged by its number so that neither side meets in a bank.  Beyond the last vector a load gives zeros.
+  // bytes are exchanged by its number so that neither side meets in a bank.  Rows beyond the last vector repeat it.  Columns
+  // beyond the last are the next vector's first ones, or, of the last vector, zeros (the buffer's bound holds for the whole offset, the
+  // scalar part included): stage_body puts zeros in the place of either.
   const int xc = lane & 15, xvec = 4 * wave + (lane >> 4);
   const __amdgpu_buffer_rsrc_t xrsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(p.x), 0, (int)((int64_t)p.vectors * p.n * 2), 0x00027000);

@@ -33,7 +33,7 @@ constexpr int kPlanesMaxUnits = 3;   // row blocks per wavefront (outputs held i
 
 // LDS map (bytes): sign table | block sums | X tile | per-wavefront key / scale / offset staging
 constexpr int kSignOff = 0;          // 16 nibbles x 32 copies x 8 B
-constexpr int kBlkSumOff = 4096;     // 16 blocks x 32 vectors fp32
+constexpr int kBlkSumOff = 4096;     // 16 blocks x 16 vectors (of 32) fp32
 constexpr int kXOff = 6144;          // 128 chunks x (NB * 16) vectors x 16 B
 
 template <int Q, int NB>
@@ -114,8 +114,8 @@ __device__ __forceinline__ void planes_stage(const PlanesRaw<Q, HAS_Z>& r, const
   if (HAS_Z && lane * 16 < t.nseg * 32) *reinterpret_cast<u32x4*>(zstage + lane * 16) = r.zz;
 }
 
-// One unit: all planes, all blocks of the tile; fin[nb][r] += contribution of this tile to
-// row 4 * (lane / 16) + r of the block for activation vector nb * 16 + lane % 16.
+// One unit: all planes, all blocks of the tile; fin[r] += contribution of this tile to
+// row 4 * (lane / 16) + r of the block for activation vector lane % 16.
 // The key words of four blocks are read from the staging area in one go; then, block by
 // block: key byte -> two sign-table reads -> matrix-core instructions, fully unrolled.  The
 // scales of a group are read when the group starts and used when it ends.  (The path is
@@ -216,26 +216,21 @@ __device__ __forceinline__ void dequant_compute(const GemvParams& p, const Plane
   }
 }
 
-template <int Q, bool HAS_Z, int NB, int T>
+template <int Q, bool HAS_Z, int T>
 __device__ __forceinline__ void planes_compute(const GemvParams& p, const PlanesTile& t, int lane, const u32x2* sign,
                                                const float* blksum, const f16x8* Xs, const uint32_t* stage,
                                                const unsigned char* astage, const unsigned char* zstage,
-                                               f32x4 (&fin)[NB]) {
-  constexpr int NB16 = NB * 16;
+                                               f32x4& fin) {
   const int sub = lane >> 4;        // slot within the block / quarter of the output rows
   const int col = lane & 15;        // row supplied to the A operand / activation vector of the outputs
   const int key_shift = 8 * (col & 3);
-  f32x4 acc[Q][NB];
-  float sx[NB];
+  f32x4 acc[Q];
+  float sx = 0.0f;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    sx[nb] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) acc[i][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
+  for (int i = 0; i < Q; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   const uint32_t* my_stage = stage + 4 * (col >> 2) + ((sub - (col >> 2)) & 3);   // (row col, slot sub) of block 0
   const u32x2* my_sign = sign + (lane & 31);
-  const f16x8* my_x = Xs + (T * sub) * NB16 + col;
+  const f16x8* my_x = Xs + (T * sub) * 16 + col;
   const unsigned char* my_alpha = astage + sub * Q * 8;
   const unsigned char* my_z = zstage + sub * 8;
   int seg = 0;                      // group segment of the current block, relative to t.G0
@@ -259,54 +254,38 @@ __device__ __forceinline__ void planes_compute(const GemvParams& p, const Planes
         for (int jj = 0; jj < 4; ++jj) kd[i][tt][jj] = my_stage[i * 512 + (tt * 16 + j0 + jj) * 16];
     // Operands of the next block are read while the current block is on the matrix cores,
     // where two sets of operands fit the registers (few planes); otherwise block by block.
-    constexpr bool kAhead = Q * NB <= 3;
-    PlanesOperands<Q, NB, T> ops[kAhead ? 2 : 1];
-    if (kAhead) planes_issue<Q, NB, T>(ops[0], kd, 0, j0, key_shift, my_sign, my_x);
+    constexpr bool kAhead = Q <= 3;
+    PlanesOperands<Q, 1, T> ops[kAhead ? 2 : 1];
+    if (kAhead) planes_issue<Q, 1, T>(ops[0], kd, 0, j0, key_shift, my_sign, my_x);
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
       const int j = j0 + jj;
       // (blocks past the end of a ragged tile read stale but valid staging memory and are not used)
       if (kAhead) {
-        if (jj < 3) planes_issue<Q, NB, T>(ops[(jj + 1) & 1], kd, jj + 1, j + 1, key_shift, my_sign, my_x);
+        if (jj < 3) planes_issue<Q, 1, T>(ops[(jj + 1) & 1], kd, jj + 1, j + 1, key_shift, my_sign, my_x);
         __builtin_amdgcn_sched_barrier(0);
       } else {
-        planes_issue<Q, NB, T>(ops[0], kd, jj, j, key_shift, my_sign, my_x);
+        planes_issue<Q, 1, T>(ops[0], kd, jj, j, key_shift, my_sign, my_x);
       }
       if (j < t.nblk) {   // wave-uniform
-        const PlanesOperands<Q, NB, T>& o = ops[kAhead ? (jj & 1) : 0];
+        const PlanesOperands<Q, 1, T>& o = ops[kAhead ? (jj & 1) : 0];
 #pragma unroll
         for (int tt = 0; tt < T; ++tt)
 #pragma unroll
-          for (int i = 0; i < Q; ++i)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-              acc[i][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(o.a[tt][i], o.b[tt][nb], acc[i][nb], 0, 0, 0);
-        if (HAS_Z) {
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) sx[nb] += blksum[j * 32 + nb * 16 + col];
-        }
+          for (int i = 0; i < Q; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(o.a[tt][i], o.b[tt][0], acc[i], 0, 0, 0);
+        if (HAS_Z) sx += blksum[j * 32 + col];
         --left;
         if (j == t.nblk - 1 || left == 0) {   // wave-uniform: the group ends here (section 3.2 rule 2)
 #pragma unroll
           for (int i = 0; i < Q; ++i) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float af = half_of(a4[i], r);
-#pragma unroll
-              for (int nb = 0; nb < NB; ++nb) fin[nb][r] = fmaf(af, acc[i][nb][r], fin[nb][r]);
-            }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int r = 0; r < 4; ++r) fin[r] = fmaf(half_of(a4[i], r), acc[i][r], fin[r]);
+            acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
           }
           if (HAS_Z) {   // offset term of eq. 3
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float zf = half_of(z4, r);
-#pragma unroll
-              for (int nb = 0; nb < NB; ++nb) fin[nb][r] = fmaf(zf, sx[nb], fin[nb][r]);
-            }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) sx[nb] = 0.0f;
+            for (int r = 0; r < 4; ++r) fin[r] = fmaf(half_of(z4, r), sx, fin[r]);
+            sx = 0.0f;
           }
           left = seg_blocks;
           seg = min(seg + 1, t.nseg - 1);   // the next group's scales, used when that group ends
@@ -389,8 +368,10 @@ __device__ __forceinline__ void finish_rows_batch(const GemvParams& p, uint32_t*
   if (threadIdx.x == 0) __hip_atomic_store(p.counters + rs, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// NB: sixteens of activation vectors (two: the dequantising form only).
 template <int Q, bool HAS_Z, int NB, bool DQ = false>
 __global__ __launch_bounds__(PlanesCfg<Q>::kThreadsM) void lutgemm_planes_mfma_kernel(GemvParams p) {
+  static_assert(DQ || NB == 1, "planes_compute");
   using C = PlanesCfg<Q>;
   constexpr int NB16 = NB * 16;
   constexpr int kThr = C::kThreadsM;
@@ -501,11 +482,11 @@ __global__ __launch_bounds__(PlanesCfg<Q>::kThreadsM) void lutgemm_planes_mfma_k
             dequant_compute<Q, HAS_Z, NB, 1>(p, t, lane, sign, reinterpret_cast<const f16x8*>(Xs), stage, astage, zstage,
                                              fin[u]);
         } else if (t.T == 2) {
-          planes_compute<Q, HAS_Z, NB, 2>(p, t, lane, sign, blksum, reinterpret_cast<const f16x8*>(Xs), stage, astage,
-                                          zstage, fin[u]);
+          planes_compute<Q, HAS_Z, 2>(p, t, lane, sign, blksum, reinterpret_cast<const f16x8*>(Xs), stage, astage,
+                                          zstage, fin[u][0]);
         } else {
-          planes_compute<Q, HAS_Z, NB, 1>(p, t, lane, sign, blksum, reinterpret_cast<const f16x8*>(Xs), stage, astage,
-                                          zstage, fin[u]);
+          planes_compute<Q, HAS_Z, 1>(p, t, lane, sign, blksum, reinterpret_cast<const f16x8*>(Xs), stage, astage,
+                                          zstage, fin[u][0]);
         }
       }
     }
