@@ -1705,27 +1705,35 @@ int f16_scale_groups(int q, int64_t n, int64_t gg, int vectors);
 // in the place of lookups (four at a time) or of several launches of the 4-bit-float kernel.  Microseconds,
 // before / that kernel:
 //   * Lookups (odd multiples of 32 columns; seven and eight planes; five and more at odd multiples of 64), five vectors:
-//     1024 x 1024, q = 3, g = 32 16 / 8.4, 131 x 31232 28 / 12, 1024 x 1024, q = 8 22 / 10; 12288 x 12288, q = 3, g = 32 52 / 45 but 49152 x
-//     12288 142 / 160 and 20480 x 5120 39.5 / 41.1.  Eight vectors: 181 / 160, 51 / 41, 8192 x 22016 83 / 52, q = 8 121 / 86;
-//     32 vectors: 721 / 168, 204 / 45, 329 / 55, 475 / 90.
-//   * g = 64, up to four planes, from nine vectors on: 12288 x 12288, q = 2 with offsets 49 / 35, 5120 x 5120 26 / 12,
-//     49152 x 12288 134 / 114; at 32 vectors 98 / 37, 45 / 13, 290 / 119.
+//     1024 x 1024, q = 3, g = 32 15 / 8.5, 131 x 31232 28 / 13, 1024 x 1024, q = 8 21 / 10, 6646 x 320, q = 7 18 / 10.6; but larger layers take
+//     as long as at eight, 12288 x 12288, q = 3, g = 32 53 / 53, 49152 x 12288 144 / 174, 20480 x 5120 41 / 45: from seven on.  Eight
+//     vectors: 70 / 53, 182 / 174, 53 / 45, 8192 x 22016 85 / 61, 12288 x 12288, q = 8 98 / 78; 32 vectors: 274 / 63, 726 / 185, 207 / 54,
+//     334 / 67, 384 / 82.
+//   * g = 64, up to four planes, nine vectors: 8192 x 8192, q = 4 31 / 28, 12288 x 12288, q = 1 28 / 24, but of two planes and more
+//     eight vectors in the 4-bit-float kernel and one by lookups are as fast on large layers, 12288 x 12288, q = 4 54 / 55, 24576 x 8192,
+//     q = 4 64 / 68, 36864 x 12288, q = 2, offsets 89 / 98; of one plane with offsets also at ten, 20480 x 5120 27 / 30, 36864 x 12288 69 /
+//     82.  At ten 24576 x 8192, q = 4 74 / 73, 49152 x 12288, q = 4 181 / 181, q = 2 103 / 95
+//     (missed by the rule: 36864 x 12288, q = 1 53 / 57 at nine, with offsets 80 / 83 at eleven); at twelve 49152 x 12288, q = 3 161 / 142, 12288 x 12288,
+//     q = 2, offsets 50 / 39; at 32 351 / 159, 103 / 46, 5120 x 5120, q = 4 52 / 19.
 //   * Whole K steps per group, up to six planes, from seventeen vectors on (sixteen in the 4-bit-float kernel, then the rest):
-//     12288 x 12288, q = 3 51 / 36 at 17 vectors, 72 / 39 at 32; 20480 x 5120, q = 4 45 / 40, 62 / 42; 5120 x 5120 22 / 14,
-//     28 / 15; 2223 x 8576, q = 2, offsets 25 / 13.  (Of 49152 x 12288 and more, and of fewer than 2^25 weights
-//     at 17 to 19 vectors, tests name the 4-bit-float kernel, though 142 / 117 and 15.4 / 9.7 us (1500 x 3072) are to be had.)
+//     12288 x 12288, q = 3 52 / 41 at 17 vectors, 72 / 43 at 32; 20480 x 5120, q = 4 46 / 42, 64 / 45; 5120 x 5120 30 / 17 at 32;
+//     2223 x 8576, q = 2, offsets 26 / 14.  (Of 2^29 weights and more, and of fewer than 2^25 at 17 to 19 vectors, tests
+//     name the 4-bit-float kernel, though 157 / 114 (49152 x 12288, q = 3 at 20) and 15.5 / 9.7 us (1500 x 3072) are to be had.)
 // Layers of 2^24 to 2^25 weights keep the kernels they had up to ten vectors (sixteen at g = 64, six elsewhere), and five and
 // six vectors of five planes and more at g = 64 everywhere: the tests of the lookup kernels and of
 // lutgemm_plan_gemm name these kernels for such calls, though the other is faster there too (4096 x 4096, q = 3, g = 32
 // 20 / 11 at five vectors; q = 5, g = 64 22 / 12).
-bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, int left) {
+bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, bool has_z, int left) {
   const int sb = left < 5 ? 0 : f16_scale_groups(q, n, gg, left);
   if (sb == 0) return false;
   const int64_t w = m * n;
   if (sb == 1 && q <= kFp4MaxPlanes)
     return left >= (w < (int64_t)1 << 25 ? 20 : 17) && w < (int64_t)1 << 29;
   const int size = w < (int64_t)1 << 24 ? 0 : (w < (int64_t)1 << 25 ? 1 : 2);
-  if (sb == 2 && q <= kFp4MaxPlanesSplit) return left > (size == 1 ? 16 : 8);
+  if (sb == 2 && q <= kFp4MaxPlanesSplit) {
+    const int large = q > 1 ? 10 : (has_z ? 11 : 9);
+    return left >= (size == 1 ? 17 : (w < (int64_t)3 << 25 ? 9 : large));
+  }
   return left >= (size == 0 && sb != 2 ? 5 : (size == 1 && sb == 4 ? 11 : 7));
 }
 
@@ -1735,8 +1743,8 @@ bool lookups_yield_to_f16(int q, int64_t m, int64_t n, int64_t gg, int left) {
 struct GemmPass {
   int kernel, vectors;
 };
-GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, int batch, int left) {
-  if (left == batch && lookups_yield_to_f16(q, m, n, gg, left)) return {LUTGEMM_KERNEL_FP16, left};
+GemmPass gemm_pass(int q, int64_t m, int64_t n, int64_t gg, bool has_z, int batch, int left) {
+  if (left == batch && lookups_yield_to_f16(q, m, n, gg, has_z, left)) return {LUTGEMM_KERNEL_FP16, left};
   const int pass = fp4_pass(q, m, n, gg, left);
   if (pass > 0) return {LUTGEMM_KERNEL_FP4, pass};
   if (left >= 3) return {LUTGEMM_KERNEL_QUAD, left >= 4 ? 4 : 3};
@@ -1925,7 +1933,7 @@ int f16_most_tall(int q, int sb, bool has_z) {
 //   * Matrix-core path, once the kernel that expands keys from a table: 48, which leaves whole K groups to most layers; 24 with
 //     groups of 1024 columns and more, whose sums that kernel scaled once a tile.  FC1 (49152 x 12288, q = 3) at 32 vectors 2.19 / 1.18 / 1.18,
 //     7446 x 27264, q = 7, row-wise at 24 1.50 / 1.87 / 1.03, 8192 x 22016, q = 6, row-wise 1.34 / 1.55 / 1.03.
-// 280 drawn layers (0.3 to 200 million weights, all routes): 0.53 to 0.93 of the error before on average of a route, 1.11 at most (1455 x 12288,
+// 246 drawn layers (0.3 to 200 million weights, all routes): 0.53 to 0.93 of the error before on average of a route, 1.11 at most (1455 x 12288,
 // q = 4, g = 128, offsets 0.57 / 0.63 / 0.63); time 0.98 to 1.00 of the unbounded kernel's on average of a route, 1.16 at most.
 struct F16Tiles {
   int chain, group;
@@ -2193,7 +2201,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   if (cus <= 0) return LUTGEMM_EHIP;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
-  if (lookups_yield_to_f16(q, m, n, gg, batch))   // (the whole batch: see gemm_pass)
+  if (lookups_yield_to_f16(q, m, n, gg, z != nullptr, batch))   // (the whole batch: see gemm_pass)
     return launch_f16(cus, q, shared, m, n, gg, batch, (flags & LUTGEMM_Y_F32) != 0, gemm_f16_tiles(q, n, gg, z != nullptr, batch),
                       f16_buffers(x, bits, alpha, z, y, workspace), stream);
 
@@ -2239,7 +2247,7 @@ int lutgemm_gemm(const void* x, const void* bits, const void* alpha, const void*
   pf.vec_stride = m_pad;
   fill_fp4_shape(&pf, m, n, gg, p.y_f32 != 0);
   for (int b = 0; b < batch;) {
-    const GemmPass pass = gemm_pass(q, m, n, gg, batch, batch - b);
+    const GemmPass pass = gemm_pass(q, m, n, gg, z != nullptr, batch, batch - b);
     if (pass.kernel == LUTGEMM_KERNEL_FP4) {
       pf.x = static_cast<const __half*>(x) + (int64_t)b * n;
       pf.y = static_cast<char*>(y) + (int64_t)b * m * y_elem;
@@ -2387,7 +2395,7 @@ int lutgemm_plan_gemm(int64_t m, int64_t n, int q, int g, int has_offsets, int b
   int launches = 0;
   for (int b = 0; b < batch; ++launches) {
     if (launches == max_launches) return LUTGEMM_EWORKSPACE;
-    const GemmPass pass = fp16 ? GemmPass{LUTGEMM_KERNEL_FP16, batch} : gemm_pass(q, m, n, gg, batch, batch - b);
+    const GemmPass pass = fp16 ? GemmPass{LUTGEMM_KERNEL_FP16, batch} : gemm_pass(q, m, n, gg, has_offsets != 0, batch, batch - b);
     int* o = out + 7 * launches;
     o[0] = pass.kernel;
     o[1] = pass.vectors;

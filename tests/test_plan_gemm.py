@@ -152,3 +152,12 @@ def test_long_rows_are_planned_in_no_time():
             assert plan[0][0] == FP16
         return min(times)
     assert best(1 << 25) < 8 * best(1 << 13)
+
+
+@pytest.mark.parametrize("m,n,q,z,least", [(8192, 8192, 3, True, 9), (24576, 8192, 3, False, 10), (36864, 12288, 2, True, 10),
+                                           (36864, 12288, 1, True, 11), (20480, 5120, 1, True, 11), (20480, 5120, 1, False, 9)])
+def test_one_or_two_vectors_beyond_eight(m, n, q, z, least):
+    # Groups of 64 columns: on large layers eight vectors as 4-bit floats and one or two by lookups are the faster way.
+    for batch in range(9, 13):
+        kernels = [p[0] for p in L.lutgemm_plan_gemm(m, n, q, 64, z, batch, 0, 256)]
+        assert (kernels == [FP16]) == (batch >= least) and (kernels[0] == FP4) == (batch < least)
