@@ -120,9 +120,9 @@ enum {
      than 2^28 weights, and from three on layers of at most 2^25.  Section 6 of the paper: the
      lookup path pays per vector, the matrix cores do not.  Up to sixteen vectors the two
      ways mostly run the same kernel anyway (see lutgemm_gemm), and where they do not the flag is
-     the faster one or within a tenth of it.  From seventeen vectors on it is the faster one on layers of 2^29
-     weights and more (49152 x 12288, q = 3: 109 us against 155 at twenty, 110 against 205 at 32), on smaller ones
-     the two ways mostly differ in the grid only.  Either path meets the same tolerance; which one ran is decided by shape and batch only, so results stay
+     the faster one or within a tenth of it.  From seventeen vectors on it is the faster one on the largest
+     layers (49152 x 12288, q = 3: 109 us against 155 at twenty, 110 against 205 at 32); on others the two
+     ways mostly differ in the grid only.  Either path meets the same tolerance; which one ran is decided by shape and batch only, so results stay
      reproducible.                                                                        */
   LUTGEMM_PATH_AUTO = 4
 };
@@ -242,22 +242,18 @@ int lutgemm_gemv_static(const void* x, const void* bits, const void* alpha, cons
 size_t lutgemm_static_scratch_bytes(void);
 
 /* As lutgemm_gemv for `batch` activation vectors (1 <= batch <= 32): x is fp16
-   [batch][n], y is [batch][m], workspace sized for this batch.  Two kinds of kernel, chosen by
+   [batch][n], y is [batch][m], workspace sized for this batch.  Three kinds of kernel, chosen by
    shape, batch and group size:
    - Group sizes that are multiples of 128 columns (g == 0, row-wise, included) and up to six planes:
      the binary planes on the matrix cores as 4-bit floats, up to sixteen vectors per launch, from
-     three vectors on (two on layers of 256 rows and more, up to 2^28 weights and five planes) and, but for layers
-     of 2^29 weights and more, up to sixteen (nineteen below 2^25 weights); odd
+     three vectors on (two on layers of 256 rows and more, up to 2^28 weights and five planes); odd
      multiples of 64 columns and up to four planes: the same for five to eight vectors at a
-     time, unless the next kind takes them.  Nothing is dequantised.  An activation is held as six 6-bit digits of its block of 32
+     time.  Either unless the next kind takes the batch.  Nothing is dequantised.  An activation is held as six 6-bit digits of its block of 32
      columns: exactly, unless it is more than 2^18 times smaller than the largest there, and else to
      2^-29 of that one (an fp32 sum that holds the largest resolves 2^-24 of it).
-   - Group sizes that are multiples of 32 columns, where neither of the others would do in one turn: the
-     planes on the matrix cores as fp16 +-1, all vectors in one launch, from five or seven vectors on (eleven
-     at odd multiples of 32 columns on layers of 2^24 to 2^25 weights; seven and eight planes too, except at
-     odd multiples of 32), at odd multiples of 64 columns and up to four planes from nine (seventeen on
-     layers of 2^24 to 2^25 weights), at multiples of 128 and up to six planes from seventeen (twenty below 2^25
-     weights, never from 2^29 weights on).
+   - Group sizes that are multiples of 32 columns (of 64 with seven and eight planes; row-wise included), where neither of the others
+     would do in one turn: the planes on the matrix cores as fp16 +-1, all vectors in one launch.  From
+     five vectors on at the least; how many it takes depends on the group size, the planes and the layer.
    - Else lookups: the vectors are taken four at a time; two or one left over have kernels of
      their own, three left over run as four (the fourth table set repeats the third vector, its
      results are dropped).  One table set per activation vector, each fetched key looked up in
