@@ -21,16 +21,18 @@
 //     of the rows) 2.
 //   * Sums of digit products of a block are small integers in units of the block scale and
 //     exact inside the instruction; blocks whose scales differ by up to 2^14 add exactly (measured).
-//     Where a chain's accumulator enters an instruction its bits below 2^-24 of the largest product
-//     are cut off, not rounded: up to three digits of a row (eight vectors) are one chain with the largest digit
-//     first, so that no accumulator meets products larger than its own; six (sixteen vectors) are two
-//     chains, the two largest, whose products are exact, and the others, which meet in a rounded addition.
-//     Error against 64-bit sums
-//     (2-norm, 8192 x 8192 to 4096 x 16384, q = 2 to 6, 2 to 16 vectors; N(0, 1) activations alone, with 30
-//     times larger ones every 1024 columns, or 2^14 times larger ones every 32): 0.62e-7 to 1.0e-7;
-//     one chain with the smallest digit first 2.6e-7 at worst; lookups 0.84e-7 to 1.8e-7, fp16 matrix path 1.0e-7 to 3.0e-7.
-//     (Three digits at eight vectors, largest first / as two chains: 0.66 / 0.72e-7 of N(0, 1), 0.77 / 0.75 with the 2^14 times
-//     larger ones, 4096 x 8192, q = 3; six digits in one chain, largest first, 0.63 / 0.68 and 0.89 / 0.71, not taken.)
+//     A chain's accumulator loses bits where it meets products that are much larger than it, or so
+//     much smaller that the sum takes more than 24 bits: a row's two largest digits, whose sum takes
+//     no more while the four block scales of a K step are within 2^7, and the others have chains
+//     of their own, which meet in a rounded addition.  Error against 64-bit sums (2-norm,
+//     8192 x 8192 to 4096 x 16384, q = 2 to 6, 2 to 16 vectors; N(0, 1) activations alone, with 30
+//     times larger ones every 1024 columns, or 2^14 times larger ones every 32): 0.64e-7 to 1.0e-7;
+//     six digits in one chain, the smallest first, 2.6e-7 at worst; lookups 0.84e-7 to 1.8e-7, fp16
+//     matrix path 1.0e-7 to 3.0e-7.
+//     Not taken, three digits (five to eight vectors) in one chain: the largest first 0.62 and 0.66e-7
+//     for 0.64 and 0.72 of N(0, 1) activations (2048 x 16384, q = 2 at six vectors; 4096 x 8192, q = 3
+//     at eight), but 0.73 and 0.77 for 0.67 and 0.75 with the 2^14 times larger ones; the smallest
+//     first 1.84 and 1.56 there.  It would save 3 us of the 67 below.
 //
 // Work split.  A K step is 128 columns, a row unit four row blocks (64 rows), a unit the two
 // together: per plane one 16-byte key load per lane and 4 x 6 / R instructions, number b of the 4
@@ -45,15 +47,13 @@
 // not depend on who computed what.
 //
 // What bounds it (MI355X, 49152 x 12288, q = 3, g = 128, weights in no cache; microseconds, before: lookups
-// at 4 vectors, fp16 matrix cores beyond): 53 at 4 vectors (before 72), 64 at 8 (113), 102 at 16 (118).
+// at 4 vectors, fp16 matrix cores beyond): 53 at 4 vectors (before 72), 67 at 8 (113), 102 at 16 (118).
 // Up to four vectors mostly the weight stream (255 MB, 38 us at the 6.7 TB/s of a read loop), with
 // 2 to 3 us until the digits stand and 2 to 8 for the hand-off around it.  At 16 the matrix and the
 // vector units together: 5184 matrix instructions per SIMD (10 to 11 ns each with random operands, 7.4
 // with zeros: 54 us) and 24,500 vector instructions, on two wavefronts that hide the one
 // behind the other only in part; the hand-off, 3 MB of partial sums per K group, is most of the
-// rest.  The sixth digit is 3 us of the 64 and, with the second chain, 9 of the 102.  A second chain for eight vectors, 48
-// more vector instructions in the 250 of a unit: 67 (8192 x 8192 13.9 for 13.2, 5120 x 5120, q = 4 11.6 for 11.0, 8192 x 8192,
-// q = 6 19.2 for 18.0; vector instructions and these products hardly overlap: 8 and 1 of them take 24 ns, alone 16 and 10).  Eight wavefronts at
+// rest.  The second chain is 3 us of the 67 and the sixth digit about 1; both are 9 of the 102.  Eight wavefronts at
 // 256 registers: with twelve or sixteen the accumulators spill or it measured slower; both
 // chains of a plane in flight together measured equal.
 #pragma once
@@ -375,10 +375,8 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
     for (int c = C - 1; c >= 0; --c) held[kHold ? c : 0] = fp4_digit(L, lds, local, c);
   }
   auto digit = [&](int c) { return kHold ? held[kHold ? c : 0] : fp4_digit(L, lds, local, c); };
-  // Three digits of a row in one chain, the largest first; six as the two largest and the others (see the head of this file).  Two are
-  // exact either way (the smaller one first: 20480 x 5120, q = 4 at four vectors 17.8 us, the other way round 18.2).
-  constexpr int kHi = C <= 3 ? C : 2, kChains = C > kHi ? 2 : 1;
-  auto nth = [&](int h, int j) { return C == 3 ? j : (h ? C : kHi) - 1 - j; };   // digit of chain h that comes j-th
+  // The two largest digits of a row, then the others (see the head of this file).
+  constexpr int kHi = C < 2 ? C : 2, kChains = C > kHi ? 2 : 1;
   f32x4 sum[4] = {zero, zero, zero, zero};
   if (ZM != 0) {   // offset term of eq. 3: z times the sum of the activations
     const int m1 = (int)0xaaaaaaaa;
@@ -387,7 +385,7 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
     for (int h = kChains - 1; h >= 0; --h) {
       f32x4 sx = zero;
 #pragma unroll
-      for (int j = 0; j < (h ? C - kHi : kHi); ++j) sx = fp4_mfma(digit(nth(h, j)), w, sx, scale - 5 * nth(h, j));
+      for (int c = (h ? C : kHi) - 1; c >= (h ? kHi : 0); --c) sx = fp4_mfma(digit(c), w, sx, scale - 5 * c);
 #pragma unroll
       for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -407,10 +405,10 @@ __device__ __forceinline__ void fp4_compute(const Fp4Unit<Q, ZM, SB>& u, const F
     for (int h = kChains - 1; h >= 0; --h) {
       f32x4 s[4] = {zero, zero, zero, zero};   // four independent chains
 #pragma unroll
-      for (int j = 0; j < (h ? C - kHi : kHi); ++j) {
-        const i32x8 a = digit(nth(h, j));
+      for (int c = (h ? C : kHi) - 1; c >= (h ? kHi : 0); --c) {
+        const i32x8 a = digit(c);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) s[b] = fp4_mfma(a, w[b], s[b], scale - 5 * nth(h, j));
+        for (int b = 0; b < 4; ++b) s[b] = fp4_mfma(a, w[b], s[b], scale - 5 * c);
       }
 #pragma unroll
       for (int b = 0; b < 4; ++b)

@@ -202,6 +202,32 @@ def test_error_with_large_outliers_is_no_larger_than_the_lookups(batch, period):
     assert planes <= lookups, f"{planes} against {lookups}"
 
 
+@pytest.mark.parametrize("offsets", [False, True])
+@pytest.mark.parametrize("batch", [4, 5, 8, 16])
+@pytest.mark.parametrize("spread", [0, 3, 7])
+def test_sum_of_a_step_is_its_nearest_number(batch, offsets, spread):
+    # K steps of numbers that the first three digits hold, in one or two blocks of the largest magnitude and others
+    # 2^spread times smaller (32 columns share a block scale: every other eight of 64).  The sum of two digits takes 24 bits at most (2^8 to 2^-8, and 7 more), the
+    # third one's 19: both are exact, and added up they are rounded once, to the exact sum's nearest
+    # fp32 number.  Where the third digit enters the accumulator of the other two its last bits are lost.
+    # Row r returns K step r's sum (the offset term's: with no signs): it has scales of 1 there and of 0 elsewhere.
+    steps, n = 256, 256 * 128
+    rng = np.random.default_rng(19000 + 100 * spread + batch)
+    signs = rng.choice(np.array([-1, 1], dtype=np.int8), (1, steps, n), p=[0.1, 0.9])
+    ones = np.eye(steps, dtype=np.float16)
+    alpha, z = L.lutgemm_pack_scales(np.zeros_like(ones)[None] if offsets else ones[None], ones if offsets else None, n, 128)
+    p = Packed(L.lutgemm_pack_planes(signs), alpha, z, steps, n, 1, 128)
+    assert [k[0] for k in L.lutgemm_plan_gemm(steps, n, 1, 128, offsets, batch)] == [L.LUTGEMM_KERNEL_FP4]
+    x = rng.integers(1024, 2048, (batch, steps, 128)) / 1024.0 * 2.0 ** -rng.integers(0, 4, (batch, steps, 128))
+    x[:, :, [0, 8, 64, 72]] = 1.0 + rng.integers(0, 1024, (batch, steps, 4)) / 1024.0     # a block's largest is 1 to 2, ...
+    down = np.array([[0, 1, 1, 1], [0, 0, 1, 1]])[rng.integers(0, 2, (batch, steps))] * spread    # ... and so many powers of two less
+    block = 2 * (np.arange(128) // 64) + np.arange(128) // 8 % 2
+    x = x * rng.choice([-1.0, 1.0], x.shape, p=[0.1, 0.9]) * 2.0 ** -down[:, :, block]
+    own = signs[0].reshape(steps, steps, 128)[np.arange(steps), np.arange(steps)].astype(np.float64)
+    exact = (x if offsets else x * own).sum(axis=2)
+    np.testing.assert_array_equal(run(p, x.reshape(batch, n).astype(np.float16), f32_out=True), exact.astype(np.float32))
+
+
 @pytest.mark.parametrize("batch,g", [(3, 128), (7, 128), (13, 128), (6, 64)])
 def test_infinite_scale_beside_infinite_activations(batch, g):
     # A row with an infinite scale is +inf for finite activations (signs and activations all positive, with
