@@ -61,16 +61,20 @@ def test_edges_match_oracle(m, n, q, g, mode, batch):
         np.testing.assert_array_equal(run(p, X, f32_out=True, auto=True), run(p, X, f32_out=True, mfma=True))
 
 
-@pytest.mark.parametrize("g,batch", [(128, 4), (128, 8), (128, 16), (64, 8)])
-def test_wide_range_activations(g, batch):
+@pytest.mark.parametrize("g,batch,mode,shared", [(128, 4, "greedy", False), (128, 8, "greedy", False), (128, 16, "greedy", False),
+                                                 (64, 8, "greedy", False), (128, 8, "greedy_z", False), (128, 8, "rtn", False),
+                                                 (128, 8, "rtn", True)])
+def test_wide_range_activations(g, batch, mode, shared):
     # Subnormals, ordinary numbers and the largest ones within one block of 32 columns.  A digit expansion
     # is off by at most 2^-29 of the block's largest magnitude per activation; everything else is exact or
-    # an fp32 rounding, of which a sum of up to 12 steps of 3 planes, added up in 64 bits behind
-    # that, has at most 24 in a row:
-    # |error| <= sum(alpha) * (32 * 2^-29 * sum over blocks of the largest + 24 * 2^-24 * |x|_1).
+    # an fp32 rounding, of which a sum of up to 12 steps of 3 planes and offsets, added up in 64 bits behind
+    # that, has at most 24 in a row (8 chains of a step, 12 steps, 3 operand rows):
+    # |error| <= (sum(alpha) + |z|) * (32 * 2^-29 * sum over blocks of the largest + 24 * 2^-24 * |x|_1).
     m, n, q = 200, 2048, 3
     W = synth.weights_fp16(m, n, seed=16900)
-    p = Packed.from_weights(W, q, g)
+    p = Packed.from_weights(W, q, g, MODES[mode])
+    if shared:
+        p.share()
     X = synth.activations_fp16(n, seed=16901, batch=batch)
     X[:, ::5] = np.float16(6.0e-8)
     X[:, 1::37] *= np.float16(1000.0)
@@ -78,8 +82,11 @@ def test_wide_range_activations(g, batch):
     X[1, :] = (np.arange(n) % 1024 + 1).astype(np.float16) * np.float16(2.0 ** -24)   # subnormals alone: exact digits
     X[2, 2::3] = 0
     y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g)
-    y = run(p, X, f32_out=True).astype(np.float64)
-    a = O.decode_alpha(p.alpha, m, n // g, q).astype(np.float64).sum(axis=0).max(axis=1)
+    y = run(p, X, f32_out=True, shared=shared).astype(np.float64)
+    a = O.decode_alpha(p.alpha, m, n // g, q).astype(np.float64).sum(axis=0)
+    if p.z is not None:
+        a += np.abs(O.decode_z(p.z, m, n // g).astype(np.float64))
+    a = a.max(axis=1)
     ax = np.abs(X.astype(np.float64))
     for b in range(batch):
         limit = a * (32 * 2.0 ** -29 * ax[b].reshape(-1, 32).max(axis=1).sum() + 24 * 2.0 ** -24 * ax[b].sum())
@@ -226,6 +233,30 @@ def test_sum_of_a_step_is_its_nearest_number(batch, offsets, spread):
     own = signs[0].reshape(steps, steps, 128)[np.arange(steps), np.arange(steps)].astype(np.float64)
     exact = (x if offsets else x * own).sum(axis=2)
     np.testing.assert_array_equal(run(p, x.reshape(batch, n).astype(np.float16), f32_out=True), exact.astype(np.float32))
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("g,batch", ROWS_PER_VECTOR)
+@pytest.mark.parametrize("period", [32, 1024])
+def test_error_of_large_offsets_with_large_outliers(g, batch, shared, period):
+    # The same where the offsets are a thousand times the scales: the result is the offset term's, which has digits and
+    # chains of its own.
+    m, n, q = 1024, 4096, 3
+    rng = np.random.default_rng(19200)
+    step = (0.001 + 0.0002 * rng.random((m, n // g))).astype(np.float16)
+    alpha = np.stack([step * np.float16(2 ** i) for i in range(q)])
+    alpha, z = L.lutgemm_pack_scales(alpha, rng.standard_normal((m, n // g)).astype(np.float16), n, g)
+    p = Packed(rng.integers(0, 256, L.lutgemm_bits_bytes(m, n, q), dtype=np.uint8), alpha, z, m, n, q, g).share()
+    X = synth.activations_fp16(n, seed=19201 + batch, batch=batch)
+    X[:, ::period] *= np.float16(2.0 ** 13)
+    y_ref, _ = c_oracle.gemv_packed(p.bits, p.alpha, p.z, X, m, n, q, g)
+
+    def error(y):
+        return np.linalg.norm(y - y_ref) / np.linalg.norm(y_ref)
+
+    planes = error(run(p, X, f32_out=True, shared=shared))
+    lookups = error(np.stack([run(p, x, f32_out=True, shared=shared) for x in X]))
+    assert planes <= lookups, f"{planes} against {lookups}"
 
 
 @pytest.mark.parametrize("batch,g", [(3, 128), (7, 128), (13, 128), (6, 64)])
