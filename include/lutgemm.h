@@ -295,7 +295,7 @@ int lutgemm_gemm_mfma(const void* x, const void* bits, const void* alpha, const 
    product to a relative L2 error of about 3e-4 (bound asked of it: 1e-3), not to the 1e-5
    of the other paths' fp32 outputs.  Same restrictions as lutgemm_gemm_mfma.  Bitwise
    reproducible.  Measured beside the plane-wise form on MI355X (49152 x 12288, q = 3): 157 us
-   up to 16 activation vectors against 64 at 8 and 102 at 16, 180 against 110 at 32: rebuilding fp16
+   up to 16 activation vectors against 67 at 8 and 102 at 16, 180 against 110 at 32: rebuilding fp16
    weights buys nothing over multiplying the planes, and costs accuracy.                  */
 int lutgemm_gemm_dequant_mfma(const void* x, const void* bits, const void* alpha, const void* z, void* y,
                               int q, int g, int mu, int64_t m, int64_t n, int batch, unsigned flags,

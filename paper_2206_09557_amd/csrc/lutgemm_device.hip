@@ -1650,7 +1650,7 @@ int fp4_rows_per_vector(int vectors, int sb) { return sb > 1 || vectors > 8 ? 1 
 // (or not for it).  Where the lines lie, old path / this kernel in microseconds (MI355X, weights in no
 // cache):
 //   * One scale group per K step, up to six planes: from three vectors on.  49152 x 12288, q = 3:
-//     75 / 53 at 3 and 4 vectors, 113 / 67 at 8, 118 / 102 at 16; 5120 x 5120, q = 4: 15.1 / 10.1, 14.4 / 12.1,
+//     75 / 53 at 3 and 4 vectors, 113 / 67 at 8, 118 / 102 at 16; 5120 x 5120, q = 4: 15.1 / 10.1, 14.4 / 11.6,
 //     15.7 / 14.4; 8192 x 8192, q = 6 with offsets: 27 / 18, 48 / 21, 50 / 31.  (The old paths there: lookups
 //     up to four or five vectors, fp16 matrix cores above, which a few layers go back to where the
 //     caller leaves the choice, see matrix_cores_take_fp4; the lookups are 2 to 5 times slower from

@@ -53,7 +53,7 @@
 // vector units together: 5184 matrix instructions per SIMD (10 to 11 ns each with random operands, 7.4
 // with zeros: 54 us) and 24,500 vector instructions, on two wavefronts that hide the one
 // behind the other only in part; the hand-off, 3 MB of partial sums per K group, is most of the
-// rest.  The second chain is 3 us of the 67 and the sixth digit about 1; both are 9 of the 102.  Eight wavefronts at
+// rest.  The second chain is 3 us of the 67, the sixth digit about 1 by difference; both are 9 of the 102.  Eight wavefronts at
 // 256 registers: with twelve or sixteen the accumulators spill or it measured slower; both
 // chains of a plane in flight together measured equal.
 #pragma once
